@@ -164,6 +164,9 @@ cfr_status build_layout(const cfr_game_desc *g, Layout &L, std::string &err) {
         std::vector<uint64_t> seq1((size_t)N), seq2((size_t)N);
         std::vector<uint64_t> iset_seq((size_t)I, 0);
         std::vector<uint8_t> iset_seen((size_t)I, 0);
+        std::vector<int32_t> last1((size_t)N, -1), last2((size_t)N, -1);
+        L.iset_seq.assign((size_t)I, -1);
+        L.opp_seq.assign((size_t)N, -1);
         pic[0] = 1.0; seq1[0] = 0; seq2[0] = 0;
         int32_t next = 1;
         for (int64_t k = 0; k < N; k++) {
@@ -174,7 +177,12 @@ cfr_status build_layout(const cfr_game_desc *g, Layout &L, std::string &err) {
             int32_t I_h = L.node_infoset[k];
             if (I_h >= 0) {
                 uint64_t own = t == CFR_NODE_P1 ? seq1[k] : seq2[k];
-                if (!iset_seen[I_h]) { iset_seen[I_h] = 1; iset_seq[I_h] = own; }
+                L.opp_seq[k] = t == CFR_NODE_P1 ? last2[k] : last1[k];
+                if (!iset_seen[I_h]) {
+                    iset_seen[I_h] = 1;
+                    iset_seq[I_h] = own;
+                    L.iset_seq[I_h] = t == CFR_NODE_P1 ? last1[k] : last2[k];
+                }
                 else if (iset_seq[I_h] != own) {
                     err = "not perfect recall: members of information set (key " + std::to_string(L.iset_key[I_h]) +
                           ") have different own-action histories";
@@ -185,6 +193,7 @@ cfr_status build_layout(const cfr_game_desc *g, Layout &L, std::string &err) {
                 int32_t ck = next++;
                 L.parent[ck] = (int32_t)k;
                 seq1[ck] = seq1[k]; seq2[ck] = seq2[k];
+                last1[ck] = last1[k]; last2[ck] = last2[k];
                 if (t == CFR_NODE_CHANCE) {
                     pic[ck] = pic[k] * g->chance_prob[g->child_begin[h] + a];
                 } else {
@@ -193,6 +202,7 @@ cfr_status build_layout(const cfr_game_desc *g, Layout &L, std::string &err) {
                     L.in_slot[ck] = q;
                     uint64_t &s = t == CFR_NODE_P1 ? seq1[ck] : seq2[ck];
                     s = mix(s ^ ((uint64_t)q + 1) * 0x100000001B3ull);
+                    (t == CFR_NODE_P1 ? last1 : last2)[ck] = q;
                 }
             }
             if (t == CFR_NODE_TERMINAL) {
@@ -382,6 +392,11 @@ cfr_status build_device_layout(const Layout &L, int kind, int group_actions, boo
             for (int32_t a = 0; a < L.slot_off[ci + 1] - L.slot_off[ci]; a++)
                 slot_map[L.slot_off[ci] + a] = D.slot_off[iset_dev[ci]] + a;
         if (pub) D.slot_canon_to_dev = slot_map; else D.slot_canon_to_dev.clear();
+        D.iset_seq.resize((size_t)I);
+        for (int64_t i = 0; i < I; i++) {
+            const int32_t q = L.iset_seq[iset_canon[i]];
+            D.iset_seq[i] = q >= 0 ? slot_map[q] : -1;
+        }
         // members ascending in device order
         D.mem_off.assign((size_t)I + 1, 0);
         for (int64_t x = 0; x < N; x++) {
@@ -390,6 +405,7 @@ cfr_status build_device_layout(const Layout &L, int kind, int group_actions, boo
         }
         for (int64_t i = 0; i < I; i++) D.mem_off[i + 1] += D.mem_off[i];
         D.mem_node.assign((size_t)L.Ndec, 0);
+        D.mem_seq.assign((size_t)L.Ndec, -1);
         {
             std::vector<int32_t> fill(D.mem_off.begin(), D.mem_off.end() - 1);
             for (int64_t x = 0; x < N; x++) {
@@ -397,7 +413,9 @@ cfr_status build_device_layout(const Layout &L, int kind, int group_actions, boo
                 if (ci >= 0) {
                     // bit 31 marks members of player-2 sets (kernels mask it off)
                     uint32_t tag = L.iset_player[ci] == CFR_NODE_P2 ? 0x80000000u : 0u;
-                    D.mem_node[fill[iset_dev[ci]]++] = (int32_t)((uint32_t)x | tag);
+                    const int32_t w = fill[iset_dev[ci]]++, q = L.opp_seq[inv[x]];
+                    D.mem_node[w] = (int32_t)((uint32_t)x | tag);
+                    if (q >= 0) D.mem_seq[w] = slot_map[q];
                 }
             }
         }
@@ -506,6 +524,37 @@ bool slot_child_offsets(const DeviceLayout &D, std::vector<int32_t> &koff) {
     }
     koff = std::move(out);
     return true;
+}
+
+void plan_reach(const DeviceLayout &D, std::vector<int32_t> &first, std::vector<int8_t> &walks) {
+    const int md = (int)D.iset_depth_off.size() - 2;
+    const int64_t I = (int64_t)D.slot_off.size() - 1;
+    std::vector<uint8_t> walk((size_t)(I > 0 ? D.slot_off[I] : 0), 0);   // per slot, within its launch
+    first.assign(1, 0);
+    walks.assign(1, 0);
+    int32_t S0 = 0;   // first slot of the launch being formed
+    for (int d = 0; d <= md; d++) {
+        const int32_t b = D.iset_depth_off[d], e = D.iset_depth_off[d + 1];
+        auto longest = [&]() {
+            int w = 0;
+            for (int32_t i = b; i < e; i++)
+                if (D.iset_seq[i] >= S0) w = std::max(w, walk[D.iset_seq[i]] + 1);
+            return w;
+        };
+        const int w = longest();
+        if (w > REACH_WALK || (w > 0 && D.slot_off[e] - D.slot_off[b] > REACH_WIDE)) {
+            first.push_back(d);
+            walks.push_back(0);
+            S0 = D.slot_off[b];
+        } else if (w > 0) {
+            walks.back() = 1;
+        }
+        for (int32_t i = b; i < e; i++) {
+            const int k = D.iset_seq[i] >= S0 ? walk[D.iset_seq[i]] + 1 : 0;
+            for (int32_t q = D.slot_off[i]; q < D.slot_off[i + 1]; q++) walk[q] = (uint8_t)k;
+        }
+    }
+    first.push_back(md + 1);
 }
 
 bool plan_persistent(const std::vector<int64_t> &nodes, int32_t wg_nodes, int32_t max_w, int n_queues,
@@ -642,6 +691,10 @@ cfr_status build_forest(std::vector<Layout> &Ls, std::vector<DeviceLayout> &Ds, 
             const int32_t i = slot_set[s][q];
             return F.slot_off[iset(s, i)] + (q - Ds[s].slot_off[i]);
         };
+        F.iset_seq.assign((size_t)I, -1);
+        for (int s = 0; s < n; s++)
+            for (int32_t i = 0; i < (int32_t)Ds[s].iset_seq.size(); i++)
+                if (Ds[s].iset_seq[i] >= 0) F.iset_seq[iset(s, i)] = slot(s, Ds[s].iset_seq[i]);
         // node arrays
         int64_t E = 0;
         for (int s = 0; s < n; s++) E += Ds[s].kid_off.back() - Ds[s].kid_off.front();
@@ -687,12 +740,14 @@ cfr_status build_forest(std::vector<Layout> &Ls, std::vector<DeviceLayout> &Ds, 
         }
         // members (player tag kept), groups, chance nodes
         F.mem_node.assign((size_t)F.mem_off[I], 0);
+        F.mem_seq.assign((size_t)F.mem_off[I], -1);
         for (int s = 0; s < n; s++) {
             const DeviceLayout &D = Ds[s];
             for (int32_t i = 0; i + 1 < (int32_t)D.mem_off.size(); i++) {
                 int32_t w = F.mem_off[iset(s, i)];
                 for (int32_t k = D.mem_off[i]; k < D.mem_off[i + 1]; k++) {
                     const uint32_t tag = (uint32_t)D.mem_node[k] & 0x80000000u;
+                    if (D.mem_seq[k] >= 0) F.mem_seq[w] = slot(s, D.mem_seq[k]);
                     F.mem_node[w++] = (int32_t)((uint32_t)node(s, D.mem_node[k] & 0x7fffffff) | tag);
                 }
             }

@@ -33,6 +33,9 @@ struct Layout {
     std::vector<int8_t> iset_player;     // [I]
     std::vector<int64_t> iset_key;       // [I]
     std::vector<int32_t> iset_depth_off; // [max_depth + 2] infosets whose members sit at depth d
+    // sequences: the slot of the last action a player took on the way to a node, -1 before the first
+    std::vector<int32_t> iset_seq;       // [I] the acting player's (one for all members: perfect recall)
+    std::vector<int32_t> opp_seq;        // [N] at decision nodes, the other player's; -1 elsewhere
     std::vector<int64_t> public_key;     // [N] canonical order, empty if not given
     // set before build_layout to keep the canonical -> input node map (in-place re-solve support)
     bool keep_maps = false;
@@ -70,6 +73,8 @@ struct DeviceLayout {
     std::vector<int32_t> node_slot;      // [N] first device slot of a decision node, -1 otherwise
     std::vector<int32_t> node_iset;      // [N] device information set, -1 otherwise
     std::vector<int32_t> slot_off, mem_off, mem_node;
+    std::vector<int32_t> iset_seq;       // [I] device slot of the acting player's last own action, -1 if none
+    std::vector<int32_t> mem_seq;        // [Ndec] aligned with mem_node: the other player's last slot, -1 if none
     std::vector<int8_t> iset_player;
     std::vector<int32_t> iset_depth_off; // [max_depth + 2]
     std::vector<float> tmpl;             // [N]
@@ -134,6 +139,17 @@ inline int32_t choose_group_sets(int64_t g128, int64_t g256) { return g128 * 10 
 // games have this property: the members of a set lie in one public-state block and the child
 // block of an action keeps the block's node order.
 bool slot_child_offsets(const DeviceLayout &D, std::vector<int32_t> &koff);
+
+// Launches of the reach pass.  The reach of a slot is its parent slot's reach times its strategy, so
+// slots whose parents lie in an earlier launch need one lookup, and slots whose parents lie in their own
+// launch walk up to it.  `first` holds the first depth of each launch (ascending, then max_depth + 1), `walk` 1
+// for the launches that hold a slot and its parent.
+// A depth joins the launch of the depths above it while no walk gets longer than REACH_WALK, and, for a
+// depth of more than REACH_WIDE slots, only while it needs no walk at all: a step of a walk costs a
+// dependent load per slot, a launch about 3 us, so narrow depths share a launch and wide ones do not.
+constexpr int REACH_WALK = 8;
+constexpr int32_t REACH_WIDE = 1 << 18;
+void plan_reach(const DeviceLayout &D, std::vector<int32_t> &first, std::vector<int8_t> &walk);
 
 // Work plan of the persistent schedule.  Game g gets W_g = max(1, ceil(nodes_g / wg_nodes)) workgroups
 // ("ranks"); games are placed largest first on the least loaded of n_queues queues (one per XCD) and a

@@ -20,6 +20,10 @@ constexpr int32_t MEMBER_NODE_MASK = 0x7fffffff;
 constexpr int32_t MEMBER_P2 = (int32_t)0x80000000u;
 // fields per (game, depth) in game_range: node lo/hi, group lo/hi, chance lo/hi, big chance lo/hi
 constexpr int GR_FIELDS_DEV = 8;
+// slots per workgroup of a launch of the reach pass, by whether it walks
+constexpr int32_t reach_tile(bool walk) { return walk ? 256 : 1024; }
+// elements before seq[0] in its allocation: seq[-1] = 1, the reach of the empty sequence
+constexpr int32_t SEQ_FRONT = 64;
 // bound on one barrier wait, in seconds of the device's constant-rate clock: a stuck wait raises
 // the error flag (the launch then reports CFR_EDEVICE) instead of hanging.  A count of polls is no
 // time bound: under contention one acquire poll can take microseconds.
@@ -41,10 +45,11 @@ struct DevGame {
     int affine = 0;
     int32_t group_sets = 256;     // sets per update group (128 or 256): sizes the affine update's LDS rows
     int32_t *koff = nullptr;      // [A]   child offset of each slot (affine only)
-    // member node | MEMBER_P2 bit, per update group in set-major order, or in node order where that
+    // member node, per update group in set-major order, or in node order where that
     // touches far fewer cache lines (grp_perm[g] = 1; mpos then gives each member's set-major position
     // in its group) (affine only)
     int32_t *mnode = nullptr;     // [Ndec]
+    int32_t *mseq = nullptr;      // [Ndec] mem_seq in the order of mnode
     uint16_t *mpos = nullptr;     // [Ndec]
     int8_t *grp_perm = nullptr;   // [G]
     int32_t *slot_map = nullptr;  // [A]   canonical slot -> device slot (nullptr: identity)
@@ -54,6 +59,11 @@ struct DevGame {
     int32_t *mem_off = nullptr;   // [I+1]
     int2 *mem = nullptr;          // [Ndec]  members: (node | MEMBER_P2 bit, first edge of the node)
     int8_t *iset_player = nullptr;// [I]
+    // sequences: the slot of the acting player's last action before a set (before a slot's set), and of
+    // the other player's before a member (order of mem); -1 where there is none
+    int32_t *iset_seq = nullptr;  // [I]
+    int32_t *slot_par = nullptr;  // [A]
+    int32_t *mem_seq = nullptr;   // [Ndec]
     int32_t G = 0;                // update groups
     int32_t *grp_iset_off = nullptr; // [G+1]
     // host copies of per-depth ranges (launch parameters)
@@ -62,16 +72,16 @@ struct DevGame {
     int32_t *chance_node = nullptr;          // device: internal chance nodes by depth (small fan-out)
     const int32_t *bigc_off = nullptr;       // [max_depth+2] big-fan-out chance nodes of depth d
     int32_t *bigc_node = nullptr;            // device: chance nodes with fan-out above BIG_FANOUT
-    // batches with retired games (cfr_set_active): the work that still runs, per depth -- forward
-    // tiles (index within the depth's tiles), update groups, chance nodes and big chance nodes --
-    // listed on the device at [off[d], off[d] + cnt[d]) of each list (host offsets and counts);
+    // batches with retired games (cfr_set_active): the work that still runs -- per reach launch its tiles
+    // (index within the launch), per depth update groups, chance nodes and big chance nodes --
+    // listed on the device at [off[d], off[d + 1]) of each list (host offsets);
     // use_lists = 0 while every game iterates (the identity)
     int use_lists = 0;
-    int32_t *fwd_list = nullptr, *grp_list = nullptr, *chance_list = nullptr, *bigc_list = nullptr;
-    const int64_t *fwd_off = nullptr, *grp_off = nullptr, *chance_off_l = nullptr, *bigc_off_l = nullptr;
+    int32_t *reach_list = nullptr, *grp_list = nullptr, *chance_list = nullptr, *bigc_list = nullptr;
+    const int64_t *reach_off = nullptr, *grp_off = nullptr, *chance_off_l = nullptr, *bigc_off_l = nullptr;
     // iteration state, element type float or double (fp64)
     void *v = nullptr;            // [N]   player-1 chance-weighted values; terminals hold the template
-    void *reach = nullptr;        // [2N]  lane 0: player 1 reach, lane 1: player 2 reach
+    void *seq = nullptr;          // [A]   reach of each slot's sequence; seq[-1] = 1
     void *sigma = nullptr;        // [A]   current strategy
     void *R = nullptr;            // [A]   cumulative regrets
     void *pred = nullptr;         // [A]   PCFR+ prediction (the latest instantaneous regret), else nullptr
@@ -92,8 +102,9 @@ struct IterFlags {
     int upd;      // players whose sets a level updates: bit 0 player 1, bit 1 player 2
 };
 
-// one level of the forward reach pass: nodes [lo, hi) of one depth; tick != nullptr bumps the counter
-hipError_t launch_forward(const DevGame &g, int d, int32_t lo, int32_t hi, int32_t *tick, hipStream_t s);
+// launch k of the reach pass: slots [lo, hi), walk where some parents are among them; tick != nullptr
+// bumps the counter
+hipError_t launch_reach(const DevGame &g, int k, int32_t lo, int32_t hi, bool walk, int32_t *tick, hipStream_t s);
 // one level of the backward value pass fused with the update of the information sets on it
 // (regrets, clamp, average, regret matching of the next strategy)
 hipError_t launch_level(const DevGame &g, int d, IterFlags f, hipStream_t s);

@@ -2,9 +2,10 @@
 // best-response evaluator.
 //
 // Iteration (paper Algorithm 'alg:iteration', Table 'tab:opsteps'):
-//   forward  : per depth level, pi_i(c) = pi_i(parent) * (owner(parent) == i ? sigma(slot) : 1)
-//              (eqs. reach, lanes; chance multiplies by 1 because its probabilities
-//              live in the values template, eq. template)
+//   reach    : per slot, seq(I, a) = seq(last own slot before I) * sigma(I, a): the acting player's
+//              reach (eqs. reach, lanes) of every node whose last own slot is (I, a).  Chance and
+//              the other player multiply by 1, so a node's two reaches are those of two slots,
+//              and by perfect recall a set has one own reach.
 //   backward : per depth level, v(h) = sum_children m(c) v(c), m = sigma(slot) below decisions,
 //              1 below chance (eqs. cfv, opbwd); terminal entries of v hold the template and
 //              are never overwritten, so no per-iteration template copy is needed
@@ -24,6 +25,7 @@
 namespace cfrx {
 
 constexpr int BLOCK = 256;
+static_assert(reach_tile(true) % BLOCK == 0 && reach_tile(false) % BLOCK == 0, "slots per thread of k_reach");
 // one thread per set of an update group; uint8 member-to-set indices
 static_assert(GROUP_SETS_MAX <= BLOCK && GROUP_SETS_MAX <= 256, "update group sets");
 
@@ -41,22 +43,43 @@ __device__ __forceinline__ int32_t child_of(const int32_t *__restrict__ kid, int
     else return edge;
 }
 
-// Forward reach of one node c (eqs. reach, lanes): both lanes copy the parent's reach; the lane of
-// the parent's owner multiplies by sigma(slot).  Terminals carry no reach.
+// The reach of the sequence that ends in slot p: the strategies along it multiplied from the root on,
+// as ((1 * s1) * s2) * ....  Slots below S0 are finished (seq holds their reach; seq[-1] = 1 is the empty
+// sequence); above, the walk collects the strategies on the way up.  Walks of at most REACH_WALK slots
+// stay in registers; a longer one looks every strategy up from the bottom again.
 template <typename T>
-__device__ __forceinline__ void forward_node(int32_t c, const int2 *__restrict__ up, const T *__restrict__ sigma,
-                                             T *__restrict__ r1, T *__restrict__ r2) {
-    const int2 u = up[c];
-    if (!(u.y & CODE_INTERNAL)) return;
-    const int owner = u.y & CODE_OWNER_MASK;
-    const T s = owner ? sigma[u.y >> CODE_SLOT_SHIFT] : T(1);
-    const T a = r1[u.x], b = r2[u.x];
-    r1[c] = owner == 1 ? a * s : a;
-    r2[c] = owner == 2 ? b * s : b;
+__device__ __forceinline__ T seq_reach(int32_t p, int32_t S0, const int32_t *slot_par, const T *sigma, const T *seq) {
+    T s[REACH_WALK];
+    int n = 0;
+    const int32_t p0 = p;
+#pragma unroll
+    for (int k = 0; k < REACH_WALK; k++) {
+        s[k] = T(1);
+        if (p >= S0) {
+            s[k] = sigma[p];
+            p = slot_par[p];
+            n = k + 1;
+        }
+    }
+    if (p >= S0) {
+        while (p >= S0) {
+            p = slot_par[p];
+            n++;
+        }
+        T acc = seq[p];
+        for (int k = n - 1; k >= 0; k--) {
+            int32_t x = p0;
+            for (int j = 0; j < k; j++) x = slot_par[x];
+            acc = acc * sigma[x];
+        }
+        return acc;
+    }
+    T acc = seq[p];
+#pragma unroll
+    for (int k = REACH_WALK - 1; k >= 0; k--)
+        if (k < n) acc = acc * s[k];
+    return acc;
 }
-
-// nodes per thread of k_forward
-constexpr int FWD_NPT = 4;
 
 // XCD-aware tile order.  The dispatcher hands the workgroups of a launch to the 8 XCDs in turn
 // (workgroup b to XCD b mod 8) and each XCD has its own L2, so neighbouring tiles -- which share
@@ -76,40 +99,40 @@ __device__ __forceinline__ int32_t xcd_tile(int32_t b, int32_t n) {
     return i / XCD_RUN * (8 * XCD_RUN) + x * XCD_RUN + i % XCD_RUN;
 }
 
-// One forward level, FWD_NPT nodes per thread (strided by the block size, so each wave's accesses
-// stay contiguous): all edge codes are loaded first, then all parent reaches and strategies, with
-// the strategy load unconditional (chance parents carry slot 0, a valid address) and only the
-// stores masked, so a thread keeps every load of its nodes in flight together.
-template <typename T>
-__global__ void __launch_bounds__(BLOCK) k_forward(int32_t lo, int32_t hi, const int2 *__restrict__ up,
-                                                   const T *__restrict__ sigma, T *__restrict__ r1,
-                                                   T *__restrict__ r2, int32_t *tick,
-                                                   const int32_t *__restrict__ tiles) {
+// The reach of slots [lo, hi), SPT per thread (strided by the block size, so each wave's accesses stay
+// contiguous).  Bound by memory: 12 bytes per slot in FP32, and the parents' reaches, which siblings and
+// neighbouring sets share.  WALK launches hold depths that depend on one another (plan_reach) and are
+// narrow, bound by the latency of the walk: one slot per thread, so that the walks of more waves
+// overlap.  Measured, FP32: 220M-node card game, 5 launches, 28.0M slots in 0.085 ms (5.3 TB/s); a pass
+// over the 76M internal nodes, a launch per depth, took 0.30 ms.  26-card Leduc, one launch of 45,864
+// slots instead of ten over its nodes: an iteration 93 -> 69 us.
+template <typename T, bool WALK>
+__global__ void __launch_bounds__(BLOCK) k_reach(int32_t lo, int32_t hi, int32_t S0,
+                                                 const int32_t *__restrict__ slot_par, const T *__restrict__ sigma,
+                                                 T *seq, int32_t *tick, const int32_t *__restrict__ tiles) {
+    constexpr int SPT = reach_tile(WALK) / BLOCK;
     if (tick && blockIdx.x == 0 && threadIdx.x == 0) tick[0] += 1;
     if (hi <= lo) return;
     // with retired games only the listed tiles run (a tile shared with a retired game rewrites that
     // game's reach with the same values: its strategy no longer changes)
-    const int32_t x = xcd_tile((int32_t)blockIdx.x, (int32_t)gridDim.x);
-    const int32_t tile = tiles ? tiles[x] : x;
-    const int32_t base = lo + tile * (BLOCK * FWD_NPT) + (int32_t)threadIdx.x;
-    int2 u[FWD_NPT];
+    const int32_t tile = tiles ? tiles[blockIdx.x] : (int32_t)blockIdx.x;
+    const int32_t base = lo + tile * (BLOCK * SPT) + (int32_t)threadIdx.x;
+    int32_t p[SPT];
+    T sv[SPT], up[SPT];
 #pragma unroll
-    for (int i = 0; i < FWD_NPT; i++) u[i] = up[min(base + i * BLOCK, hi - 1)];
-    T sv[FWD_NPT], a[FWD_NPT], b[FWD_NPT];
-#pragma unroll
-    for (int i = 0; i < FWD_NPT; i++) {
-        sv[i] = sigma[u[i].y >> CODE_SLOT_SHIFT];
-        a[i] = r1[u[i].x];
-        b[i] = r2[u[i].x];
+    for (int i = 0; i < SPT; i++) {
+        const int32_t q = min(base + i * BLOCK, hi - 1);
+        p[i] = slot_par[q];
+        sv[i] = sigma[q];
     }
 #pragma unroll
-    for (int i = 0; i < FWD_NPT; i++) {
-        const int32_t c = base + i * BLOCK;
-        if (c >= hi || !(u[i].y & CODE_INTERNAL)) continue;
-        const int owner = u[i].y & CODE_OWNER_MASK;
-        r1[c] = owner == 1 ? a[i] * sv[i] : a[i];
-        r2[c] = owner == 2 ? b[i] * sv[i] : b[i];
+    for (int i = 0; i < SPT; i++) {
+        if constexpr (WALK) up[i] = seq_reach<T>(p[i], S0, slot_par, sigma, seq);
+        else up[i] = seq[p[i]];
     }
+#pragma unroll
+    for (int i = 0; i < SPT; i++)
+        if (base + i * BLOCK < hi) seq[base + i * BLOCK] = up[i] * sv[i];
 }
 
 // Arrays read and written by the backward/update level.
@@ -120,11 +143,14 @@ struct LevelArgs {
     const int8_t *iset_player;
     const int32_t *kid_off, *kid, *chance_node, *bigc_node;
     const int32_t *grp_list, *chance_list, *bigc_list;   // batches with retired games (nullptr: all)
+    const int32_t *iset_seq, *slot_par;  // last own slot before a set, and before the set of a slot
+    const int32_t *mem_seq;        // the other player's last slot before each member (order of mem)
     const int32_t *koff, *mnode;   // affine layouts: per-slot child offset, compact member list
+    const int32_t *mseq;           // affine layouts: mem_seq in the order of mnode
     const uint16_t *mpos;          // affine layouts: set-major position of each member of a node-order group
     const int8_t *grp_perm;        // affine layouts: 1 where a group's member list is in node order
     T *v;
-    T *r1, *r2;   // reach lanes (the level only reads them; the persistent form's forward levels write)
+    T *seq;       // reach of every slot's sequence; seq[-1] = 1
     T *R;
     double *sbar;
     T *sigma;
@@ -418,7 +444,7 @@ __device__ void group_update(int32_t g, const RuleArgs &ru, const LevelArgs<T> &
             na[u] = L.slot[lo + 1] - sb[u];
             const int2 x = a.mem[m];
             hh[u] = x.x & MEMBER_NODE_MASK;
-            po[u] = ((x.x & MEMBER_P2) ? a.r1 : a.r2)[hh[u]];
+            po[u] = a.seq[a.mem_seq[m]];
 #pragma unroll
             for (int k = 0; k < MAXA; k++) {
                 const int32_t kk = min(k, na[u] - 1);
@@ -445,8 +471,7 @@ __device__ void group_update(int32_t g, const RuleArgs &ru, const LevelArgs<T> &
     if (!has_set) return;
     // alternating order: the other player's half leaves this set's state alone (values only)
     if (!((ru.upd >> (pl - 1)) & 1)) return;
-    const T *own = pl == 1 ? a.r1 : a.r2;
-    set_update<T, MAXA, EXT>(ru, a, s0, nA, pl, (double)own[a.mem[m0].x & MEMBER_NODE_MASK], r);
+    set_update<T, MAXA, EXT>(ru, a, s0, nA, pl, (double)a.seq[a.iset_seq[i0 + tid]], r);
 }
 
 // LDS staging of one update group in an affine layout: the slot offsets of its sets, the set of each
@@ -490,7 +515,9 @@ __device__ __forceinline__ void with_action_bound(int32_t n, F &&f) {
 // loads are issued.  The vector-memory pipeline (address and data units at ~90 % busy) bounds
 // this pass, so the per-slot child offsets and strategy, the same for every member of a set, are
 // loaded once per set (by its thread, into an LDS row) instead of once per member; a member then
-// loads only its record, its opponent reach and its child values.  Loads are unconditional: past
+// loads only its record, its opponent reach and its child values.  The opponent's reach is that of his
+// last sequence, which the members of his sets there share: a gather from a compact per-slot array
+// through a 4-byte index per member.  Loads are unconditional: past
 // a set's last action they repeat its last child (an address already read), lanes past the
 // chunk's end repeat its first member, so a chunk's loads are in flight together; only stores
 // and arithmetic are masked.  (A guard that skips a load no lane needs compiles to a branch with
@@ -502,7 +529,7 @@ __device__ __forceinline__ void with_action_bound(int32_t n, F &&f) {
 // each one's set-major position: consecutive lanes then touch consecutive nodes, children and values
 // instead of one cache line each, and the staging stays set-major, so the reduction, and every
 // result, is unchanged.  The two orders are separate instantiations of the member pass, chosen per
-// group.  Each set thread fetches its own reach through its first member.
+// group.
 template <typename T, int MAXA, int MPT, bool EXT, int GS>
 __device__ void group_update_affine(int32_t g, const RuleArgs &ru, const LevelArgs<T> &a,
                                     GroupLdsA<T, MAXA, MPT, GS> &L) {
@@ -518,13 +545,8 @@ __device__ void group_update_affine(int32_t g, const RuleArgs &ru, const LevelAr
     const int32_t s0 = a.slot_off[ti], nA = a.slot_off[ti + 1] - s0;
     const int pl = a.iset_player[ti];
     const bool perm = a.grp_perm[g] != 0;
-    // the set's first member: in a set-major list at m0 (lines the member pass reads anyway; the
-    // 8-byte member records would cost one extra line per set); in a node-order list, from them
-    int32_t h0;
-    if (perm) h0 = a.mem[m0].x & MEMBER_NODE_MASK;
-    else h0 = a.mnode[m0] & MEMBER_NODE_MASK;
-    const T *__restrict__ r1 = a.r1;
-    const T *__restrict__ r2 = a.r2;
+    const T *__restrict__ seq = a.seq;
+    const int32_t sq = a.iset_seq[ti];
     const T *__restrict__ sig = a.sigma;
     const int32_t *__restrict__ koff = a.koff;
     // the widest set of this wave, then (after the barrier) of the group
@@ -566,7 +588,7 @@ __device__ void group_update_affine(int32_t g, const RuleArgs &ru, const LevelAr
     int32_t ga = 0;
 #pragma unroll
     for (int w = 0; w < BLOCK / 64; w++) ga = max(ga, L.wmax[w]);
-    const T pown = (pl == 1 ? r1 : r2)[h0];
+    const T pown = seq[sq];
     T r[MAXA];
 #pragma unroll
     for (int k = 0; k < MAXA; k++) r[k] = T(0);
@@ -576,7 +598,7 @@ __device__ void group_update_affine(int32_t g, const RuleArgs &ru, const LevelAr
         for (int32_t cb = mbeg; cb < mend; cb += CHUNK) {
             const int32_t ce = min(cb + CHUNK, mend);
             bool in[MPT];
-            int32_t hn[MPT], pj[MPT], st[MPT], sb[MPT], na[MPT];
+            int32_t hn[MPT], ms[MPT], pj[MPT], st[MPT], sb[MPT], na[MPT];
 #pragma unroll
             for (int u = 0; u < MPT; u++) {
                 const int32_t j = u * BLOCK + tid;
@@ -585,6 +607,7 @@ __device__ void group_update_affine(int32_t g, const RuleArgs &ru, const LevelAr
                 // thread j takes the group's j-th listed member; in a node-order group pj is its
                 // slot in the set-major staging
                 hn[u] = a.mnode[cb + jj];
+                ms[u] = a.mseq[cb + jj];
                 if constexpr (PERM) pj[u] = a.mpos[cb + jj];
                 else pj[u] = jj;
                 st[u] = L.mset[pj[u]];
@@ -594,8 +617,8 @@ __device__ void group_update_affine(int32_t g, const RuleArgs &ru, const LevelAr
             T po[MPT], cv[MPT][NA], sg[MPT][ROWS ? 1 : NA];
 #pragma unroll
             for (int u = 0; u < MPT; u++) {
-                const int32_t h = hn[u] & MEMBER_NODE_MASK;
-                po[u] = ((hn[u] & MEMBER_P2) ? r1 : r2)[h];
+                const int32_t h = hn[u];
+                po[u] = seq[ms[u]];
                 int32_t ko[NA];
 #pragma unroll
                 for (int k = 0; k < NA; k++) {
@@ -622,7 +645,7 @@ __device__ void group_update_affine(int32_t g, const RuleArgs &ru, const LevelAr
                 }
                 if (!in[u]) continue;
                 const int32_t j = pj[u];
-                a.v[hn[u] & MEMBER_NODE_MASK] = vh;
+                a.v[hn[u]] = vh;
                 L.po[j] = po[u];
 #pragma unroll
                 for (int k = 0; k < NA; k++) L.diff[j * MAXA + k] = cv[u][k] - vh;
@@ -767,14 +790,14 @@ __device__ __forceinline__ bool game_barrier(int32_t *ctr, int32_t W, int32_t &e
 }
 
 // The work of one (game, rank): n_iter whole iterations of game gm as rank `rank` of its W workgroups,
-// which stride over each forward level's nodes and each backward level's update groups and chance
+// which stride over the game's slots (reach) and over each backward level's update groups and chance
 // nodes and meet at the game's barrier between levels.  Iteration t0 + k (k = 1..n_iter) uses the
 // same arithmetic, in the same order per set, as the level-synchronous kernels.  Returns false once
 // a barrier reported an error.
 template <typename T, int MAXA, int MPT, bool EXPLICIT, bool EXT, int AF>
 __device__ bool persistent_game(int32_t gm, int32_t rank, int32_t W, const int32_t *__restrict__ game_range,
                                 const int32_t *__restrict__ game_depth, int32_t MD, int32_t n_iter,
-                                const int2 *__restrict__ up, const LevelArgs<T> &a, int32_t t0, int32_t *barrier,
+                                const LevelArgs<T> &a, int32_t t0, int32_t *barrier,
                                 int32_t *err, int64_t timeout_ticks, int rule, int linear, int alternating,
                                 LevelLds<T, MAXA, MPT, EXPLICIT, AF> &L) {
     const int32_t *gr = game_range + (size_t)gm * (MD + 1) * GR_FIELDS_DEV;
@@ -785,12 +808,14 @@ __device__ bool persistent_game(int32_t gm, int32_t rank, int32_t W, const int32
     for (int32_t it = 1; it <= n_iter; it++) {
         for (int half = 0; half < halves; half++) {
             const RuleArgs ru = rule_args(rule, linear, alternating ? 1 << half : 3, t0 + it);
-            for (int32_t d = 1; d <= Ds; d++) {
-                const int32_t lo = gr[d * GR_FIELDS_DEV], hi = gr[d * GR_FIELDS_DEV + 1];
-                for (int32_t c = lo + rank * BLOCK + tid; c < hi; c += W * BLOCK)
-                    forward_node<T>(c, up, a.sigma, a.r1, a.r2);
-                if (!game_barrier(barrier + gm, W, epoch, err, timeout_ticks)) return false;
+            // every slot walks its whole sequence, so the pass needs no barrier between depths
+            for (int32_t d = 0; d < Ds; d++) {
+                const int32_t *r = gr + d * GR_FIELDS_DEV;
+                const int32_t lo = a.slot_off[a.grp_iset_off[r[2]]], hi = a.slot_off[a.grp_iset_off[r[3]]];
+                for (int32_t q = lo + rank * BLOCK + tid; q < hi; q += W * BLOCK)
+                    a.seq[q] = seq_reach<T>(a.slot_par[q], 0, a.slot_par, a.sigma, a.seq) * a.sigma[q];
             }
+            if (!game_barrier(barrier + gm, W, epoch, err, timeout_ticks)) return false;
             for (int32_t d = Ds - 1; d >= 0; d--) {
                 const int32_t *r = gr + d * GR_FIELDS_DEV;
                 for (int32_t g = r[2] + rank; g < r[3]; g += W) update_group<T, MAXA, MPT, EXPLICIT, EXT, AF>(g, ru, a, L);
@@ -814,7 +839,7 @@ template <typename T, int MAXA, int MPT, bool EXPLICIT, bool EXT, int AF>
 __global__ void __launch_bounds__(BLOCK) k_persistent(const int4 *__restrict__ tickets, const int32_t *__restrict__ q_off,
                                                       int32_t *claim, const int32_t *__restrict__ game_range,
                                                       const int32_t *__restrict__ game_depth, int32_t MD, int32_t n_iter,
-                                                      const int2 *__restrict__ up, LevelArgs<T> a,
+                                                      LevelArgs<T> a,
                                                       const int32_t *__restrict__ tcount, int32_t *barrier,
                                                       int32_t *err, int64_t timeout_ticks, int rule, int linear,
                                                       int alternating) {
@@ -833,7 +858,7 @@ __global__ void __launch_bounds__(BLOCK) k_persistent(const int4 *__restrict__ t
             __syncthreads();
             if (t >= qn) break;
             const int4 wt = tickets[qlo + t];
-            if (!persistent_game<T, MAXA, MPT, EXPLICIT, EXT, AF>(wt.x, wt.y, wt.z, game_range, game_depth, MD, n_iter, up,
+            if (!persistent_game<T, MAXA, MPT, EXPLICIT, EXT, AF>(wt.x, wt.y, wt.z, game_range, game_depth, MD, n_iter,
                                                                 a, t0, barrier, err, timeout_ticks, rule, linear,
                                                                 alternating, L))
                 return;
@@ -844,7 +869,7 @@ __global__ void __launch_bounds__(BLOCK) k_persistent(const int4 *__restrict__ t
 // ---- the LDS-resident schedule for tiny standalone games --------------------------------------
 //
 // One workgroup runs n_iter whole iterations of a game whose state fits in LDS: the values (with
-// the terminal template), both reach lanes, strategy, regrets, strategy sums and (PCFR+) the
+// the terminal template), the slots' reach, strategy, regrets, strategy sums and (PCFR+) the
 // prediction are staged in, every level of every iteration runs between block barriers, and the
 // state is written back at the end.  No launch per level and no trip to HBM inside the loop.  The
 // structure arrays stay in global memory (read-only and small, so cache-resident).  One thread
@@ -867,7 +892,7 @@ __device__ void set_serial(int32_t i, const RuleArgs &ru, const LevelArgs<T> &a)
     for (int32_t m = m0; m < m1; m++) {
         const int2 x = a.mem[m];
         const int32_t h = x.x & MEMBER_NODE_MASK;
-        const T po = ((x.x & MEMBER_P2) ? a.r1 : a.r2)[h];
+        const T po = a.seq[a.mem_seq[m]];
         T cv[MAXA];
 #pragma unroll
         for (int k = 0; k < MAXA; k++) cv[k] = a.v[child_of<EXPLICIT>(a.kid, x.y + min(k, nA - 1))];
@@ -879,12 +904,13 @@ __device__ void set_serial(int32_t i, const RuleArgs &ru, const LevelArgs<T> &a)
         for (int q = 0; q < MAXA; q++) r[q] = fma_t(po, cv[q] - vh, r[q]);
     }
     if (!((ru.upd >> (pl - 1)) & 1)) return;
-    const T *own = pl == 1 ? a.r1 : a.r2;
-    set_update<T, MAXA, EXT>(ru, a, s0, nA, pl, (double)own[a.mem[m0].x & MEMBER_NODE_MASK], r);
+    set_update<T, MAXA, EXT>(ru, a, s0, nA, pl, (double)a.seq[a.iset_seq[i]], r);
 }
 
-// Dynamic LDS of k_lds: strategy sums (double) first, then v, r1, r2 [N] and sigma, R (and the
-// PCFR+ prediction) [A] in the state type, then BLOCK reduction slots for big chance nodes.
+// The LDS a game is admitted by: strategy sums (double), then values and two words per node and
+// strategy, regrets (and the PCFR+ prediction) per slot in the state type, then BLOCK reduction slots
+// for big chance nodes.  k_lds uses less: instead of the two words per node it keeps A + 1 for the
+// slots' reach (a game has fewer slots than nodes).
 size_t lds_schedule_bytes(int32_t N, int32_t A, int fp64, int pred) {
     const size_t es = fp64 ? 8 : 4;
     return 8 * (size_t)A + es * (3 * (size_t)N + (pred ? 3 : 2) * (size_t)A + BLOCK);
@@ -892,21 +918,18 @@ size_t lds_schedule_bytes(int32_t N, int32_t A, int fp64, int pred) {
 
 template <typename T, int MAXA, bool EXPLICIT, bool EXT>
 __global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, int32_t D, int32_t N, int32_t A,
-                                               int32_t n_iter, const int2 *__restrict__ up, LevelArgs<T> g,
+                                               int32_t n_iter, LevelArgs<T> g,
                                                const int32_t *__restrict__ tcount, int rule, int linear,
                                                int alternating) {
     extern __shared__ __align__(16) unsigned char smem[];
     double *sb = reinterpret_cast<double *>(smem);
     T *v = reinterpret_cast<T *>(sb + A);
-    T *r1 = v + N, *r2 = r1 + N, *sig = r2 + N, *R = sig + A;
+    T *seq = v + N + 1, *sig = seq + A, *R = sig + A;   // seq[-1] = 1
     T *pred = g.pred ? R + A : nullptr;
     T *red = R + A + (g.pred ? A : 0);
     const int tid = threadIdx.x;
-    for (int32_t i = tid; i < N; i += BLOCK) {
-        v[i] = g.v[i];
-        r1[i] = g.r1[i];
-        r2[i] = g.r2[i];
-    }
+    for (int32_t i = tid; i < N; i += BLOCK) v[i] = g.v[i];
+    if (tid == 0) seq[-1] = T(1);
     for (int32_t q = tid; q < A; q += BLOCK) {
         sb[q] = g.sbar[q];
         sig[q] = g.sigma[q];
@@ -915,17 +938,15 @@ __global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, i
     }
     __syncthreads();
     LevelArgs<T> a = g;
-    a.v = v; a.r1 = r1; a.r2 = r2; a.sigma = sig; a.R = R; a.sbar = sb; a.pred = pred;
+    a.v = v; a.seq = seq; a.sigma = sig; a.R = R; a.sbar = sb; a.pred = pred;
     const int32_t t0 = tcount[0];
     const int halves = alternating ? 2 : 1;
     for (int32_t it = 1; it <= n_iter; it++) {
         for (int half = 0; half < halves; half++) {
             const RuleArgs ru = rule_args(rule, linear, alternating ? 1 << half : 3, t0 + it);
-            for (int32_t d = 1; d <= D; d++) {
-                const int32_t lo = gr[d * GR_FIELDS_DEV], hi = gr[d * GR_FIELDS_DEV + 1];
-                for (int32_t c = lo + tid; c < hi; c += BLOCK) forward_node<T>(c, up, sig, r1, r2);
-                __syncthreads();
-            }
+            for (int32_t q = tid; q < A; q += BLOCK)
+                seq[q] = seq_reach<T>(a.slot_par[q], 0, a.slot_par, sig, seq) * sig[q];
+            __syncthreads();
             for (int32_t d = D - 1; d >= 0; d--) {
                 const int32_t *r = gr + d * GR_FIELDS_DEV;
                 const int32_t ib = a.grp_iset_off[r[2]], ie = a.grp_iset_off[r[3]];
@@ -936,11 +957,7 @@ __global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, i
             }
         }
     }
-    for (int32_t i = tid; i < N; i += BLOCK) {
-        g.v[i] = v[i];
-        g.r1[i] = r1[i];
-        g.r2[i] = r2[i];
-    }
+    for (int32_t i = tid; i < N; i += BLOCK) g.v[i] = v[i];
     for (int32_t q = tid; q < A; q += BLOCK) {
         g.sbar[q] = sb[q];
         g.sigma[q] = sig[q];
@@ -1114,24 +1131,27 @@ __global__ void __launch_bounds__(BLOCK) k_br_backward(int32_t lo, int32_t hi, c
 // ---- launchers ------------------------------------------------------------
 
 template <typename T>
-static hipError_t forward_t(const DevGame &g, int32_t lo, int32_t hi, int32_t *tick, const int32_t *fwd_tiles,
-                           int64_t n_tiles, hipStream_t s) {
-    T *r = (T *)g.reach;
+static hipError_t reach_t(const DevGame &g, int32_t lo, int32_t hi, bool walk, int32_t *tick, const int32_t *tiles,
+                          int64_t n_tiles, hipStream_t s) {
     // one block still runs the counter bump
-    if (fwd_tiles && n_tiles == 0) hi = lo;
-    const unsigned blocks = hi <= lo ? 1u : fwd_tiles ? (unsigned)n_tiles
-                                                       : (unsigned)((hi - lo + BLOCK * FWD_NPT - 1) / (BLOCK * FWD_NPT));
-    hipLaunchKernelGGL(k_forward<T>, dim3(blocks), dim3(BLOCK), 0, s, lo, hi, g.up, (const T *)g.sigma, r,
-                       r + g.N, tick, fwd_tiles);
+    if (tiles && n_tiles == 0) hi = lo;
+    const int32_t tile = reach_tile(walk);
+    const unsigned blocks = hi <= lo ? 1u : tiles ? (unsigned)n_tiles : (unsigned)(((int64_t)hi - lo + tile - 1) / tile);
+    if (walk)
+        hipLaunchKernelGGL((k_reach<T, true>), dim3(blocks), dim3(BLOCK), 0, s, lo, hi, lo, g.slot_par,
+                           (const T *)g.sigma, (T *)g.seq, tick, tiles);
+    else
+        hipLaunchKernelGGL((k_reach<T, false>), dim3(blocks), dim3(BLOCK), 0, s, lo, hi, lo, g.slot_par,
+                           (const T *)g.sigma, (T *)g.seq, tick, tiles);
     return hipGetLastError();
 }
 
-hipError_t launch_forward(const DevGame &g, int d, int32_t lo, int32_t hi, int32_t *tick, hipStream_t s) {
+hipError_t launch_reach(const DevGame &g, int k, int32_t lo, int32_t hi, bool walk, int32_t *tick, hipStream_t s) {
     if (hi <= lo && !tick) return hipSuccess;
-    const int32_t *tiles = g.use_lists ? g.fwd_list + g.fwd_off[d] : nullptr;
-    const int64_t nt = g.use_lists ? g.fwd_off[d + 1] - g.fwd_off[d] : 0;
+    const int32_t *tiles = g.use_lists ? g.reach_list + g.reach_off[k] : nullptr;
+    const int64_t nt = g.use_lists ? g.reach_off[k + 1] - g.reach_off[k] : 0;
     if (g.use_lists && nt == 0 && !tick) return hipSuccess;
-    return g.fp64 ? forward_t<double>(g, lo, hi, tick, tiles, nt, s) : forward_t<float>(g, lo, hi, tick, tiles, nt, s);
+    return g.fp64 ? reach_t<double>(g, lo, hi, walk, tick, tiles, nt, s) : reach_t<float>(g, lo, hi, walk, tick, tiles, nt, s);
 }
 
 template <typename T>
@@ -1140,13 +1160,13 @@ static LevelArgs<T> level_args(const DevGame &g) {
     a.grp_iset_off = g.grp_iset_off; a.slot_off = g.slot_off; a.mem_off = g.mem_off; a.mem = g.mem;
     a.iset_player = g.iset_player; a.kid_off = g.kid_off; a.kid = g.kid; a.chance_node = g.chance_node;
     a.bigc_node = g.bigc_node;
+    a.iset_seq = g.iset_seq; a.slot_par = g.slot_par; a.mem_seq = g.mem_seq; a.mseq = g.mseq;
     a.koff = g.koff; a.mnode = g.mnode; a.mpos = g.mpos; a.grp_perm = g.grp_perm;
     a.grp_list = g.use_lists ? g.grp_list : nullptr;
     a.chance_list = g.use_lists ? g.chance_list : nullptr;
     a.bigc_list = g.use_lists ? g.bigc_list : nullptr;
     a.v = (T *)g.v;
-    a.r1 = (T *)g.reach;
-    a.r2 = (T *)g.reach + g.N;
+    a.seq = (T *)g.seq;
     a.R = (T *)g.R; a.sbar = g.sbar; a.sigma = (T *)g.sigma;
     a.pred = (T *)g.pred;
     return a;
@@ -1217,7 +1237,7 @@ struct PersistentLaunch {
     template <typename T, int MAXA, int MPT, bool EX, bool XT, int AF>
     hipError_t operator()() const {
         hipLaunchKernelGGL((k_persistent<T, MAXA, MPT, EX, XT, AF>), dim3(p.blocks), dim3(BLOCK), 0, s, p.tickets,
-                           p.q_off, p.claim, p.game_range, p.game_depth, p.max_depth, T_, g.up, level_args<T>(g), g.t,
+                           p.q_off, p.claim, p.game_range, p.game_depth, p.max_depth, T_, level_args<T>(g), g.t,
                            p.barrier, p.err, p.timeout_ticks, f.rule, f.linear, alt);
         return hipGetLastError();
     }
@@ -1249,7 +1269,7 @@ struct LdsLaunch {
             if (prepare)
                 return hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-            hipLaunchKernelGGL(fn, dim3(1), dim3(BLOCK), bytes, s, gr, g.max_depth, g.N, g.A, T_, g.up,
+            hipLaunchKernelGGL(fn, dim3(1), dim3(BLOCK), bytes, s, gr, g.max_depth, g.N, g.A, T_,
                                level_args<T>(g), g.t, f.rule, f.linear, alt);
             return hipGetLastError();
         }

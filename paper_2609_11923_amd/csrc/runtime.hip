@@ -2,7 +2,7 @@
 // declared in include/cfr.h.
 //
 // One iteration is a fixed sequence of launches (paper Proposition 3 (iii):
-// c1 + c2 D operations): D forward levels (the first also bumps the device
+// c1 + c2 D operations): the reach pass (its first launch also bumps the device
 // iteration counter), D backward levels and one fused update.  The first
 // cfr_iterate call runs one iteration with direct launches, then captures
 // the body once into a hipGraph (k iterations per graph optional) and replays
@@ -54,8 +54,11 @@ struct cfr_handle {
     DevGame g{};
     // host copies of the schedule
     std::vector<int32_t> depth_off, int_end, iset_depth_off, grp_depth_off, chance_off, bigc_off;
-    // the static launch schedule of one iteration: (kind, depth), kind 0 tick, 1 forward, 2 level,
-    // plus HALF for the second (player 2) half of an alternating iteration
+    // launch k of the reach pass: slots [reach_slot[k], reach_slot[k + 1]), reach_walk[k] (plan_reach)
+    std::vector<int32_t> reach_slot;
+    std::vector<int8_t> reach_walk;
+    // the static launch schedule of one iteration: (kind, index), kind 0 tick, 1 reach (launch of the
+    // pass), 2 level (depth), plus HALF for the second (player 2) half of an alternating iteration
     std::vector<std::pair<int, int>> plan;
     std::vector<int32_t> slot_map;     // canonical slot -> device slot (empty: identity)
     // batches: number of games, canonical slot offsets, per-game depth and ranges, pots
@@ -84,12 +87,12 @@ struct cfr_handle {
     double pot = 1.0;
     int64_t device_bytes = 0;
     std::vector<double> perm_members;  // per depth: members of update groups listed in node order
-    // batches: per-game activity (cfr_set_active); each depth's forward tiles (first tile per depth,
-    // each tile's first and last game) and the lists of the work that still runs, per depth
+    // batches: per-game activity (cfr_set_active); the tiles of the reach launches (first tile per launch,
+    // each tile's first and last game) and the lists of the work that still runs
     std::vector<int8_t> active;
-    std::vector<int64_t> fwd_tile_base;
-    std::vector<int2> fwd_games;
-    std::vector<int64_t> fwd_off, grp_off, chance_off_l, bigc_off_l;
+    std::vector<int64_t> reach_tile_base;
+    std::vector<int2> reach_games;
+    std::vector<int64_t> reach_off, grp_off, chance_off_l, bigc_off_l;
     bool any_inactive = false;
     int32_t node_order_groups = 0;
     int64_t node_order_members = 0;
@@ -160,10 +163,11 @@ static void parallel_games(int n, F &&fn) {
 // perm[g] and mpos gives each listed member's set-major position in its group (groups of several
 // sets hold at most one staging chunk, so it fits 16 bits).  perm_members[d] counts the members of
 // flagged groups of depth d (their extra position reads are design bytes).
-static void member_lists(const DeviceLayout &D, std::vector<int32_t> &mnode, std::vector<uint16_t> &mpos,
-                         std::vector<int8_t> &perm, std::vector<double> &perm_members) {
+static void member_lists(const DeviceLayout &D, std::vector<int32_t> &mnode, std::vector<int32_t> &mseq,
+                         std::vector<uint16_t> &mpos, std::vector<int8_t> &perm, std::vector<double> &perm_members) {
     const int64_t Ndec = (int64_t)D.mem_node.size();
     mnode = D.mem_node;
+    mseq = D.mem_seq;
     mpos.assign((size_t)Ndec, 0);
     const int32_t G = (int32_t)D.grp_iset_off.size() - 1;
     perm.assign((size_t)std::max(G, 1), 0);
@@ -189,7 +193,10 @@ static void member_lists(const DeviceLayout &D, std::vector<int32_t> &mnode, std
         for (int32_t g = task * SPAN; g < std::min(G, (task + 1) * SPAN); g++) {
             const int32_t i0 = D.grp_iset_off[(size_t)g], i1 = D.grp_iset_off[(size_t)g + 1];
             const int32_t mb = D.mem_off[(size_t)i0], me = D.mem_off[(size_t)i1], n = me - mb;
-            for (int32_t k = 0; k < n; k++) mpos[(size_t)(mb + k)] = (uint16_t)(k & 0xffff);
+            for (int32_t k = 0; k < n; k++) {
+                mpos[(size_t)(mb + k)] = (uint16_t)(k & 0xffff);
+                mnode[(size_t)(mb + k)] &= MEMBER_NODE_MASK;
+            }
             if (i1 - i0 == 1) continue;
             const int32_t *list = D.mem_node.data() + mb;
             idx.resize((size_t)n);
@@ -202,7 +209,8 @@ static void member_lists(const DeviceLayout &D, std::vector<int32_t> &mnode, std
             if (2 * spans(sorted_nodes.data(), n) > spans(list, n)) continue;
             perm[(size_t)g] = 1;
             for (int32_t k = 0; k < n; k++) {
-                mnode[(size_t)(mb + k)] = sorted_nodes[(size_t)k];
+                mnode[(size_t)(mb + k)] = sorted_nodes[(size_t)k] & MEMBER_NODE_MASK;
+                mseq[(size_t)(mb + k)] = D.mem_seq[(size_t)(mb + idx[(size_t)k])];
                 mpos[(size_t)(mb + k)] = (uint16_t)idx[(size_t)k];
             }
         }
@@ -247,13 +255,13 @@ cfr_status upload(T *dst, const std::vector<T> &src) {
 // address only; no kernel or copy ever sees a shifted pointer.
 std::vector<const void *> persistent_ptrs(const cfr_handle *h) {
     return {h->R_base + h->rebind[0] * (int64_t)h->es, h->sbar_base + h->rebind[1] * 8,
-            h->sigma_base + h->rebind[2] * (int64_t)h->es, h->g.v, h->g.reach, h->g.t, h->g.up, h->g.kid_off,
+            h->sigma_base + h->rebind[2] * (int64_t)h->es, h->g.v, h->g.seq, h->g.t, h->g.slot_par, h->g.kid_off,
             h->g.mem};
 }
 
-// The launch schedule of one iteration (paper Proposition 3 (iii): a fixed sequence whose length
-// depends on the depth only): the forward pass over depths 1..max_depth (depth 1 always launches,
-// because its first thread advances the iteration counter), then the fused backward/update level
+// The launch schedule of one iteration (paper Proposition 3 (iii): a fixed sequence of at most two
+// launches per depth): the reach pass (plan_reach; its first launch always runs, because its first
+// thread advances the iteration counter), then the fused backward/update level
 // over depths max_depth-1..0, skipping levels with nothing to do.  A single-node game only ticks.
 constexpr int HALF = 10;
 
@@ -263,8 +271,7 @@ void build_plan(cfr_handle *h) {
     if (g.max_depth == 0) { h->plan.push_back({0, 0}); return; }
     const int halves = h->opt.order == CFR_ORDER_ALTERNATING ? 2 : 1;
     for (int half = 0; half < halves; half++) {
-        for (int d = 1; d <= g.max_depth; d++)
-            if (d == 1 || h->int_end[d] > h->depth_off[d]) h->plan.push_back({1 + HALF * half, d});
+        for (int k = 0; k + 1 < (int)h->reach_slot.size(); k++) h->plan.push_back({1 + HALF * half, k});
         for (int d = g.max_depth - 1; d >= 0; d--)
             if (h->grp_depth_off[d + 1] > h->grp_depth_off[d] || h->chance_off[d + 1] > h->chance_off[d] ||
                 h->bigc_off[d + 1] > h->bigc_off[d])
@@ -293,7 +300,9 @@ cfr_status enqueue_iteration(cfr_handle *h, hipStream_t s, int64_t *count, Launc
         if (alt) f.upd = 1 << half;
         if (kind == 0) HIP_TRY(launch_tick(g, s));
         else if (kind == 1)
-            HIP_TRY(launch_forward(g, d, h->depth_off[d], h->int_end[d], d == 1 && half == 0 ? g.t : nullptr, s));
+            HIP_TRY(launch_reach(g, d, h->reach_slot[(size_t)d], h->reach_slot[(size_t)d + 1],
+                                 h->reach_walk[(size_t)d] != 0,
+                                 d == 0 && half == 0 ? g.t : nullptr, s));
         else HIP_TRY(launch_level(g, d, f, s));
         if (tm) {
             tm->cls.push_back(-1);
@@ -322,17 +331,19 @@ void model_bytes(cfr_handle *h, const DeviceLayout &D) {
         }
     }
     double f = 0, lv = 0;
-    for (int d = 1; d <= md; d++) f += 8 * Nr[d] + 2 * es * Nint[d - 1] + 2 * es * Nint[d] + es * Ad[d - 1];
+    // reach: per slot its parent, strategy and reach written; its parent's reach counts once per slot read
+    for (int d = 0; d < md; d++) f += (4 + 3 * es) * Ad[d];
     for (int d = 0; d < md; d++) {
-        // decision members: id, edge offset, value write, opponent reach; edges: child (index), value;
+        // decision members: id, edge offset, opponent's sequence, value write; edges: child (index), value;
+        // the sequences' reach, once per slot;
         // sets: member and slot offsets, player, own reach; slots: sigma read + write, R read + write,
         // sbar read + write
         // (affine layouts: a 4-byte member record, plus a 2-byte staging position in node-order
         // groups; no child index per edge, one offset per slot)
         if (h->g.affine)
-            lv += (4 + 2 * es) * Md[d] + es * Ed[d] + (9 + es) * Id[d] + (4 * es + 20) * Ad[d] +
+            lv += (8 + es) * Md[d] + es * Ed[d] + (13 + es) * Id[d] + (5 * es + 20) * Ad[d] +
                   2.0 * ((size_t)d < h->perm_members.size() ? h->perm_members[(size_t)d] : 0.0);
-        else lv += (8 + 2 * es) * Md[d] + (kb + es) * Ed[d] + (9 + es) * Id[d] + (4 * es + 16) * Ad[d];
+        else lv += (12 + es) * Md[d] + (kb + es) * Ed[d] + (13 + es) * Id[d] + (5 * es + 16) * Ad[d];
         // chance nodes: list entry, edge offset, value write; edges: child (index), value
         for (int32_t j = D.chance_off[d]; j < D.chance_off[d + 1]; j++) {
             const int32_t x = D.chance_node[j];
@@ -863,10 +874,14 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     if (g.affine) {
         ALLOC(g.koff, A > 0 ? A : 1);
         ALLOC(g.mnode, Ndec > 0 ? Ndec : 1);
+        ALLOC(g.mseq, Ndec > 0 ? Ndec : 1);
         ALLOC(g.mpos, Ndec > 0 ? Ndec : 1);
         ALLOC(g.grp_perm, std::max<int64_t>((int64_t)DL.grp_iset_off.size() - 1, 1));
     }
     ALLOC(g.iset_player, I);
+    ALLOC(g.iset_seq, I);
+    ALLOC(g.slot_par, A);
+    ALLOC(g.mem_seq, Ndec);
     g.G = (int32_t)DL.grp_iset_off.size() - 1;
     ALLOC(g.grp_iset_off, (int64_t)DL.grp_iset_off.size());
     ALLOC(g.chance_node, (int64_t)DL.chance_node.size());
@@ -877,10 +892,10 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     {
         char *pv = nullptr, *pr = nullptr, *ps = nullptr, *pR = nullptr;
         ALLOC(pv, N * (int64_t)h->es);
-        ALLOC(pr, 2 * N * (int64_t)h->es);
+        ALLOC(pr, (A + SEQ_FRONT) * (int64_t)h->es);
         ALLOC(ps, (A > 0 ? A : 1) * (int64_t)h->es);
         ALLOC(pR, (A > 0 ? A : 1) * (int64_t)h->es);
-        g.v = pv; g.reach = pr; g.sigma = ps; g.R = pR;
+        g.v = pv; g.seq = pr + SEQ_FRONT * (int64_t)h->es; g.sigma = ps; g.R = pR;
         if (o.rule == CFR_RULE_PCFR_PLUS) {
             char *pp = nullptr;
             ALLOC(pp, (A > 0 ? A : 1) * (int64_t)h->es);
@@ -918,50 +933,74 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     }
     if (g.affine) {
         UP(g.koff, koff);
-        std::vector<int32_t> mnode;
+        std::vector<int32_t> mnode, mseq;
         std::vector<uint16_t> mpos;
         std::vector<int8_t> perm;
-        member_lists(DL, mnode, mpos, perm, h->perm_members);
+        member_lists(DL, mnode, mseq, mpos, perm, h->perm_members);
         for (int8_t f : perm) h->node_order_groups += f;
         for (double m : h->perm_members) h->node_order_members += (int64_t)m;
         UP(g.mnode, mnode);
+        UP(g.mseq, mseq);
         UP(g.mpos, mpos);
         UP(g.grp_perm, perm);
     }
     UP(g.iset_player, DL.iset_player);
+    UP(g.iset_seq, DL.iset_seq);
+    UP(g.mem_seq, DL.mem_seq);
+    {
+        std::vector<int32_t> par((size_t)A);
+        for (int64_t i = 0; i < I; i++)
+            for (int32_t q = DL.slot_off[(size_t)i]; q < DL.slot_off[(size_t)i + 1]; q++) par[(size_t)q] = DL.iset_seq[(size_t)i];
+        UP(g.slot_par, par);
+    }
+    {
+        std::vector<int32_t> first;
+        plan_reach(DL, first, h->reach_walk);
+        for (int32_t d : first) h->reach_slot.push_back(DL.slot_off[(size_t)DL.iset_depth_off[(size_t)d]]);
+    }
     UP(g.grp_iset_off, DL.grp_iset_off);
     UP(g.chance_node, DL.chance_node);
     UP(g.bigc_node, DL.bigc_node);
     if (DL.n_games > 1) {
-        // the first and last game of every forward tile (BLOCK * 4 nodes of one depth) and room for the
-        // lists of the work that still runs once games retire (cfr_set_active)
+        // the first and last game of every tile of the reach pass, and room for the lists of the work
+        // that still runs once games retire (cfr_set_active).  A depth's slots are those of its games in
+        // turn; a tile that crosses depths counts as every game's.
         const int ng = DL.n_games, MD = (int)DL.depth_off.size() - 2;
-        auto range = [&](int s_, int d, int f) { return DL.game_range[((size_t)s_ * (MD + 1) + d) * GR_FIELDS + f]; };
-        constexpr int32_t TILE = 1024;   // k_forward's nodes per workgroup
-        h->fwd_tile_base.assign((size_t)MD + 2, 0);
-        h->fwd_games.clear();
-        for (int d = 0; d <= MD; d++) {
-            h->fwd_tile_base[(size_t)d] = (int64_t)h->fwd_games.size();
-            const int32_t lo = DL.depth_off[(size_t)d], hi = DL.int_end[(size_t)d];
-            int s_ = 0;
-            for (int32_t a0 = lo; a0 < hi; a0 += TILE) {
-                const int32_t a1 = std::min(hi, a0 + TILE) - 1;
-                while (s_ + 1 < ng && range(s_, d, 1) <= a0) s_++;
+        auto slots = [&](int s_, int d, int f) {
+            const int32_t grp = DL.game_range[((size_t)s_ * (MD + 1) + d) * GR_FIELDS + 2 + f];
+            return DL.slot_off[(size_t)DL.grp_iset_off[(size_t)grp]];
+        };
+        h->reach_games.clear();
+        h->reach_tile_base.clear();
+        for (size_t k = 0; k + 1 < h->reach_slot.size(); k++) {
+            h->reach_tile_base.push_back((int64_t)h->reach_games.size());
+            const int32_t tile = reach_tile(h->reach_walk[k] != 0);
+            int d = 0, s_ = 0;
+            for (int32_t a0 = h->reach_slot[k]; a0 < h->reach_slot[k + 1]; a0 += tile) {
+                const int32_t a1 = std::min(h->reach_slot[k + 1], a0 + tile) - 1;
+                auto depth_end = [&](int dd) { return DL.slot_off[(size_t)DL.iset_depth_off[(size_t)dd + 1]]; };
+                while (depth_end(d) <= a0) { d++; s_ = 0; }
+                if (depth_end(d) <= a1) {
+                    h->reach_games.push_back(make_int2(0, ng - 1));
+                    continue;
+                }
+                while (s_ + 1 < ng && slots(s_, d, 1) <= a0) s_++;
                 int e_ = s_;
-                while (e_ + 1 < ng && range(e_, d, 1) <= a1) e_++;
-                h->fwd_games.push_back(make_int2(s_, e_));
+                while (e_ + 1 < ng && slots(e_, d, 1) <= a1) e_++;
+                h->reach_games.push_back(make_int2(s_, e_));
             }
         }
-        h->fwd_tile_base[(size_t)MD + 1] = (int64_t)h->fwd_games.size();
+        h->reach_tile_base.push_back((int64_t)h->reach_games.size());
         h->active.assign((size_t)ng, 1);
-        for (auto *v : {&h->fwd_off, &h->grp_off, &h->chance_off_l, &h->bigc_off_l}) v->assign((size_t)MD + 2, 0);
+        for (auto *v : {&h->grp_off, &h->chance_off_l, &h->bigc_off_l}) v->assign((size_t)MD + 2, 0);
+        h->reach_off.assign(h->reach_slot.size(), 0);
 #define BA(ptr, cnt) do { st = dev_alloc(h, &(ptr), (cnt)); if (st != CFR_OK) { free_handle(h); return st; } } while (0)
-        BA(g.fwd_list, std::max<int64_t>((int64_t)h->fwd_games.size(), 1));
+        BA(g.reach_list, std::max<int64_t>((int64_t)h->reach_games.size(), 1));
         BA(g.grp_list, std::max<int64_t>(g.G, 1));
         BA(g.chance_list, std::max<int64_t>((int64_t)DL.chance_node.size(), 1));
         BA(g.bigc_list, std::max<int64_t>((int64_t)DL.bigc_node.size(), 1));
 #undef BA
-        g.fwd_off = h->fwd_off.data();
+        g.reach_off = h->reach_off.data();
         g.grp_off = h->grp_off.data();
         g.chance_off_l = h->chance_off_l.data();
         g.bigc_off_l = h->bigc_off_l.data();
@@ -985,14 +1024,12 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     if (g.fp64) { UP((double *)g.v, DL.tmpl64); } else { UP((float *)g.v, DL.tmpl); }
     UP(g.vbr, DL.tmpl64);
     {
-        // roots (the first n nodes) have reach 1 in both lanes and in the best-response lane;
+        // the empty sequence, and the roots (the first n nodes) in the best-response lane, have reach 1;
         // written once, never overwritten
         std::vector<float> onef((size_t)n, 1.0f);
         std::vector<double> oned((size_t)n, 1.0);
-        char *r = (char *)g.reach;
         const void *src = g.fp64 ? (const void *)oned.data() : (const void *)onef.data();
-        hipError_t e = hipMemcpy(r, src, h->es * n, hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMemcpy(r + N * (int64_t)h->es, src, h->es * n, hipMemcpyHostToDevice);
+        hipError_t e = hipMemcpy((char *)g.seq - h->es, src, h->es, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(g.qbr, oned.data(), sizeof(double) * n, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking);
         if (e != hipSuccess) { free_handle(h); return fail(CFR_EDEVICE, std::string("setup: ") + hipGetErrorString(e)); }
@@ -1077,23 +1114,26 @@ cfr_status cfr_set_active(cfr_handle *h, const uint8_t *active, int32_t n, void 
     HIP_TRY(hipDeviceSynchronize());
     for (int32_t s_ = 0; s_ < n; s_++) h->active[(size_t)s_] = active[s_] ? 1 : 0;
     if (any) {
-        // per depth, the forward tiles with an active game and the active games' update groups, chance
+        // the reach tiles with an active game, and per depth the active games' update groups, chance
         // nodes and big chance nodes
-        const int MD = (int)h->fwd_off.size() - 2;
+        const int MD = (int)h->grp_off.size() - 2;
         const int ng = h->n_games;
         auto range = [&](int s_, int d, int f) { return h->game_range[((size_t)s_ * (MD + 1) + d) * GR_FIELDS + f]; };
         std::vector<int32_t> fl, gl, cl, bl;
+        for (size_t k = 0; k + 1 < h->reach_tile_base.size(); k++) {
+            h->reach_off[k] = (int64_t)fl.size();
+            for (int64_t t = h->reach_tile_base[k]; t < h->reach_tile_base[k + 1]; t++) {
+                const int2 gr = h->reach_games[(size_t)t];
+                bool on = false;
+                for (int q = gr.x; q <= gr.y && !on; q++) on = h->active[(size_t)q] != 0;
+                if (on) fl.push_back((int32_t)(t - h->reach_tile_base[k]));
+            }
+        }
+        h->reach_off.back() = (int64_t)fl.size();
         for (int d = 0; d <= MD; d++) {
-            h->fwd_off[(size_t)d] = (int64_t)fl.size();
             h->grp_off[(size_t)d] = (int64_t)gl.size();
             h->chance_off_l[(size_t)d] = (int64_t)cl.size();
             h->bigc_off_l[(size_t)d] = (int64_t)bl.size();
-            for (int64_t t = h->fwd_tile_base[(size_t)d]; t < h->fwd_tile_base[(size_t)d + 1]; t++) {
-                const int2 gr = h->fwd_games[(size_t)t];
-                bool on = false;
-                for (int q = gr.x; q <= gr.y && !on; q++) on = h->active[(size_t)q] != 0;
-                if (on) fl.push_back((int32_t)(t - h->fwd_tile_base[(size_t)d]));
-            }
             for (int s_ = 0; s_ < ng; s_++) {
                 if (!h->active[(size_t)s_]) continue;
                 for (int32_t x = range(s_, d, 2); x < range(s_, d, 3); x++) gl.push_back(x);
@@ -1101,11 +1141,10 @@ cfr_status cfr_set_active(cfr_handle *h, const uint8_t *active, int32_t n, void 
                 for (int32_t x = range(s_, d, 6); x < range(s_, d, 7); x++) bl.push_back(x);
             }
         }
-        h->fwd_off[(size_t)MD + 1] = (int64_t)fl.size();
         h->grp_off[(size_t)MD + 1] = (int64_t)gl.size();
         h->chance_off_l[(size_t)MD + 1] = (int64_t)cl.size();
         h->bigc_off_l[(size_t)MD + 1] = (int64_t)bl.size();
-        if (!fl.empty()) HIP_TRY(hipMemcpy(h->g.fwd_list, fl.data(), fl.size() * 4, hipMemcpyHostToDevice));
+        if (!fl.empty()) HIP_TRY(hipMemcpy(h->g.reach_list, fl.data(), fl.size() * 4, hipMemcpyHostToDevice));
         if (!gl.empty()) HIP_TRY(hipMemcpy(h->g.grp_list, gl.data(), gl.size() * 4, hipMemcpyHostToDevice));
         if (!cl.empty()) HIP_TRY(hipMemcpy(h->g.chance_list, cl.data(), cl.size() * 4, hipMemcpyHostToDevice));
         if (!bl.empty()) HIP_TRY(hipMemcpy(h->g.bigc_list, bl.data(), bl.size() * 4, hipMemcpyHostToDevice));
@@ -1449,7 +1488,7 @@ cfr_status cfr_profile(cfr_handle *h, int64_t n, void *stream, cfr_kernel_stat *
     for (auto &ev : tm.ev) (void)hipEventDestroy(ev);
     if (st != CFR_OK) return st;
     if (e != hipSuccess) return fail(CFR_EDEVICE, std::string("profiling events: ") + hipGetErrorString(e));
-    const char *names[4] = {"k_tick", "k_forward", "k_level", ""};
+    const char *names[4] = {"k_tick", "k_reach", "k_level", ""};
     const double bytes[4] = {0.0, h->bytes_fwd, h->bytes_lvl, 0.0};
     const double method[4] = {0.0, h->method_fwd, h->method_lvl, 0.0};
     int32_t k = 0;
