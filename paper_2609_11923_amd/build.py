@@ -13,6 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 SO = os.path.join(HERE, "libcfr.so")
 SOURCES = ["compiler.cpp", "kernels.hip", "runtime.hip", "mlp.hip"]
+PARTS = {"kernels.hip": 5}   # compiled once per CFR_PART, side by side
 ARCH = "gfx950"
 
 
@@ -39,9 +40,11 @@ def build(verbose: bool = False) -> str:
     os.makedirs(tmpdir, exist_ok=True)
     cc = hipcc()
     procs = []
-    for src in SOURCES:
-        obj = os.path.join(tmpdir, src + ".o")
+    for src, part in [(s, p) for s in SOURCES for p in range(PARTS.get(s, 1))]:
+        obj = os.path.join(tmpdir, f"{src}.{part}.o")
         cmd = [cc] + [f for f in flags() if f != "-shared"] + ["-c", os.path.join(CSRC, src), "-o", obj]
+        if src in PARTS:
+            cmd.append(f"-DCFR_PART={part}")
         if src.endswith(".cpp"):
             cmd = [cc, "-O3", "-std=c++17", "-fPIC", "-Wall", "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:

@@ -17,6 +17,10 @@
 // configured dtype -- or double; strategy sums are double in both.  Every
 // reduction runs in a fixed order inside one thread, so results are bitwise
 // reproducible run to run (no float atomics).
+//
+// The update's instantiations take most of the compile time, so this file is compiled once per CFR_PART
+// (build.py): 0 everything that is not listed here, 1 / 2 the level launches in FP32 / FP64, 3 / 4 the
+// persistent and LDS-resident launches in FP32 / FP64.
 #include <type_traits>
 
 #include "compiler.hpp"
@@ -24,12 +28,37 @@
 
 namespace cfrx {
 
+// the pieces compiled per state type
+hipError_t level_f32(const DevGame &g, int d, IterFlags f, hipStream_t s);
+hipError_t level_f64(const DevGame &g, int d, IterFlags f, hipStream_t s);
+hipError_t persistent_f32(const DevGame &g, const PersistentPlan &p, int32_t T_, IterFlags f, int alt, hipStream_t s);
+hipError_t persistent_f64(const DevGame &g, const PersistentPlan &p, int32_t T_, IterFlags f, int alt, hipStream_t s);
+const void *persistent_fn_f32(const DevGame &g);
+const void *persistent_fn_f64(const DevGame &g);
+hipError_t lds_f32(const DevGame &g, const int32_t *gr, int32_t T_, IterFlags f, int alt, hipStream_t s, size_t bytes,
+                   bool prepare);
+hipError_t lds_f64(const DevGame &g, const int32_t *gr, int32_t T_, IterFlags f, int alt, hipStream_t s, size_t bytes,
+                   bool prepare);
+#if CFR_PART == 1 || CFR_PART == 3
+using PartT = float;
+#define LEVEL_OF level_f32
+#define PERSISTENT_OF persistent_f32
+#define PERSISTENT_FN_OF persistent_fn_f32
+#define LDS_OF lds_f32
+#elif CFR_PART == 2 || CFR_PART == 4
+using PartT = double;
+#define LEVEL_OF level_f64
+#define PERSISTENT_OF persistent_f64
+#define PERSISTENT_FN_OF persistent_fn_f64
+#define LDS_OF lds_f64
+#endif
+
 constexpr int BLOCK = 256;
 static_assert(reach_tile(true) % BLOCK == 0 && reach_tile(false) % BLOCK == 0, "slots per thread of k_reach");
 // one thread per set of an update group; uint8 member-to-set indices
 static_assert(GROUP_SETS_MAX <= BLOCK && GROUP_SETS_MAX <= 256, "update group sets");
 
-static inline unsigned grid_for(int64_t n) { return (unsigned)((n + BLOCK - 1) / BLOCK); }
+[[maybe_unused]] static inline unsigned grid_for(int64_t n) { return (unsigned)((n + BLOCK - 1) / BLOCK); }
 
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
@@ -911,10 +940,12 @@ __device__ void set_serial(int32_t i, const RuleArgs &ru, const LevelArgs<T> &a)
 // strategy, regrets (and the PCFR+ prediction) per slot in the state type, then BLOCK reduction slots
 // for big chance nodes.  k_lds uses less: instead of the two words per node it keeps A + 1 for the
 // slots' reach (a game has fewer slots than nodes).
+#if CFR_PART == 0
 size_t lds_schedule_bytes(int32_t N, int32_t A, int fp64, int pred) {
     const size_t es = fp64 ? 8 : 4;
     return 8 * (size_t)A + es * (3 * (size_t)N + (pred ? 3 : 2) * (size_t)A + BLOCK);
 }
+#endif
 
 template <typename T, int MAXA, bool EXPLICIT, bool EXT>
 __global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, int32_t D, int32_t N, int32_t A,
@@ -966,6 +997,7 @@ __global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, i
     }
 }
 
+#if CFR_PART == 0
 __global__ void k_fill_int(int32_t n, int32_t *p, int32_t value) {
     const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
     if (i < n) p[i] = value;
@@ -1127,9 +1159,11 @@ __global__ void __launch_bounds__(BLOCK) k_br_backward(int32_t lo, int32_t hi, c
     }
     vbr[h] = acc;
 }
+#endif
 
 // ---- launchers ------------------------------------------------------------
 
+#if CFR_PART == 0
 template <typename T>
 static hipError_t reach_t(const DevGame &g, int32_t lo, int32_t hi, bool walk, int32_t *tick, const int32_t *tiles,
                           int64_t n_tiles, hipStream_t s) {
@@ -1153,6 +1187,7 @@ hipError_t launch_reach(const DevGame &g, int k, int32_t lo, int32_t hi, bool wa
     if (g.use_lists && nt == 0 && !tick) return hipSuccess;
     return g.fp64 ? reach_t<double>(g, lo, hi, walk, tick, tiles, nt, s) : reach_t<float>(g, lo, hi, walk, tick, tiles, nt, s);
 }
+#endif
 
 template <typename T>
 static LevelArgs<T> level_args(const DevGame &g) {
@@ -1227,10 +1262,11 @@ struct LevelLaunch {
     hipError_t operator()() const { return level_t<T, MAXA, MPT, EX, XT, AF>(g, d, f, s); }
 };
 
-hipError_t launch_level(const DevGame &g, int d, IterFlags f, hipStream_t s) {
-    const LevelLaunch L{g, d, f, s};
-    return g.fp64 ? by_kind<double>(g, f.rule, L) : by_kind<float>(g, f.rule, L);
+#if CFR_PART == 1 || CFR_PART == 2
+hipError_t LEVEL_OF(const DevGame &g, int d, IterFlags f, hipStream_t s) {
+    return by_kind<PartT>(g, f.rule, LevelLaunch{g, d, f, s});
 }
+#endif
 
 struct PersistentLaunch {
     const DevGame &g; const PersistentPlan &p; int32_t T_; IterFlags f; int alt; hipStream_t s;
@@ -1243,19 +1279,11 @@ struct PersistentLaunch {
     }
 };
 
-hipError_t launch_persistent(const DevGame &g, const PersistentPlan &p, int32_t T_, IterFlags f, int alt,
-                             hipStream_t s) {
-    // the barrier counters and, right after them, the queues' claim counters start at zero
-    const int32_t nz = p.n_games + PERSISTENT_QUEUES;
-    hipLaunchKernelGGL(k_fill_int, dim3((nz + 255) / 256), dim3(256), 0, s, nz, p.barrier, 0);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const PersistentLaunch L{g, p, T_, f, alt, s};
-    e = g.fp64 ? by_kind<double>(g, f.rule, L) : by_kind<float>(g, f.rule, L);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_add_counter, dim3(1), dim3(64), 0, s, g.t, T_);
-    return hipGetLastError();
+#if CFR_PART == 3 || CFR_PART == 4
+hipError_t PERSISTENT_OF(const DevGame &g, const PersistentPlan &p, int32_t T_, IterFlags f, int alt, hipStream_t s) {
+    return by_kind<PartT>(g, f.rule, PersistentLaunch{g, p, T_, f, alt, s});
 }
+#endif
 
 struct LdsLaunch {
     const DevGame &g; const int32_t *gr; int32_t T_; IterFlags f; int alt; hipStream_t s; size_t bytes;
@@ -1285,30 +1313,59 @@ static hipError_t lds_dispatch(const DevGame &g, const LdsLaunch &L) {
     return x ? by_actions<T, false, true, 0>(g, L) : by_actions<T, false, false, 0>(g, L);
 }
 
-hipError_t prepare_lds(const DevGame &g, int rule, size_t *bytes) {
-    *bytes = lds_schedule_bytes(g.N, g.A, g.fp64, g.pred != nullptr);
-    if (g.max_actions > 16) return hipErrorInvalidValue;
-    const LdsLaunch L{g, nullptr, 0, IterFlags{rule, 0, 3}, 0, nullptr, *bytes, true};
-    return g.fp64 ? lds_dispatch<double>(g, L) : lds_dispatch<float>(g, L);
+#if CFR_PART == 3 || CFR_PART == 4
+hipError_t LDS_OF(const DevGame &g, const int32_t *gr, int32_t T_, IterFlags f, int alt, hipStream_t s, size_t bytes,
+                  bool prepare) {
+    return lds_dispatch<PartT>(g, LdsLaunch{g, gr, T_, f, alt, s, bytes, prepare});
 }
-
-hipError_t launch_lds(const DevGame &g, const int32_t *game_range, int32_t T_, IterFlags f, int alt, hipStream_t s) {
-    const size_t bytes = lds_schedule_bytes(g.N, g.A, g.fp64, g.pred != nullptr);
-    const LdsLaunch L{g, game_range, T_, f, alt, s, bytes, false};
-    hipError_t e = g.fp64 ? lds_dispatch<double>(g, L) : lds_dispatch<float>(g, L);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_add_counter, dim3(1), dim3(64), 0, s, g.t, T_);
-    return hipGetLastError();
-}
+#endif
 
 struct PersistentFn {
     template <typename T, int MAXA, int MPT, bool EX, bool XT, int AF>
     const void *operator()() const { return reinterpret_cast<const void *>(&k_persistent<T, MAXA, MPT, EX, XT, AF>); }
 };
 
+#if CFR_PART == 3 || CFR_PART == 4
+const void *PERSISTENT_FN_OF(const DevGame &g) { return by_kind<PartT>(g, g.rule, PersistentFn{}); }
+#endif
+
+#if CFR_PART == 0
+hipError_t launch_level(const DevGame &g, int d, IterFlags f, hipStream_t s) {
+    return g.fp64 ? level_f64(g, d, f, s) : level_f32(g, d, f, s);
+}
+
+hipError_t launch_persistent(const DevGame &g, const PersistentPlan &p, int32_t T_, IterFlags f, int alt,
+                             hipStream_t s) {
+    // the barrier counters and, right after them, the queues' claim counters start at zero
+    const int32_t nz = p.n_games + PERSISTENT_QUEUES;
+    hipLaunchKernelGGL(k_fill_int, dim3((nz + 255) / 256), dim3(256), 0, s, nz, p.barrier, 0);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    e = g.fp64 ? persistent_f64(g, p, T_, f, alt, s) : persistent_f32(g, p, T_, f, alt, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_add_counter, dim3(1), dim3(64), 0, s, g.t, T_);
+    return hipGetLastError();
+}
+
+hipError_t prepare_lds(const DevGame &g, int rule, size_t *bytes) {
+    *bytes = lds_schedule_bytes(g.N, g.A, g.fp64, g.pred != nullptr);
+    if (g.max_actions > 16) return hipErrorInvalidValue;
+    const IterFlags f{rule, 0, 3};
+    return g.fp64 ? lds_f64(g, nullptr, 0, f, 0, nullptr, *bytes, true) : lds_f32(g, nullptr, 0, f, 0, nullptr, *bytes, true);
+}
+
+hipError_t launch_lds(const DevGame &g, const int32_t *game_range, int32_t T_, IterFlags f, int alt, hipStream_t s) {
+    const size_t bytes = lds_schedule_bytes(g.N, g.A, g.fp64, g.pred != nullptr);
+    hipError_t e = g.fp64 ? lds_f64(g, game_range, T_, f, alt, s, bytes, false)
+                          : lds_f32(g, game_range, T_, f, alt, s, bytes, false);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_add_counter, dim3(1), dim3(64), 0, s, g.t, T_);
+    return hipGetLastError();
+}
+
 // the instantiation launch_persistent uses for this game
 hipError_t persistent_occupancy(const DevGame &g, int *blocks_per_cu) {
-    const void *fn = g.fp64 ? by_kind<double>(g, g.rule, PersistentFn{}) : by_kind<float>(g, g.rule, PersistentFn{});
+    const void *fn = g.fp64 ? persistent_fn_f64(g) : persistent_fn_f32(g);
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, fn, BLOCK, 0);
 }
 
@@ -1451,5 +1508,7 @@ hipError_t launch_br_backward(const DevGame &g, int32_t lo, int32_t hi, int br, 
                            g.node_slot, g.node_iset, g.iset_player, g.sigbar, g.astar, g.vbr, br);
     return hipGetLastError();
 }
+
+#endif  // CFR_PART == 0
 
 }  // namespace cfrx
