@@ -167,6 +167,7 @@ cfr_status build_layout(const cfr_game_desc *g, Layout &L, std::string &err) {
         std::vector<int32_t> last1((size_t)N, -1), last2((size_t)N, -1);
         L.iset_seq.assign((size_t)I, -1);
         L.opp_seq.assign((size_t)N, -1);
+        L.slot_kids.assign((size_t)L.A, 0);
         pic[0] = 1.0; seq1[0] = 0; seq2[0] = 0;
         int32_t next = 1;
         for (int64_t k = 0; k < N; k++) {
@@ -200,6 +201,7 @@ cfr_status build_layout(const cfr_game_desc *g, Layout &L, std::string &err) {
                     pic[ck] = pic[k];
                     int32_t q = L.slot_off[I_h] + a;
                     L.in_slot[ck] = q;
+                    L.slot_kids[q] |= L.node_type[ck] == CFR_NODE_TERMINAL ? KIDS_TERMINAL : KIDS_INTERNAL;
                     uint64_t &s = t == CFR_NODE_P1 ? seq1[ck] : seq2[ck];
                     s = mix(s ^ ((uint64_t)q + 1) * 0x100000001B3ull);
                     (t == CFR_NODE_P1 ? last1 : last2)[ck] = q;
@@ -242,13 +244,6 @@ cfr_status build_layout(const cfr_game_desc *g, Layout &L, std::string &err) {
         return CFR_ENOMEM;
     }
 }
-
-namespace {
-// edge code: owner of the parent in bits 0-1, internal flag in bit 2, slot from bit 3
-inline int32_t edge_code(int owner, bool internal, int32_t slot) {
-    return (int32_t)(((uint32_t)slot << 3) | (internal ? 4u : 0u) | (uint32_t)owner);
-}
-}  // namespace
 
 namespace {
 // Groups of D with at most cap members and `sets` sets; the offsets are stored when iset_off is given.
@@ -392,6 +387,8 @@ cfr_status build_device_layout(const Layout &L, int kind, int group_actions, boo
             for (int32_t a = 0; a < L.slot_off[ci + 1] - L.slot_off[ci]; a++)
                 slot_map[L.slot_off[ci] + a] = D.slot_off[iset_dev[ci]] + a;
         if (pub) D.slot_canon_to_dev = slot_map; else D.slot_canon_to_dev.clear();
+        D.slot_kids.resize((size_t)A);
+        for (int64_t q = 0; q < A; q++) D.slot_kids[slot_map[q]] = L.slot_kids[q];
         D.iset_seq.resize((size_t)I);
         for (int64_t i = 0; i < I; i++) {
             const int32_t q = L.iset_seq[iset_canon[i]];
@@ -434,10 +431,6 @@ cfr_status build_device_layout(const Layout &L, int kind, int group_actions, boo
             }
         }
         // node arrays in device order
-        D.up_parent.assign((size_t)N, -1);
-        D.up_code.assign((size_t)N, 0);
-        D.node_slot.assign((size_t)N, -1);
-        D.node_iset.assign((size_t)N, -1);
         D.tmpl.assign((size_t)N, 0.0f);
         D.tmpl64.assign((size_t)N, 0.0);
         D.kid_off.assign((size_t)N + 1, 0);
@@ -445,17 +438,6 @@ cfr_status build_device_layout(const Layout &L, int kind, int group_actions, boo
         int32_t e = 0;
         for (int64_t x = 0; x < N; x++) {
             int64_t k = inv[x];
-            int32_t p = L.parent[k];
-            int owner = 0;
-            if (p >= 0 && (L.node_type[p] == CFR_NODE_P1 || L.node_type[p] == CFR_NODE_P2)) owner = L.node_type[p];
-            int32_t slot = owner ? slot_map[L.in_slot[k]] : 0;
-            D.up_parent[x] = p >= 0 ? perm[p] : -1;
-            D.up_code[x] = edge_code(owner, internal(k), slot);
-            int32_t ci = L.node_infoset[k];
-            if (ci >= 0) {
-                D.node_iset[x] = iset_dev[ci];
-                D.node_slot[x] = D.slot_off[iset_dev[ci]];
-            }
             D.tmpl[x] = L.tmpl[k];
             D.tmpl64[x] = L.tmpl64[k];
             if (pub) {
@@ -475,12 +457,18 @@ cfr_status build_device_layout(const Layout &L, int kind, int group_actions, boo
         D.bigc_off.assign((size_t)md + 2, 0);
         D.chance_node.clear();
         D.bigc_node.clear();
+        D.chance_kids.clear();
+        D.bigc_kids.clear();
         for (int d = 0; d <= md; d++) {
             for (int32_t x = D.depth_off[d]; x < D.int_end[d]; x++) {
                 if (L.node_type[inv[x]] != CFR_NODE_CHANCE) continue;
                 const int32_t k = D.kid_off[x + 1] - D.kid_off[x];
-                if (k > BIG_FANOUT) D.bigc_node.push_back(x);
-                else if (k > 0) D.chance_node.push_back(x);
+                if (k == 0) continue;
+                uint8_t kinds = 0;
+                for (int32_t c = L.child_off[inv[x]]; c < L.child_off[inv[x] + 1]; c++)
+                    kinds |= L.node_type[c] == CFR_NODE_TERMINAL ? KIDS_TERMINAL : KIDS_INTERNAL;
+                (k > BIG_FANOUT ? D.bigc_node : D.chance_node).push_back(x);
+                (k > BIG_FANOUT ? D.bigc_kids : D.chance_kids).push_back(kinds);
             }
             D.chance_off[d + 1] = (int32_t)D.chance_node.size();
             D.bigc_off[d + 1] = (int32_t)D.bigc_node.size();
@@ -691,6 +679,9 @@ cfr_status build_forest(std::vector<Layout> &Ls, std::vector<DeviceLayout> &Ds, 
             const int32_t i = slot_set[s][q];
             return F.slot_off[iset(s, i)] + (q - Ds[s].slot_off[i]);
         };
+        F.slot_kids.assign((size_t)F.slot_off[I], 0);
+        for (int s = 0; s < n; s++)
+            for (int32_t q = 0; q < (int32_t)Ds[s].slot_kids.size(); q++) F.slot_kids[slot(s, q)] = Ds[s].slot_kids[q];
         F.iset_seq.assign((size_t)I, -1);
         for (int s = 0; s < n; s++)
             for (int32_t i = 0; i < (int32_t)Ds[s].iset_seq.size(); i++)
@@ -699,10 +690,6 @@ cfr_status build_forest(std::vector<Layout> &Ls, std::vector<DeviceLayout> &Ds, 
         int64_t E = 0;
         for (int s = 0; s < n; s++) E += Ds[s].kid_off.back() - Ds[s].kid_off.front();
         F.explicit_kids = true;
-        F.up_parent.assign((size_t)N, -1);
-        F.up_code.assign((size_t)N, 0);
-        F.node_slot.assign((size_t)N, -1);
-        F.node_iset.assign((size_t)N, -1);
         F.tmpl.assign((size_t)N, 0.0f);
         F.tmpl64.assign((size_t)N, 0.0);
         F.kid_off.assign((size_t)N + 1, 0);
@@ -713,15 +700,6 @@ cfr_status build_forest(std::vector<Layout> &Ls, std::vector<DeviceLayout> &Ds, 
             const int32_t Ns = D.depth_off.back();
             for (int32_t x = 0; x < Ns; x++) {
                 const int32_t fx = node(s, x);
-                F.up_parent[fx] = D.up_parent[x] >= 0 ? node(s, D.up_parent[x]) : -1;
-                int32_t code = D.up_code[x];
-                const int owner = code & 3;
-                if (owner) code = (int32_t)(((uint32_t)slot(s, (int32_t)((uint32_t)code >> 3)) << 3) | (uint32_t)(code & 7));
-                F.up_code[fx] = code;
-                if (D.node_iset[x] >= 0) {
-                    F.node_iset[fx] = iset(s, D.node_iset[x]);
-                    F.node_slot[fx] = F.slot_off[F.node_iset[fx]];
-                }
                 F.tmpl[fx] = D.tmpl[x];
                 F.tmpl64[fx] = D.tmpl64[x];
                 nkids[fx] = D.kid_off[x + 1] - D.kid_off[x];
@@ -755,6 +733,8 @@ cfr_status build_forest(std::vector<Layout> &Ls, std::vector<DeviceLayout> &Ds, 
         F.grp_iset_off.assign((size_t)G + 1, 0);
         F.chance_node.assign((size_t)C, 0);
         F.bigc_node.assign((size_t)B, 0);
+        F.chance_kids.assign((size_t)C, 0);
+        F.bigc_kids.assign((size_t)B, 0);
         for (int d = 0; d <= MD; d++)
             for (int s = 0; s < n; s++) {
                 const DeviceLayout &D = Ds[s];
@@ -767,9 +747,15 @@ cfr_status build_forest(std::vector<Layout> &Ls, std::vector<DeviceLayout> &Ds, 
                     F.grp_iset_off[g + 1] = iset(s, last) + 1;
                 }
                 int64_t c = cb[(size_t)d * n + s];
-                for (int32_t k = D.chance_off[d]; k < D.chance_off[d + 1]; k++) F.chance_node[c++] = node(s, D.chance_node[k]);
+                for (int32_t k = D.chance_off[d]; k < D.chance_off[d + 1]; k++) {
+                    F.chance_kids[c] = D.chance_kids[k];
+                    F.chance_node[c++] = node(s, D.chance_node[k]);
+                }
                 int64_t b = bb[(size_t)d * n + s];
-                for (int32_t k = D.bigc_off[d]; k < D.bigc_off[d + 1]; k++) F.bigc_node[b++] = node(s, D.bigc_node[k]);
+                for (int32_t k = D.bigc_off[d]; k < D.bigc_off[d + 1]; k++) {
+                    F.bigc_kids[b] = D.bigc_kids[k];
+                    F.bigc_node[b++] = node(s, D.bigc_node[k]);
+                }
             }
         F.int_end.assign((size_t)MD + 1, 0);
         for (int d = 0; d <= MD; d++) F.int_end[d] = F.depth_off[d + 1];  // terminals interleave across games

@@ -15,6 +15,9 @@
 
 namespace cfrx {
 
+// kinds of children below a slot or chance node
+constexpr uint8_t KIDS_TERMINAL = 1, KIDS_INTERNAL = 2;
+
 struct Layout {
     int64_t N = 0, E = 0, Z = 0, Ndec = 0, I = 0, A = 0;
     int max_depth = 0, D = 0, max_actions = 0;
@@ -35,6 +38,7 @@ struct Layout {
     std::vector<int32_t> iset_depth_off; // [max_depth + 2] infosets whose members sit at depth d
     // sequences: the slot of the last action a player took on the way to a node, -1 before the first
     std::vector<int32_t> iset_seq;       // [I] the acting player's (one for all members: perfect recall)
+    std::vector<uint8_t> slot_kids;      // [A] KIDS_* bits of the children below each slot
     std::vector<int32_t> opp_seq;        // [N] at decision nodes, the other player's; -1 elsewhere
     std::vector<int64_t> public_key;     // [N] canonical order, empty if not given
     // set before build_layout to keep the canonical -> input node map (in-place re-solve support)
@@ -66,15 +70,12 @@ struct DeviceLayout {
     bool explicit_kids = false;
     std::vector<int32_t> depth_off;      // [max_depth + 2]
     std::vector<int32_t> int_end;        // [max_depth + 1] internal nodes of depth d: [depth_off[d], int_end[d])
-    std::vector<int32_t> up_parent;      // [N] parent (device id), -1 at the root
-    std::vector<int32_t> up_code;        // [N] edge code (see device.hpp), slot in device numbering
     std::vector<int32_t> kid_off;        // [N + 1]
     std::vector<int32_t> kid;            // [E] when explicit_kids
-    std::vector<int32_t> node_slot;      // [N] first device slot of a decision node, -1 otherwise
-    std::vector<int32_t> node_iset;      // [N] device information set, -1 otherwise
     std::vector<int32_t> slot_off, mem_off, mem_node;
     std::vector<int32_t> iset_seq;       // [I] device slot of the acting player's last own action, -1 if none
     std::vector<int32_t> mem_seq;        // [Ndec] aligned with mem_node: the other player's last slot, -1 if none
+    std::vector<uint8_t> slot_kids;      // [A] KIDS_* bits of the children below each slot
     std::vector<int8_t> iset_player;
     std::vector<int32_t> iset_depth_off; // [max_depth + 2]
     std::vector<float> tmpl;             // [N]
@@ -97,6 +98,7 @@ struct DeviceLayout {
     std::vector<int32_t> chance_off;     // [max_depth + 2]
     std::vector<int32_t> bigc_node;
     std::vector<int32_t> bigc_off;       // [max_depth + 2]
+    std::vector<uint8_t> chance_kids, bigc_kids;  // KIDS_* bits of the listed nodes' children
     // forests (batches of independent games, depth-major: the depth-d nodes of game 0, then of
     // game 1, ...; likewise information sets, slots, groups and chance nodes)
     int32_t n_games = 1;
@@ -109,6 +111,7 @@ struct DeviceLayout {
 
 constexpr int GR_FIELDS = 8;  // node lo/hi, group lo/hi, chance lo/hi, big chance lo/hi
 constexpr int BIG_FANOUT = 64;
+constexpr int GROUP_MEMBERS_MAX = 1024;   // the largest group_members
 
 // members per update group (members per thread times the 256-thread block): with at most 4 actions
 // per set four per thread for FP32 state and two for FP64 (whose LDS staging is twice as large),

@@ -7,13 +7,6 @@
 
 namespace cfrx {
 
-// Edge code stored with every node for the edge into it:
-//   bits 0-1  owner of the parent (0 chance / root, 1 player 1, 2 player 2)
-//   bit  2    the node is internal (has children); terminals carry no reach
-//   bits 3-30 slot of the edge (decision parents only)
-constexpr int CODE_OWNER_MASK = 3;
-constexpr int CODE_INTERNAL = 4;
-constexpr int CODE_SLOT_SHIFT = 3;
 // Member-list entries: node id in bits 0-30, bit 31 set when the set belongs to player 2;
 // paired with the node's first edge so that no edge-offset lookup sits on the load chain.
 constexpr int32_t MEMBER_NODE_MASK = 0x7fffffff;
@@ -37,7 +30,6 @@ struct DevGame {
     int rule = 0;                 // CFR_RULE_* (selects the update's instantiation)
     // structure (read-only after compile)
     int explicit_kids = 0;        // 1: child a of n is kid[kid_off[n] + a]; 0: it is kid_off[n] + a
-    int2 *up = nullptr;           // [N]   (parent, edge code)
     int32_t *kid_off = nullptr;   // [N+1] edges of n are [kid_off[n], kid_off[n+1])
     int32_t *kid = nullptr;       // [E]   child of each edge (explicit layouts only)
     // affine layouts (explicit, and child a of every member h of a set is h + koff[slot a]): the
@@ -53,8 +45,6 @@ struct DevGame {
     uint16_t *mpos = nullptr;     // [Ndec]
     int8_t *grp_perm = nullptr;   // [G]
     int32_t *slot_map = nullptr;  // [A]   canonical slot -> device slot (nullptr: identity)
-    int32_t *node_slot = nullptr; // [N]   first slot of a decision node, -1 otherwise
-    int32_t *node_iset = nullptr; // [N]   information set of a decision node, -1 otherwise
     int32_t *slot_off = nullptr;  // [I+1]
     int32_t *mem_off = nullptr;   // [I+1]
     int2 *mem = nullptr;          // [Ndec]  members: (node | MEMBER_P2 bit, first edge of the node)
@@ -87,13 +77,14 @@ struct DevGame {
     void *pred = nullptr;         // [A]   PCFR+ prediction (the latest instantaneous regret), else nullptr
     double *sbar = nullptr;       // [A]   strategy sums (FP64)
     int32_t *t = nullptr;         // [1]   iterations started (device counter)
-    // evaluation scratch (best response, FP64)
-    double *vbr = nullptr;        // [N]   terminals hold pi_c(z) u(z) in double
-    double *qbr = nullptr;        // [N]   opponent reach of the best responder
+    // evaluation (FP64): node values under the average profile and under each player's best response to
+    // it; terminals hold pi_c(z) u(z) in val[0] only
+    double *val[3] = {nullptr, nullptr, nullptr};   // [N] each
     double *sigbar = nullptr;     // [A]   normalised average strategy
-    int32_t *astar = nullptr;     // [I]   best-response action
-    float *out = nullptr;         // [A]   staging for strategy output (canonical order)
-    float *out2 = nullptr;        // [A]   staging in device order
+    double *seqbar = nullptr;     // [A]   its reach of each slot's sequence; seqbar[-1] = 1
+    uint8_t *slot_kids = nullptr; // [A]   KIDS_* bits of the children below each slot
+    uint8_t *chance_kids = nullptr, *bigc_kids = nullptr;   // of the listed chance nodes
+    float *out = nullptr;         // [A]   staging for strategies and regrets (canonical order)
 };
 
 struct IterFlags {
@@ -139,12 +130,11 @@ hipError_t launch_lds(const DevGame &g, const int32_t *game_range, int32_t T, It
                       hipStream_t s);
 // counter bump for games without edges
 hipError_t launch_tick(const DevGame &g, hipStream_t s);
-// out2[q] <- normalised average strategy (float, device order), sigbar[q] <- same in double
+// sigbar[q] <- normalised average strategy (device order)
 hipError_t launch_average(const DevGame &g, hipStream_t s);
-// out-of-band conversions between device slot order and canonical order:
-// dst[q] <- sigma[map q] as float; dst[q] <- src[map q]; R[map q] <- src[q]
-hipError_t launch_sigma_to_float(const DevGame &g, float *dst, hipStream_t s);
-hipError_t launch_gather_float(const DevGame &g, const float *src, float *dst, hipStream_t s);
+// dst <- average or current strategy in canonical order (canon_off: the canonical sets' slots)
+hipError_t launch_strategy(const DevGame &g, const int32_t *canon_off, bool average, float *dst, hipStream_t s);
+// out-of-band conversions from canonical order: R[map q] <- src[q]
 hipError_t launch_regrets_from_float(const DevGame &g, const float *src, hipStream_t s);
 // R[map q] += src[q] (canonical float source)
 hipError_t launch_regrets_add_float(const DevGame &g, const float *src, hipStream_t s);
@@ -153,14 +143,15 @@ hipError_t launch_scatter_double(const DevGame &g, const double *src, void *dst,
 // zero A slots of the state type
 hipError_t launch_fill_state(const DevGame &g, void *dst, hipStream_t s);
 // in-place re-solve: u[j] <- payoff_in[in[j]] for records [lo, hi); then the template of those
-// terminals: v = vbr = (root ? root[branch] * pic : pic) * u
+// terminals: v = val[0] = (root ? root[branch] * pic : pic) * u
 hipError_t launch_gather_payoffs(int64_t lo, int64_t hi, const int32_t *in, const double *payoff_in, double *u,
                                  hipStream_t s);
 hipError_t launch_template(const DevGame &g, int64_t lo, int64_t hi, const int32_t *node, const int32_t *branch,
                            const double *u, const double *pic, const double *root, hipStream_t s);
-// best response pieces (FP64); br = 1 or 2 selects the best responder, 0 evaluates the average profile
-hipError_t launch_br_forward(const DevGame &g, int32_t lo, int32_t hi, int br, hipStream_t s);
-hipError_t launch_br_argmax(const DevGame &g, int32_t ilo, int32_t ihi, int br, hipStream_t s);
-hipError_t launch_br_backward(const DevGame &g, int32_t lo, int32_t hi, int br, hipStream_t s);
+// evaluation: the reach pass on the average strategy (slots [lo, hi) of one launch), one level of the
+// sweep, the root values into out[3 * n] (average profile, best response of player 1, of player 2)
+hipError_t launch_reach_average(const DevGame &g, int32_t lo, int32_t hi, bool walk, hipStream_t s);
+hipError_t launch_eval_level(const DevGame &g, int d, hipStream_t s);
+hipError_t launch_eval_roots(const DevGame &g, int32_t n, double *out, hipStream_t s);
 
 }  // namespace cfrx

@@ -1,5 +1,4 @@
-// kernels.hip -- gfx950 kernels of one compiled CFR iteration and of the FP64
-// best-response evaluator.
+// kernels.hip -- gfx950 kernels of one compiled CFR iteration.
 //
 // Iteration (paper Algorithm 'alg:iteration', Table 'tab:opsteps'):
 //   reach    : per slot, seq(I, a) = seq(last own slot before I) * sigma(I, a): the acting player's
@@ -21,8 +20,7 @@
 // The update's instantiations take most of the compile time, so this file is compiled once per CFR_PART
 // (build.py): 0 everything that is not listed here, 1 / 2 the level launches in FP32 / FP64, 3 / 4 the
 // persistent and LDS-resident launches in FP32 / FP64.
-#include <type_traits>
-
+#include "common.hpp"
 #include "compiler.hpp"
 #include "device.hpp"
 
@@ -53,24 +51,9 @@ using PartT = double;
 #define LDS_OF lds_f64
 #endif
 
-constexpr int BLOCK = 256;
 static_assert(reach_tile(true) % BLOCK == 0 && reach_tile(false) % BLOCK == 0, "slots per thread of k_reach");
 // one thread per set of an update group; uint8 member-to-set indices
 static_assert(GROUP_SETS_MAX <= BLOCK && GROUP_SETS_MAX <= 256, "update group sets");
-
-[[maybe_unused]] static inline unsigned grid_for(int64_t n) { return (unsigned)((n + BLOCK - 1) / BLOCK); }
-
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
-__device__ __forceinline__ float max_t(float a, float b) { return fmaxf(a, b); }
-__device__ __forceinline__ double max_t(double a, double b) { return fmax(a, b); }
-
-// child a of node n: explicit layouts list children, the breadth-first layout numbers them
-template <bool EXPLICIT>
-__device__ __forceinline__ int32_t child_of(const int32_t *__restrict__ kid, int32_t edge) {
-    if constexpr (EXPLICIT) return kid[edge];
-    else return edge;
-}
 
 // The reach of the sequence that ends in slot p: the strategies along it multiplied from the root on,
 // as ((1 * s1) * s2) * ....  Slots below S0 are finished (seq holds their reach; seq[-1] = 1 is the empty
@@ -108,24 +91,6 @@ __device__ __forceinline__ T seq_reach(int32_t p, int32_t S0, const int32_t *slo
     for (int k = REACH_WALK - 1; k >= 0; k--)
         if (k < n) acc = acc * s[k];
     return acc;
-}
-
-// XCD-aware tile order.  The dispatcher hands the workgroups of a launch to the 8 XCDs in turn
-// (workgroup b to XCD b mod 8) and each XCD has its own L2, so neighbouring tiles -- which share
-// cache lines: the child values of interleaved information sets, the strategy rows of one set --
-// would be fetched once per XCD.  Tiles are dealt out instead in runs of XCD_RUN consecutive tiles
-// per XCD: workgroup b = 8 i + x runs tile (i / R) 8R + x R + (i mod R), R = XCD_RUN, a bijection
-// of [0, M) with M the largest multiple of 8R not above n; tiles from M on keep their index.  Runs
-// (rather than one contiguous eighth of the level per XCD) keep the XCDs' shares of a level
-// alike where the work per tile drifts along it.  Measured: on the 256-subgame batch the update
-// levels took 13 % less time than with the plain order, the large game was 1 % faster; one
-// contiguous eighth per XCD was as fast on the batch but 3-7 % slower on the large game.
-constexpr int32_t XCD_RUN = 16;
-__device__ __forceinline__ int32_t xcd_tile(int32_t b, int32_t n) {
-    const int32_t M = n / (8 * XCD_RUN) * (8 * XCD_RUN);
-    if (b >= M) return b;
-    const int32_t x = b & 7, i = b >> 3;
-    return i / XCD_RUN * (8 * XCD_RUN) + x * XCD_RUN + i % XCD_RUN;
 }
 
 // The reach of slots [lo, hi), SPT per thread (strided by the block size, so each wave's accesses stay
@@ -521,23 +486,6 @@ struct GroupLdsA {
     int32_t wmax[BLOCK / 64];
     uint8_t mset[MPT * BLOCK];
 };
-
-// Calls f with the smallest action bound of {2, 3, MAXA} (MAXA = 4) or {4, MAXA} (wider
-// instantiations) that is at least n, as a compile-time constant, so a pass over sets or members
-// that need fewer actions issues fewer loads (large game: FP64 state 5 % faster, FP32 unchanged; a
-// 16-action instantiation would otherwise load 16 children per member of a 2-action set).  n must
-// be uniform over the wave (or the block).
-template <int MAXA, typename F>
-__device__ __forceinline__ void with_action_bound(int32_t n, F &&f) {
-    if constexpr (MAXA <= 4) {
-        if (n <= 2) f(std::integral_constant<int, 2>{});
-        else if (n <= 3) f(std::integral_constant<int, 3>{});
-        else f(std::integral_constant<int, MAXA>{});
-    } else {
-        if (n <= 4) f(std::integral_constant<int, 4>{});
-        else f(std::integral_constant<int, MAXA>{});
-    }
-}
 
 // group_update for affine layouts (child a of member h is h + koff[slot a]): the same arithmetic
 // in the same order, so the results are bitwise those of group_update.  What changes is how the
@@ -1027,30 +975,6 @@ __global__ void k_tick(int32_t *t) {
     if (threadIdx.x == 0) t[0] += 1;
 }
 
-__global__ void __launch_bounds__(BLOCK) k_average(int32_t I, const int32_t *__restrict__ slot_off,
-                                                   const double *__restrict__ sbar, double *__restrict__ sigbar,
-                                                   float *__restrict__ out) {
-    int32_t i = (int32_t)(blockIdx.x * BLOCK + threadIdx.x);
-    if (i >= I) return;
-    int32_t s0 = slot_off[i], s1 = slot_off[i + 1];
-    double tot = 0.0;
-    for (int32_t q = s0; q < s1; q++) tot += sbar[q];
-    const double uni = 1.0 / (double)(s1 - s0);
-    for (int32_t q = s0; q < s1; q++) {
-        double x = tot > 0.0 ? sbar[q] / tot : uni;
-        sigbar[q] = x;
-        out[q] = (float)x;
-    }
-}
-
-// dst[i] = src[map i] (map == nullptr: identity)
-template <typename S, typename D>
-__global__ void __launch_bounds__(BLOCK) k_gather(int32_t n, const int32_t *__restrict__ map,
-                                                  const S *__restrict__ src, D *__restrict__ dst) {
-    int32_t i = (int32_t)(blockIdx.x * BLOCK + threadIdx.x);
-    if (i < n) dst[i] = (D)src[map ? map[i] : i];
-}
-
 // dst[map i] = src[i] (map == nullptr: identity)
 template <typename S, typename D>
 __global__ void __launch_bounds__(BLOCK) k_scatter(int32_t n, const int32_t *__restrict__ map,
@@ -1081,83 +1005,13 @@ template <typename T>
 __global__ void __launch_bounds__(BLOCK) k_template(int64_t lo, int64_t hi, const int32_t *__restrict__ node,
                                                     const int32_t *__restrict__ branch, const double *__restrict__ u,
                                                     const double *__restrict__ pic, const double *__restrict__ root,
-                                                    T *__restrict__ v, double *__restrict__ vbr) {
+                                                    T *__restrict__ v, double *__restrict__ v0) {
     const int64_t j = lo + (int64_t)blockIdx.x * BLOCK + threadIdx.x;
     if (j >= hi) return;
     const double c = root ? root[branch[j]] * pic[j] : pic[j];
     const double t = c * u[j];
     v[node[j]] = (T)t;
-    vbr[node[j]] = t;
-}
-
-// ---- best response (FP64) -------------------------------------------------
-
-__global__ void __launch_bounds__(BLOCK) k_br_forward(int32_t lo, int32_t hi, const int2 *__restrict__ up,
-                                                      const double *__restrict__ sigbar, double *__restrict__ q,
-                                                      int br) {
-    int32_t c = lo + (int32_t)(blockIdx.x * BLOCK + threadIdx.x);
-    if (c >= hi) return;
-    int2 u = up[c];
-    if (!(u.y & CODE_INTERNAL)) return;
-    int owner = u.y & CODE_OWNER_MASK;
-    double m = (owner != 0 && owner != br) ? sigbar[u.y >> CODE_SLOT_SHIFT] : 1.0;
-    q[c] = q[u.x] * m;
-}
-
-template <bool EXPLICIT>
-__global__ void __launch_bounds__(BLOCK) k_br_argmax(int32_t ilo, int32_t ihi, const int32_t *__restrict__ slot_off,
-                                                     const int32_t *__restrict__ mem_off,
-                                                     const int2 *__restrict__ mem,
-                                                     const int8_t *__restrict__ iset_player,
-                                                     const int32_t *__restrict__ kid_off,
-                                                     const int32_t *__restrict__ kid,
-                                                     const double *__restrict__ vbr, const double *__restrict__ q,
-                                                     int32_t *__restrict__ astar, int br) {
-    int32_t i = ilo + (int32_t)(blockIdx.x * BLOCK + threadIdx.x);
-    if (i >= ihi) return;
-    if (iset_player[i] != br) return;
-    int32_t nA = slot_off[i + 1] - slot_off[i];
-    int32_t m0 = mem_off[i], m1 = mem_off[i + 1];
-    const double sign = br == 1 ? 1.0 : -1.0;
-    int best = 0;
-    double bq = 0.0;
-    for (int a = 0; a < nA; a++) {
-        double Q = 0.0;
-        for (int32_t m = m0; m < m1; m++) {
-            const int2 x = mem[m];
-            Q += q[x.x & MEMBER_NODE_MASK] * (sign * vbr[child_of<EXPLICIT>(kid, x.y + a)]);
-        }
-        if (a == 0 || Q > bq) { bq = Q; best = a; }
-    }
-    astar[i] = best;
-}
-
-template <bool EXPLICIT>
-__global__ void __launch_bounds__(BLOCK) k_br_backward(int32_t lo, int32_t hi, const int32_t *__restrict__ kid_off,
-                                                       const int32_t *__restrict__ kid,
-                                                       const int32_t *__restrict__ node_slot,
-                                                       const int32_t *__restrict__ node_iset,
-                                                       const int8_t *__restrict__ iset_player,
-                                                       const double *__restrict__ sigbar,
-                                                       const int32_t *__restrict__ astar, double *__restrict__ vbr,
-                                                       int br) {
-    int32_t h = lo + (int32_t)(blockIdx.x * BLOCK + threadIdx.x);
-    if (h >= hi) return;
-    int32_t b = kid_off[h], e = kid_off[h + 1];
-    if (b == e) return;
-    int32_t s = node_slot[h];
-    double acc = 0.0;
-    if (s < 0) {
-        for (int32_t c = b; c < e; c++) acc += vbr[child_of<EXPLICIT>(kid, c)];
-    } else {
-        int32_t i = node_iset[h];
-        if (iset_player[i] == br) {
-            acc = vbr[child_of<EXPLICIT>(kid, b + astar[i])];
-        } else {
-            for (int32_t c = b; c < e; c++) acc += sigbar[s + (c - b)] * vbr[child_of<EXPLICIT>(kid, c)];
-        }
-    }
-    vbr[h] = acc;
+    v0[node[j]] = t;
 }
 #endif
 
@@ -1186,6 +1040,21 @@ hipError_t launch_reach(const DevGame &g, int k, int32_t lo, int32_t hi, bool wa
     const int64_t nt = g.use_lists ? g.reach_off[k + 1] - g.reach_off[k] : 0;
     if (g.use_lists && nt == 0 && !tick) return hipSuccess;
     return g.fp64 ? reach_t<double>(g, lo, hi, walk, tick, tiles, nt, s) : reach_t<float>(g, lo, hi, walk, tick, tiles, nt, s);
+}
+#endif
+
+#if CFR_PART == 0
+// launch k of the reach pass on the average strategy (sigbar into seqbar)
+hipError_t launch_reach_average(const DevGame &g, int32_t lo, int32_t hi, bool walk, hipStream_t s) {
+    if (hi <= lo) return hipSuccess;
+    const unsigned blocks = (unsigned)(((int64_t)hi - lo + reach_tile(walk) - 1) / reach_tile(walk));
+    if (walk)
+        hipLaunchKernelGGL((k_reach<double, true>), dim3(blocks), dim3(BLOCK), 0, s, lo, hi, lo, g.slot_par, g.sigbar,
+                           g.seqbar, nullptr, nullptr);
+    else
+        hipLaunchKernelGGL((k_reach<double, false>), dim3(blocks), dim3(BLOCK), 0, s, lo, hi, lo, g.slot_par, g.sigbar,
+                           g.seqbar, nullptr, nullptr);
+    return hipGetLastError();
 }
 #endif
 
@@ -1385,29 +1254,6 @@ hipError_t launch_tick(const DevGame &g, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_average(const DevGame &g, hipStream_t s) {
-    if (g.I == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_average, dim3(grid_for(g.I)), dim3(BLOCK), 0, s, g.I, g.slot_off, g.sbar, g.sigbar, g.out2);
-    return hipGetLastError();
-}
-
-hipError_t launch_sigma_to_float(const DevGame &g, float *dst, hipStream_t s) {
-    if (g.A == 0) return hipSuccess;
-    if (g.fp64)
-        hipLaunchKernelGGL((k_gather<double, float>), dim3(grid_for(g.A)), dim3(BLOCK), 0, s, g.A, g.slot_map,
-                           (const double *)g.sigma, dst);
-    else
-        hipLaunchKernelGGL((k_gather<float, float>), dim3(grid_for(g.A)), dim3(BLOCK), 0, s, g.A, g.slot_map,
-                           (const float *)g.sigma, dst);
-    return hipGetLastError();
-}
-
-hipError_t launch_gather_float(const DevGame &g, const float *src, float *dst, hipStream_t s) {
-    if (g.A == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_gather<float, float>), dim3(grid_for(g.A)), dim3(BLOCK), 0, s, g.A, g.slot_map, src, dst);
-    return hipGetLastError();
-}
-
 hipError_t launch_regrets_from_float(const DevGame &g, const float *src, hipStream_t s) {
     if (g.A == 0) return hipSuccess;
     if (g.fp64)
@@ -1474,38 +1320,10 @@ hipError_t launch_template(const DevGame &g, int64_t lo, int64_t hi, const int32
     const dim3 grid((unsigned)((hi - lo + BLOCK - 1) / BLOCK));
     if (g.fp64)
         hipLaunchKernelGGL(k_template<double>, grid, dim3(BLOCK), 0, s, lo, hi, node, branch, u, pic, root,
-                           (double *)g.v, g.vbr);
+                           (double *)g.v, g.val[0]);
     else
         hipLaunchKernelGGL(k_template<float>, grid, dim3(BLOCK), 0, s, lo, hi, node, branch, u, pic, root,
-                           (float *)g.v, g.vbr);
-    return hipGetLastError();
-}
-
-hipError_t launch_br_forward(const DevGame &g, int32_t lo, int32_t hi, int br, hipStream_t s) {
-    if (hi <= lo) return hipSuccess;
-    hipLaunchKernelGGL(k_br_forward, dim3(grid_for(hi - lo)), dim3(BLOCK), 0, s, lo, hi, g.up, g.sigbar, g.qbr, br);
-    return hipGetLastError();
-}
-
-hipError_t launch_br_argmax(const DevGame &g, int32_t ilo, int32_t ihi, int br, hipStream_t s) {
-    if (ihi <= ilo) return hipSuccess;
-    if (g.explicit_kids)
-        hipLaunchKernelGGL(k_br_argmax<true>, dim3(grid_for(ihi - ilo)), dim3(BLOCK), 0, s, ilo, ihi, g.slot_off,
-                           g.mem_off, g.mem, g.iset_player, g.kid_off, g.kid, g.vbr, g.qbr, g.astar, br);
-    else
-        hipLaunchKernelGGL(k_br_argmax<false>, dim3(grid_for(ihi - ilo)), dim3(BLOCK), 0, s, ilo, ihi, g.slot_off,
-                           g.mem_off, g.mem, g.iset_player, g.kid_off, g.kid, g.vbr, g.qbr, g.astar, br);
-    return hipGetLastError();
-}
-
-hipError_t launch_br_backward(const DevGame &g, int32_t lo, int32_t hi, int br, hipStream_t s) {
-    if (hi <= lo) return hipSuccess;
-    if (g.explicit_kids)
-        hipLaunchKernelGGL(k_br_backward<true>, dim3(grid_for(hi - lo)), dim3(BLOCK), 0, s, lo, hi, g.kid_off, g.kid,
-                           g.node_slot, g.node_iset, g.iset_player, g.sigbar, g.astar, g.vbr, br);
-    else
-        hipLaunchKernelGGL(k_br_backward<false>, dim3(grid_for(hi - lo)), dim3(BLOCK), 0, s, lo, hi, g.kid_off, g.kid,
-                           g.node_slot, g.node_iset, g.iset_player, g.sigbar, g.astar, g.vbr, br);
+                           (float *)g.v, g.val[0]);
     return hipGetLastError();
 }
 

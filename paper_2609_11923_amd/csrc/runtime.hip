@@ -53,7 +53,7 @@ struct cfr_handle {
     cfr_options opt{};
     DevGame g{};
     // host copies of the schedule
-    std::vector<int32_t> depth_off, int_end, iset_depth_off, grp_depth_off, chance_off, bigc_off;
+    std::vector<int32_t> depth_off, iset_depth_off, grp_depth_off, chance_off, bigc_off;
     // launch k of the reach pass: slots [reach_slot[k], reach_slot[k + 1]), reach_walk[k] (plan_reach)
     std::vector<int32_t> reach_slot;
     std::vector<int8_t> reach_walk;
@@ -113,6 +113,7 @@ struct cfr_handle {
     double method_fwd = 0, method_lvl = 0;   // per-unit byte figures of the method (see model_bytes)
     // canonical information sets of all games (rows of the warm-start network)
     int64_t I_canon = 0;
+    double *roots = nullptr;           // [3 * games] pinned: root values of the evaluation
     int32_t *canon_off = nullptr;      // [I + 1] canonical slot offsets, global over the batch
     int8_t *canon_player = nullptr;    // [I]
     float *warm_z = nullptr;           // [I * 4] logits, allocated on first warm start
@@ -423,6 +424,7 @@ void free_handle(cfr_handle *h) {
     if (h->pexec) (void)hipGraphExecDestroy(h->pexec);
     if (h->pgraph) (void)hipGraphDestroy(h->pgraph);
     if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
+    if (h->roots) (void)hipHostFree(h->roots);
     for (void *p : h->pp_allocs) (void)hipFree(p);
     for (void *p : h->allocs) (void)hipFree(p);
     delete h;
@@ -826,7 +828,6 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     h->opt = o;
     h->use_graph = o.use_graph != 0;
     h->depth_off = DL.depth_off;
-    h->int_end = DL.int_end;
     h->iset_depth_off = DL.iset_depth_off;
     h->slot_map = DL.slot_canon_to_dev;
     h->grp_depth_off = DL.grp_depth_off;
@@ -856,18 +857,10 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     g.affine = o.affine && slot_child_offsets(DL, koff) ? 1 : 0;
     g.group_sets = DL.group_sets;
 
-    std::vector<int2> up((size_t)N);
-    for (int64_t k = 0; k < N; k++) up[k] = make_int2(DL.up_parent[k], DL.up_code[k]);
-    DL.up_parent = std::vector<int32_t>();
-    DL.up_code = std::vector<int32_t>();
-
 #define ALLOC(ptr, cnt) do { st = dev_alloc(h, &(ptr), (cnt)); if (st != CFR_OK) { free_handle(h); return st; } } while (0)
-    ALLOC(g.up, N);
     ALLOC(g.kid_off, N + 1);
     if (g.explicit_kids) ALLOC(g.kid, E);
     if (!h->slot_map.empty()) ALLOC(g.slot_map, A);
-    ALLOC(g.node_slot, N);
-    ALLOC(g.node_iset, N);
     ALLOC(g.slot_off, I + 1);
     ALLOC(g.mem_off, I + 1);
     ALLOC(g.mem, Ndec);
@@ -904,12 +897,21 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     }
     ALLOC(g.sbar, A);
     ALLOC(g.t, 1);
-    ALLOC(g.vbr, N);
-    ALLOC(g.qbr, N);
+    for (double *&v : g.val) ALLOC(v, N);
     ALLOC(g.sigbar, A);
-    ALLOC(g.astar, I);
+    {
+        double *p = nullptr;
+        ALLOC(p, A + SEQ_FRONT);
+        g.seqbar = p + SEQ_FRONT;
+    }
+    if (hipHostMalloc((void **)&h->roots, sizeof(double) * 3 * (size_t)n) != hipSuccess) {
+        free_handle(h);
+        return fail(CFR_ENOMEM, "pinned host allocation failed");
+    }
+    ALLOC(g.slot_kids, A);
+    ALLOC(g.chance_kids, (int64_t)DL.chance_kids.size());
+    ALLOC(g.bigc_kids, (int64_t)DL.bigc_kids.size());
     ALLOC(g.out, A);
-    ALLOC(g.out2, A);
     ALLOC(h->canon_off, I + 1);
     ALLOC(h->canon_player, I);
     ALLOC(h->warm_mag, I);
@@ -917,12 +919,9 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     h->I_canon = I;
     h->R_base = (char *)g.R; h->sbar_base = (char *)g.sbar; h->sigma_base = (char *)g.sigma;
 #define UP(dst, src) do { st = upload(dst, src); if (st != CFR_OK) { free_handle(h); return st; } } while (0)
-    UP(g.up, up);
     UP(g.kid_off, DL.kid_off);
     if (g.explicit_kids) UP(g.kid, DL.kid);
     if (g.slot_map) UP(g.slot_map, h->slot_map);
-    UP(g.node_slot, DL.node_slot);
-    UP(g.node_iset, DL.node_iset);
     UP(g.slot_off, DL.slot_off);
     UP(g.mem_off, DL.mem_off);
     {
@@ -961,6 +960,9 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     UP(g.grp_iset_off, DL.grp_iset_off);
     UP(g.chance_node, DL.chance_node);
     UP(g.bigc_node, DL.bigc_node);
+    UP(g.slot_kids, DL.slot_kids);
+    UP(g.chance_kids, DL.chance_kids);
+    UP(g.bigc_kids, DL.bigc_kids);
     if (DL.n_games > 1) {
         // the first and last game of every tile of the reach pass, and room for the lists of the work
         // that still runs once games retire (cfr_set_active).  A depth's slots are those of its games in
@@ -1022,15 +1024,14 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
         h->lc_nodes = lc.nodes;
     }
     if (g.fp64) { UP((double *)g.v, DL.tmpl64); } else { UP((float *)g.v, DL.tmpl); }
-    UP(g.vbr, DL.tmpl64);
+    UP(g.val[0], DL.tmpl64);
     {
-        // the empty sequence, and the roots (the first n nodes) in the best-response lane, have reach 1;
-        // written once, never overwritten
-        std::vector<float> onef((size_t)n, 1.0f);
-        std::vector<double> oned((size_t)n, 1.0);
-        const void *src = g.fp64 ? (const void *)oned.data() : (const void *)onef.data();
-        hipError_t e = hipMemcpy((char *)g.seq - h->es, src, h->es, hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMemcpy(g.qbr, oned.data(), sizeof(double) * n, hipMemcpyHostToDevice);
+        // the empty sequence has reach 1; written once, never overwritten
+        const float onef = 1.0f;
+        const double oned = 1.0;
+        hipError_t e = hipMemcpy((char *)g.seq - h->es, g.fp64 ? (const void *)&oned : (const void *)&onef, h->es,
+                                 hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(g.seqbar - 1, &oned, sizeof oned, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking);
         if (e != hipSuccess) { free_handle(h); return fail(CFR_EDEVICE, std::string("setup: ") + hipGetErrorString(e)); }
     }
@@ -1217,6 +1218,19 @@ cfr_status cfr_iterations(cfr_handle *h, int64_t *t) {
     return CFR_OK;
 }
 
+// whether p[0..bytes) lies in one allocation of `device` that kernels may write as floats
+static bool on_device(const void *p, size_t bytes, int device) {
+    hipPointerAttribute_t at{};
+    void *base = nullptr;
+    size_t size = 0;
+    if ((uintptr_t)p % sizeof(float) == 0 && hipPointerGetAttributes(&at, p) == hipSuccess &&
+        at.type == hipMemoryTypeDevice && at.device == device &&
+        hipMemGetAddressRange((hipDeviceptr_t *)&base, &size, (hipDeviceptr_t)const_cast<void *>(p)) == hipSuccess)
+        return (const char *)p + bytes <= (const char *)base + size;
+    (void)hipGetLastError();   // the lookup's own error is not the caller's
+    return false;
+}
+
 cfr_status cfr_strategy(cfr_handle *h, int which, float *dst, int64_t len, int dst_on_device, void *stream) {
     if (!h || (!dst && len > 0)) return fail(CFR_EINVAL, "NULL argument");
     if (len != h->g.A) return fail(CFR_EINVAL, "len must equal the slot count " + std::to_string(h->g.A));
@@ -1224,15 +1238,13 @@ cfr_status cfr_strategy(cfr_handle *h, int which, float *dst, int64_t len, int d
     if (len == 0) return CFR_OK;
     HIP_TRY(hipSetDevice(h->opt.device));
     hipStream_t s = (hipStream_t)stream;
-    const float *src = h->g.out;
-    if (which == CFR_STRATEGY_AVERAGE) {
-        HIP_TRY(launch_average(h->g, s));                    // device order into out2
-        HIP_TRY(launch_gather_float(h->g, h->g.out2, h->g.out, s));
-    } else {
-        HIP_TRY(launch_sigma_to_float(h->g, h->g.out, s));   // gathers into canonical order
-    }
-    HIP_TRY(hipMemcpyAsync(dst, src, (size_t)len * sizeof(float),
-                           dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
+    // straight into dst where that is memory of this device, else through the staging buffer
+    const bool direct = dst_on_device && on_device(dst, (size_t)len * sizeof(float), h->opt.device);
+    float *to = direct ? dst : h->g.out;
+    HIP_TRY(launch_strategy(h->g, h->canon_off, which == CFR_STRATEGY_AVERAGE, to, s));
+    if (!direct)
+        HIP_TRY(hipMemcpyAsync(dst, to, (size_t)len * sizeof(float),
+                               dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
     if (!dst_on_device) HIP_TRY(hipStreamSynchronize(s));
     return CFR_OK;
 }
@@ -1389,7 +1401,7 @@ cfr_status cfr_get_prediction(cfr_handle *h, double *prediction, int64_t len, vo
     return CFR_OK;
 }
 
-// Best responses of every game of the handle: vals[k][s] for k = best responder 1, 2 and the
+// Evaluation of every game of the handle: vals[k][s] for k = best responder 1, 2 and the
 // average-profile value (k = 0), read at each game's root.
 static cfr_status best_responses(cfr_handle *h, hipStream_t s, std::vector<double> vals[3]) {
     if (!h->br_ok) return fail(CFR_EUNSUPPORTED, "an information set spans several depths; the level-synchronous best response needs one depth per set");
@@ -1397,19 +1409,13 @@ static cfr_status best_responses(cfr_handle *h, hipStream_t s, std::vector<doubl
     const DevGame &g = h->g;
     const int n = h->n_games;
     HIP_TRY(launch_average(g, s));
-    const int order[3] = {1, 2, 0};
-    for (int k = 0; k < 3; k++) {
-        const int br = order[k];
-        if (br != 0)
-            for (int d = 1; d <= g.max_depth; d++) HIP_TRY(launch_br_forward(g, h->depth_off[d], h->int_end[d], br, s));
-        for (int d = g.max_depth - 1; d >= 0; d--) {
-            if (br != 0) HIP_TRY(launch_br_argmax(g, h->iset_depth_off[d], h->iset_depth_off[d + 1], br, s));
-            HIP_TRY(launch_br_backward(g, h->depth_off[d], h->int_end[d], br, s));
-        }
-        vals[br].assign((size_t)n, 0.0);
-        HIP_TRY(hipMemcpyAsync(vals[br].data(), g.vbr, sizeof(double) * n, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-    }
+    for (size_t k = 0; k + 1 < h->reach_slot.size(); k++)
+        HIP_TRY(launch_reach_average(g, h->reach_slot[k], h->reach_slot[k + 1], h->reach_walk[k] != 0, s));
+    for (int d = g.max_depth - 1; d >= 0; d--) HIP_TRY(launch_eval_level(g, d, s));
+    // the root values go straight to pinned host memory
+    HIP_TRY(launch_eval_roots(g, n, h->roots, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    for (int k = 0; k < 3; k++) vals[k].assign(h->roots + k * n, h->roots + (k + 1) * n);
     return CFR_OK;
 }
 
