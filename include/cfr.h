@@ -457,10 +457,10 @@ cfr_status cfr_mlp_set_params(cfr_mlp *n, const float *params, int64_t len);
  * CFR_MLP_ADAM_M or CFR_MLP_ADAM_V.  Synchronous. */
 cfr_status cfr_mlp_get(cfr_mlp *n, int which, float *dst, int64_t len);
 /* Logits z[rows][4] (device, float32) of device rows x[rows][in_dim] (bf16), on `stream`.  Any
- * number of rows: one fused launch per 2^27 rows keeps each block's activations in LDS (no row limit,
- * no activation buffers), after a small launch that refreshes the network's transposed bf16 weight
- * copy; calls on one network that overlap on different streams (with each other or with training)
- * race on that copy and must be ordered by the caller. */
+ * number of rows: one launch per 2^27 rows keeps each block's activations in LDS (no row limit, no
+ * activation buffers, no device allocation).  A row's logits do not depend on how many rows the call has.
+ * Calls only read the network, so they may overlap with each other on different streams, not with training
+ * or cfr_mlp_set_params. */
 cfr_status cfr_mlp_forward(cfr_mlp *n, const void *x, int64_t rows, float *z, void *stream);
 /* Loss and parameter gradients of one minibatch of rows <= max_rows, on `stream`.  Device
  * arrays: x [.][in_dim] bf16, target [.][4] float32 (entries past a row's legal actions are
@@ -471,17 +471,10 @@ cfr_status cfr_mlp_forward(cfr_mlp *n, const void *x, int64_t rows, float *z, vo
 cfr_status cfr_mlp_backward(cfr_mlp *n, const void *x, const float *target, const float *weight,
                             const uint8_t *nact, const int32_t *idx, int64_t n_data, int64_t rows, double *loss,
                             void *stream);
-/* Logits bitwise equal to cfr_mlp_forward's (computed layer by layer, each hidden layer's activations
- * staged in device memory), for callers that
- * cannot allocate device memory: code under hipGraph capture, tight serving loops, harnesses that
- * forbid hipMalloc.  The call allocates nothing (no hipMalloc, hipFree or allocating library call):
- * the hidden activations go to one static device array of 2 x 8192 x 256 bf16 (8 MiB) that each GPU
- * the library runs on holds until the process ends; its device address is looked up on the first
- * call on a device.  rows <= 8192 (CFR_EINVAL beyond; cfr_mlp_forward has no such limit), the network's
- * hidden width <= 256.  Every call on one GPU shares that GPU's array: calls that overlap on one GPU
- * (other streams, other threads, other networks) race and must be serialised by the caller; each call
- * writes the activations it reads, so nothing has to be cleared between calls.  x, z as for
- * cfr_mlp_forward; enqueued on `stream`. */
+/* cfr_mlp_forward for callers that cannot allocate device memory (code under hipGraph capture, tight
+ * serving loops, harnesses that forbid hipMalloc): the same launch, which allocates nothing (no hipMalloc,
+ * hipFree or allocating library call), with its row count bounded: rows <= 8192 (CFR_EINVAL beyond;
+ * cfr_mlp_forward has no such limit).  x, z as for cfr_mlp_forward; enqueued on `stream`. */
 cfr_status cfr_mlp_forward_noalloc(cfr_mlp *n, const void *x, int64_t rows, float *z, void *stream);
 /* One Adam step with learning rate lr on the gradients of the last backward call. */
 cfr_status cfr_mlp_adam(cfr_mlp *n, float lr, void *stream);

@@ -484,7 +484,7 @@ class Mlp:
         _check(load().cfr_mlp_forward(self.h, _dptr(x), int(rows), _dptr(z), _stream_arg(stream)))
 
     def forward_noalloc(self, x, rows: int, z, stream=None):
-        """cfr_mlp_forward without device allocation (activations in the library's static scratch; rows <= 8192)."""
+        """cfr_mlp_forward, which allocates no device memory, with a bounded row count (rows <= 8192)."""
         _check(load().cfr_mlp_forward_noalloc(self.h, _dptr(x), int(rows), _dptr(z), _stream_arg(stream)))
 
     def backward(self, x, target, weight, nact, rows: int, idx=None, n_data: int = 0, want_loss=True, stream=None):

@@ -9,18 +9,22 @@
 // part; these definitions are the project's own.
 //
 // Arithmetic: every hidden-layer product runs on v_mfma_f32_32x32x16_bf16 with bfloat16
-// operands and FP32 accumulation.  Stored in bfloat16 (round to nearest even): feature rows,
-// the weight copies the matrix cores read, hidden activations, and the gradients of the hidden
-// pre-activations.  FP32: biases, logits, the loss, all parameter gradients, Adam state.  The
-// four-wide output layer is a per-row dot product on the vector units (64 lanes, 4 hidden units
-// each) fused with the loss.  Every reduction has a fixed order (block partials, then one
-// sequential pass), so a step is bitwise reproducible.
+// operands and FP32 accumulation, one accumulator per output over the inputs in ascending order, so
+// every kernel that computes a layer gives the same bits.  Stored in bfloat16 (round to nearest even): feature rows,
+// the weight copies the matrix cores read (both layouts, refreshed with every parameter update), hidden
+// activations, and the gradients of the hidden pre-activations.  FP32: biases, logits, the loss, all
+// parameter gradients, Adam state.  The four-wide output layer is a per-row dot product on the vector
+// units fused with the loss.  Every reduction has a fixed order (partials, then one sequential pass), so
+// a step is bitwise reproducible.
+//
+// A training step is three launches: k_rows takes a tile of rows through all layers, the loss and back
+// (everything that is local to a row) and leaves activations and gradients behind with rows contiguous,
+// k_wgrad forms the partial sums over rows, k_finish adds them in order and applies Adam.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstdint>
 #include <cstring>
-#include <mutex>
 #include <string>
 #include <vector>
 
@@ -33,11 +37,12 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ uint16_t to_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;  // NaN stays NaN
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+// round to nearest even, NaN stays NaN (v_cvt_pk_bf16_f32)
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint16_t to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+__device__ __forceinline__ uint32_t to_bf16x2(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, bf16x2));
 }
 __device__ __forceinline__ float from_bf16(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
@@ -45,423 +50,614 @@ __device__ __forceinline__ float softplus_f(float z) { return fmaxf(z, 0.f) + lo
 __device__ __forceinline__ float sigmoid_f(float z) { return 1.f / (1.f + expf(-z)); }
 constexpr float LOG_CUT = -30.f;  // below: log softplus(z) = z, sigmoid(z) / softplus(z) = 1
 
-// ---- tiled GEMM ---------------------------------------------------------------------------
-// C[M][N] = sum_k A(m, k) B(k, n) over one K range per block (grid z = split).  A(m, k) is
-// A[m * lda + k] (row major) or, with A_T, At[k * lda + m]; B(k, n) is B[k * ldb + n] or, with
-// B_T, Bt[n * ldb + k].  Block tile 64 x 64 x 32, four wavefronts of 32 x 32 each; both operand
-// tiles are staged in LDS k-contiguous so every MFMA operand is one 16-byte LDS read.
-constexpr int BM = 64, BN = 64, BK = 32, LDK = BK + 8;  // LDS row stride 80 bytes
-
-enum { EPI_BIAS_RELU = 0, EPI_GRAD_MASK = 1, EPI_PARTIAL = 2 };
-
-struct GemmArgs {
-    const uint16_t *A, *B;
-    int M, N, K, lda, ldb, kchunk;
-    const float *bias;      // EPI_BIAS_RELU: relu(acc + bias[n]) -> bf16
-    const uint16_t *mask;   // EPI_GRAD_MASK: acc where mask[m][n] > 0, else 0 -> bf16
-    uint16_t *C16;          // [M][N] bf16
-    float *C32;             // EPI_PARTIAL: [split][M][N]
+// ---- a tile of rows through the network -----------------------------------------------------
+// k_rows takes a block's rows through every layer with the activations in LDS, [row][unit], overwritten
+// layer by layer.  A layer is computed transposed: the weights are the matrix cores' first operand, the
+// activations the second, so that a lane ends up with four consecutive units of one row (accumulator i
+// of lane l holds unit 8 (i / 4) + 4 (l / 32) + i % 4 of row l % 32) and stores them as one 8-byte LDS
+// write.  A wave owns RT x CT tiles of 32 rows x 32 units and reads its weights straight from L2 into
+// registers, PF steps ahead: no wave shares them within the tile except the WR waves of other rows, so
+// staging them in LDS would only add barriers.
+//
+// Tiles (by rows, see rows_tile): 32 rows, one wave per 32 units, for up to 8,192 rows -- there a launch
+// has at most a block per compute unit, so the shortest chain per block wins -- and 128 rows beyond, whose
+// weight reads (0.3 MB per tile in inference) are shared by more rows.  In inference four waves of
+// up to 4 x 2 tiles (half an LDS read and a quarter of a KB of weights per MFMA) leave room for two blocks per
+// compute unit, which hide each other's loads, stores and output layers.
+// Measured: 240,930 rows through 128 -> 3 x 256 -> 4, 377 -> 98 us (810 TFLOP/s; its products alone at the rate of
+// a large library GEMM: 66 us).  A training step on 4,096 rows, 190 -> 60 us (23 launches before): this
+// kernel 39, k_wgrad 12, k_finish 9.
+//
+// The bf16 copies of the hidden weights are kept in the order the matrix cores take them, so that a wave's
+// load of one operand is 1 KB of consecutive memory: tiles of 32 rows, within a tile steps of 16 inputs, of
+// which lane l holds inputs 8 (l / 32) .. + 7 of row l % 32.
+struct Weights {
+    float *theta;             // FP32 parameters
+    uint16_t *fwd, *bwd;      // hidden layer l at wt_off[l]: rows = units (inputs = fan in), and rows = fan in
+                              // (inputs = units)
+    float *out;               // [HID][4] output weights, rounded to bf16 (FP32, so uniform reads are scalar loads)
+    int64_t woff[5], boff[5], wt_off[4];
+    int n_hidden, in_dim, hidden;
 };
 
-template <bool A_T, bool B_T, int EPI>
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
-    __shared__ __attribute__((aligned(16))) uint16_t As[BM][LDK];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[BN][LDK];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
-    const int k_beg = blockIdx.z * g.kchunk;
-    const int k_end = min(g.K, k_beg + g.kchunk);
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    f32x16 acc;
-    for (int i = 0; i < 16; i++) acc[i] = 0.f;
-    for (int k0 = k_beg; k0 < k_end; k0 += BK) {
-        if (!A_T) {  // 64 rows x 4 chunks of 8 k
-            const int m = tid >> 2, kk = (tid & 3) * 8;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (m0 + m < g.M && k0 + kk < k_end) v = *(const uint4 *)(g.A + (int64_t)(m0 + m) * g.lda + k0 + kk);
-            *(uint4 *)&As[m][kk] = v;
-        } else {     // 32 k x 8 chunks of 8 m, transposed into LDS
-            const int kk = tid >> 3, m = (tid & 7) * 8;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (k0 + kk < k_end && m0 + m < g.M) v = *(const uint4 *)(g.A + (int64_t)(k0 + kk) * g.lda + m0 + m);
-            const uint16_t *e = (const uint16_t *)&v;
-#pragma unroll
-            for (int j = 0; j < 8; j++) As[m + j][kk] = e[j];
-        }
-        if (B_T) {   // 64 columns x 4 chunks of 8 k
-            const int n = tid >> 2, kk = (tid & 3) * 8;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (n0 + n < g.N && k0 + kk < k_end) v = *(const uint4 *)(g.B + (int64_t)(n0 + n) * g.ldb + k0 + kk);
-            *(uint4 *)&Bs[n][kk] = v;
-        } else {     // 32 k x 8 chunks of 8 n, transposed into LDS
-            const int kk = tid >> 3, n = (tid & 7) * 8;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (k0 + kk < k_end && n0 + n < g.N) v = *(const uint4 *)(g.B + (int64_t)(k0 + kk) * g.ldb + n0 + n);
-            const uint16_t *e = (const uint16_t *)&v;
-#pragma unroll
-            for (int j = 0; j < 8; j++) Bs[n + j][kk] = e[j];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < BK; ks += 16) {
-            // lane l supplies row (col) l % 32 and k = ks + 8 (l / 32) .. + 7 of both operands
-            const bf16x8 a = *(const bf16x8 *)&As[wm + (lane & 31)][ks + (lane >> 5) * 8];
-            const bf16x8 b = *(const bf16x8 *)&Bs[wn + (lane & 31)][ks + (lane >> 5) * 8];
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    // accumulator i of lane l holds row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32
-    const int col = n0 + wn + (lane & 31);
-    if (col >= g.N) return;
-#pragma unroll
-    for (int i = 0; i < 16; i++) {
-        const int row = m0 + wm + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
-        if (row >= g.M) continue;
-        float x = acc[i];
-        const int64_t o = (int64_t)row * g.N + col;
-        if (EPI == EPI_BIAS_RELU) {
-            g.C16[o] = to_bf16(fmaxf(x + g.bias[col], 0.f));
-        } else if (EPI == EPI_GRAD_MASK) {
-            g.C16[o] = to_bf16(from_bf16(g.mask[o]) > 0.f ? x : 0.f);
-        } else {
-            g.C32[(int64_t)blockIdx.z * g.M * g.N + o] = x;
-        }
-    }
+// place of (row, input) in that order, `inputs` inputs per row
+__device__ __forceinline__ int64_t operand_at(int row, int input, int inputs) {
+    return ((int64_t)(row >> 5) * (inputs >> 4) + (input >> 4)) * 512 + ((row & 31) + 32 * ((input >> 3) & 1)) * 8 +
+           (input & 7);
 }
 
-// ---- output layer, loss and its gradient ---------------------------------------------------
-struct HeadArgs {
-    const uint16_t *H;      // [rows][hidden] last hidden activations
-    const uint16_t *W;      // [hidden][4] bf16 output weights
-    const float *b;         // [4]
-    const float *T;         // [rows][4] target distribution (training)
-    const float *w;         // [rows] row weights or nullptr (training)
-    const uint8_t *nact;    // [rows] legal actions (training; clamped to 1..4)
-    const float *inv_wsum;  // device scalar 1 / sum of row weights (training)
+struct RowsArgs {
+    Weights W;
+    const uint16_t *x;        // [.][in_dim] bf16
     int rows;
-    float *z;               // [rows][4] logits (inference)
-    uint16_t *dA;           // [rows][hidden] gradient of the last hidden pre-activation (training)
-    float *part;            // [gridDim.x][hidden * 4 + 5] block partials (training)
+    float *z;                 // inference: logits [rows][4]
+    // training: row r of the minibatch is row idx[r] (clamped into [0, n_data)) of x, T, w, nact
+    const int32_t *idx;
+    int64_t n_data;
+    const float *T, *w;       // [.][4] targets, [.] weights or nullptr
+    const uint8_t *nact;      // [.] legal actions (clamped to 1..4)
+    const float *inv_wsum;    // 1 / sum of the minibatch's weights, or nullptr: every block sums them itself
+    int64_t ld;               // rows of the transposed arrays, a multiple of the tile; rows past the last are zero
+    // transposed: units (or input columns) as rows, minibatch rows as inputs, in operand order
+    uint16_t *Xt;             // inputs
+    uint16_t *H[4], *Ht[4];   // [ld][HID] and transposed activations
+    uint16_t *dAt[4];         // transposed gradients of the pre-activations
+    float *dz, *ce, *wr;      // [ld][4], [ld], [ld]: logit gradients, cross entropy and weight of each row
+    float *bias_part[4];      // [ld / BIAS_ROWS][HID] sums of dA over BIAS_ROWS rows each
 };
 
-template <int HPL, bool TRAIN>
-__global__ __launch_bounds__(256) void k_head(HeadArgs a) {
-    constexpr int HID = 64 * HPL;
-    constexpr int NP = HID * 4 + 5;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float wk[HPL][4];
-#pragma unroll
-    for (int j = 0; j < HPL; j++)
-#pragma unroll
-        for (int c = 0; c < 4; c++) wk[j][c] = from_bf16(a.W[(lane * HPL + j) * 4 + c]);
-    float gw[HPL][4], gb[4] = {0.f, 0.f, 0.f, 0.f}, gl = 0.f;
-#pragma unroll
-    for (int j = 0; j < HPL; j++)
-#pragma unroll
-        for (int c = 0; c < 4; c++) gw[j][c] = 0.f;
-    const float invw = TRAIN ? *a.inv_wsum : 0.f;
-    for (int r = blockIdx.x * 4 + wave; r < a.rows; r += gridDim.x * 4) {
-        float h[HPL];
-        const uint16_t *hr = a.H + (int64_t)r * HID + lane * HPL;
-#pragma unroll
-        for (int j = 0; j < HPL; j++) h[j] = from_bf16(hr[j]);
-        float z[4];
-#pragma unroll
-        for (int c = 0; c < 4; c++) {
-            float s = 0.f;
-#pragma unroll
-            for (int j = 0; j < HPL; j++) s = fmaf(h[j], wk[j][c], s);
-            z[c] = s;
-        }
-        // butterfly: every lane ends with the same sums
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-            for (int c = 0; c < 4; c++) z[c] += __shfl_xor(z[c], off, 64);
-#pragma unroll
-        for (int c = 0; c < 4; c++) z[c] += a.b[c];
-        if (!TRAIN) {
-            if (lane < 4) a.z[(int64_t)r * 4 + lane] = lane == 0 ? z[0] : lane == 1 ? z[1] : lane == 2 ? z[2] : z[3];
-            continue;
-        }
-        const int n = min(max((int)a.nact[r], 1), 4);
-        const float wr = (a.w ? a.w[r] : 1.f) * invw;
-        float ls[4], lmax = -INFINITY;
-#pragma unroll
-        for (int c = 0; c < 4; c++) {
-            ls[c] = z[c] < LOG_CUT ? z[c] : logf(softplus_f(z[c]));
-            if (c < n) lmax = fmaxf(lmax, ls[c]);
-        }
-        float se = 0.f;
-#pragma unroll
-        for (int c = 0; c < 4; c++)
-            if (c < n) se += expf(ls[c] - lmax);
-        const float lS = lmax + logf(se);
-        float tsum = 0.f, ce = 0.f, t[4];
-#pragma unroll
-        for (int c = 0; c < 4; c++) {
-            t[c] = c < n ? a.T[(int64_t)r * 4 + c] : 0.f;
-            tsum += t[c];
-            ce -= t[c] * (ls[c] - lS);
-        }
-        float dz[4];
-#pragma unroll
-        for (int c = 0; c < 4; c++) {
-            if (c < n) {
-                const float ratio = z[c] < LOG_CUT ? 1.f : sigmoid_f(z[c]) / softplus_f(z[c]);
-                const float lsig = -softplus_f(-z[c]);
-                dz[c] = wr * (-t[c] * ratio + tsum * expf(lsig - lS));
-            } else {
-                dz[c] = 0.f;
-            }
-        }
-        uint16_t *dr = a.dA + (int64_t)r * HID + lane * HPL;
-#pragma unroll
-        for (int j = 0; j < HPL; j++) {
-            float d = 0.f;
-#pragma unroll
-            for (int c = 0; c < 4; c++) d = fmaf(dz[c], wk[j][c], d);
-            dr[j] = to_bf16(h[j] > 0.f ? d : 0.f);
-#pragma unroll
-            for (int c = 0; c < 4; c++) gw[j][c] = fmaf(h[j], dz[c], gw[j][c]);
-        }
-        if (lane == 0) {
-#pragma unroll
-            for (int c = 0; c < 4; c++) gb[c] += dz[c];
-            gl += wr * ce;
-        }
-    }
-    if (!TRAIN) return;
-    __shared__ float red[4][NP];
-#pragma unroll
-    for (int j = 0; j < HPL; j++)
-#pragma unroll
-        for (int c = 0; c < 4; c++) red[wave][(lane * HPL + j) * 4 + c] = gw[j][c];
-    if (lane == 0) {
-        for (int c = 0; c < 4; c++) red[wave][HID * 4 + c] = gb[c];
-        red[wave][HID * 4 + 4] = gl;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < NP; i += 256)
-        a.part[(int64_t)blockIdx.x * NP + i] = ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
+constexpr int BIAS_ROWS = 16;   // rows per bias partial
+constexpr int WSUM_ROWS = 8192; // up to here each block sums the row weights itself
+
+// row of the training arrays that minibatch row r stands for
+__device__ __forceinline__ int64_t data_row(const int32_t *idx, int64_t n_data, int r) {
+    return idx ? min(max((int64_t)idx[r], (int64_t)0), n_data - 1) : (int64_t)r;
 }
 
-// 1 / sum of the row weights (rows when there are none); one block, fixed order
-__global__ __launch_bounds__(256) void k_inv_wsum(const float *w, int rows, float *out) {
-    __shared__ float s[256];
-    float acc = 0.f;
-    for (int r = threadIdx.x; r < rows; r += 256) acc += w ? w[r] : 1.f;
-    s[threadIdx.x] = acc;
+// 1 / sum of the row weights (rows when there are none) in fixed order: 256 strided sums, then a tree; red
+// holds 256 floats.  Every thread of the block calls it.
+__device__ __forceinline__ float inv_weight_sum(const float *w, const int32_t *idx, int64_t n_data, int rows,
+                                                float *red) {
+    for (int t = threadIdx.x; t < 256; t += blockDim.x) {
+        float acc = 0.f;
+        if (w) {
+            constexpr int U = 16;
+            for (int b = t; b < rows; b += 256 * U) {
+                int64_t at[U];
+                float x[U];
+#pragma unroll
+                for (int i = 0; i < U; i++) at[i] = data_row(idx, n_data, min(b + i * 256, rows - 1));
+#pragma unroll
+                for (int i = 0; i < U; i++) x[i] = w[at[i]];
+#pragma unroll
+                for (int i = 0; i < U; i++) acc = b + i * 256 < rows ? acc + x[i] : acc;
+            }
+        } else {
+            for (int r = t; r < rows; r += 256) acc += 1.f;
+        }
+        red[t] = acc;
+    }
     __syncthreads();
     for (int k = 128; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) s[threadIdx.x] += s[threadIdx.x + k];
+        if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[0] = s[0] > 0.f ? 1.f / s[0] : 0.f;
+    const float s = red[0];
+    __syncthreads();
+    return s > 0.f ? 1.f / s : 0.f;
 }
 
-// part[b][n] = sum of rows [b * chunk, (b + 1) * chunk) of column n (bias gradients)
-__global__ __launch_bounds__(256) void k_colsum(const uint16_t *X, int rows, int N, int chunk, float *part) {
-    const int r0 = blockIdx.x * chunk, r1 = min(rows, r0 + chunk);
-    for (int n = threadIdx.x; n < N; n += 256) {
-        float s = 0.f;
-#pragma unroll 8
-        for (int r = r0; r < r1; r++) s += from_bf16(X[(int64_t)r * N + n]);
-        part[(int64_t)blockIdx.x * N + n] = s;
+__global__ __launch_bounds__(256) void k_inv_wsum(const float *w, const int32_t *idx, int64_t n_data, int rows,
+                                                  float *out) {
+    __shared__ float red[256];
+    const float x = inv_weight_sum(w, idx, n_data, rows, red);
+    if (threadIdx.x == 0) out[0] = x;
+}
+
+// acc[r][c] += (32 units at n0 + 32 c) x (32 rows at m0 + 32 r) over K inputs: W in operand order,
+// act [.][LDA] in LDS, inputs in ascending steps of 16
+// (buffer loads: the weights of the next PF steps are requested while this group is multiplied, and plain
+// loads are moved back to their first use).  The buffer ends with the matrix, `units` rows of K inputs.
+template <int RT, int CT, int LDA, int PF>
+__device__ __forceinline__ void layer_mfma(const uint16_t *W, int units, int K, const uint16_t *act, int m0, int n0,
+                                           f32x16 (&acc)[RT][CT]) {
+    const int lane = threadIdx.x & 63, row = lane & 31, k8 = (lane >> 5) * 8;
+#pragma unroll
+    for (int r = 0; r < RT; r++)
+#pragma unroll
+        for (int c = 0; c < CT; c++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) acc[r][c][i] = 0.f;
+    // lane l supplies unit (row) l % 32 and inputs 8 (l / 32) .. + 7 of each step
+    constexpr int RAW_32BIT = 0x20000;   // buffer descriptor: untyped 32-bit elements
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)W, 0, units * K * 2, RAW_32BIT);
+    auto weights = [&](int c, int k) {   // byte offsets: 1 KB per tile and step
+        return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                              rsrc, lane * 16, ((n0 >> 5) + c) * K * 64 + k * 64, 0));
+    };
+    const uint16_t *ap = act + (m0 + row) * LDA + k8;
+    bf16x8 w[PF][CT];
+#pragma unroll
+    for (int p = 0; p < PF; p++)
+#pragma unroll
+        for (int c = 0; c < CT; c++) w[p][c] = weights(c, p * 16);
+    for (int k0 = 0; k0 < K; k0 += 16 * PF) {
+        const int kn = k0 + 16 * PF < K ? k0 + 16 * PF : 0;   // the last group requests the first again, unused
+#pragma unroll
+        for (int p = 0; p < PF; p++) {
+            bf16x8 b[RT];
+#pragma unroll
+            for (int r = 0; r < RT; r++) b[r] = *(const bf16x8 *)(ap + r * 32 * LDA + k0 + p * 16);
+            bf16x8 a[CT];
+#pragma unroll
+            for (int c = 0; c < CT; c++) {
+                a[c] = w[p][c];
+                w[p][c] = weights(c, kn + p * 16);
+            }
+#pragma unroll
+            for (int r = 0; r < RT; r++)
+#pragma unroll
+                for (int c = 0; c < CT; c++)
+                    acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[c], b[r], acc[r][c], 0, 0, 0);
+        }
     }
 }
 
-// out[j] = sum over b of part[b * stride + j], in order of b
-__global__ void k_reduce(const float *part, int nb, int64_t stride, int n, float *out) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    float s = 0.f;
-#pragma unroll 8
-    for (int b = 0; b < nb; b++) s += part[(int64_t)b * stride + j];
-    out[j] = s;
+// The output layer's sums as the 64-lane butterfly adds them: leaf l is the FMA chain over units
+// l * HPL .. + HPL - 1, and leaves combine by index bits 5, 4, ..., 0.  One thread takes the leaves of
+// residue j = l % 4, l = j + 4 t, and returns their sum (bits 5 .. 2); bits 1 and 0 combine the residues.
+struct Four { float c[4]; };
+template <int HPL, int BIT, int T>
+__device__ __forceinline__ Four head_leaves(const uint16_t *h, const float *w, int j) {
+    Four s;
+    if constexpr (BIT == 4) {
+        const int u = (j + 4 * T) * HPL;
+#pragma unroll
+        for (int c = 0; c < 4; c++) s.c[c] = 0.f;
+#pragma unroll
+        for (int q = 0; q < HPL; q++) {
+            const float x = from_bf16(h[u + q]);
+#pragma unroll
+            for (int c = 0; c < 4; c++) s.c[c] = fmaf(x, w[(u + q) * 4 + c], s.c[c]);
+        }
+    } else {
+        const Four a = head_leaves<HPL, BIT + 1, T>(h, w, j);
+        const Four b = head_leaves<HPL, BIT + 1, T | (1 << BIT)>(h, w, j);
+#pragma unroll
+        for (int c = 0; c < 4; c++) s.c[c] = a.c[c] + b.c[c];
+    }
+    return s;
 }
 
-// Adam (Kingma and Ba 2015, Algorithm 1) on the FP32 master copy; refreshes the bf16 copy.
-// c1 = 1 / (1 - beta1^t), c2 = 1 / (1 - beta2^t) for step t.
-__global__ void k_adam(float *theta, const float *g, float *m, float *v, uint16_t *theta16, int64_t n, float lr,
-                       float b1, float b2, float eps, float c1, float c2) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float th = theta[i] - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-    theta[i] = th;
-    theta16[i] = to_bf16(th);
+// logits of one row by one wave (every lane returns them): the same sums, lane l holding leaf l
+template <int HPL>
+__device__ __forceinline__ void head_row(const float (&h)[HPL], const float (&wk)[HPL][4], const float *b, float (&z)[4]) {
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < HPL; j++) s = fmaf(h[j], wk[j][c], s);
+        z[c] = s;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int c = 0; c < 4; c++) z[c] += __shfl_xor(z[c], off, 64);
+#pragma unroll
+    for (int c = 0; c < 4; c++) z[c] += b[c];
 }
 
-__global__ void k_to_bf16(const float *x, uint16_t *y, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] = to_bf16(x[i]);
+// Cross entropy of minibatch row r and its gradient dz by the logits z; with `store`, both and the row's
+// weight go to memory.
+__device__ __forceinline__ void loss_row(const RowsArgs &f, int r, float invw, const float (&z)[4], bool store,
+                                         float (&dz)[4]) {
+    const int64_t src = data_row(f.idx, f.n_data, r);
+    const int n = min(max((int)f.nact[src], 1), 4);
+    const float wr = (f.w ? f.w[src] : 1.f) * invw;
+    float T[4];
+#pragma unroll
+    for (int c = 0; c < 4; c++) T[c] = f.T[src * 4 + c];
+    float ls[4], lmax = -INFINITY;
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+        ls[c] = z[c] < LOG_CUT ? z[c] : logf(softplus_f(z[c]));
+        if (c < n) lmax = fmaxf(lmax, ls[c]);
+    }
+    float se = 0.f;
+#pragma unroll
+    for (int c = 0; c < 4; c++)
+        if (c < n) se += expf(ls[c] - lmax);
+    const float lS = lmax + logf(se);
+    float tsum = 0.f, ce = 0.f, t[4];
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+        t[c] = c < n ? T[c] : 0.f;
+        tsum += t[c];
+        ce -= t[c] * (ls[c] - lS);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+        if (c < n) {
+            const float ratio = z[c] < LOG_CUT ? 1.f : sigmoid_f(z[c]) / softplus_f(z[c]);
+            const float lsig = -softplus_f(-z[c]);
+            dz[c] = wr * (-t[c] * ratio + tsum * expf(lsig - lS));
+        } else {
+            dz[c] = 0.f;
+        }
+    }
+    if (!store) return;
+    *(float4 *)(f.dz + (int64_t)r * 4) = make_float4(dz[0], dz[1], dz[2], dz[3]);
+    f.ce[r] = ce;
+    f.wr[r] = wr;
 }
 
-// ---- fused inference ------------------------------------------------------------------------
-// Inference needs no activations outside the kernel, so one launch runs every layer: a block takes
-// FB_ROWS rows, keeps their activations in LDS from the input row to the last hidden layer, and
-// writes only the four logits.  Each hidden layer is the product of the LDS activations with the
-// layer's weights, streamed through LDS in chunks of 32 input units (double-buffered, the next
-// chunk's global loads in flight while the matrix cores work on the current one); the four waves
-// each own a 64-row x HID/2-column slab (2 x HID/64 accumulators of 32 x 32).  The arithmetic is the
-// layer-by-layer path's, in its order: the same MFMA on the same 16-wide k steps from k = 0 up,
-// relu(acc + bias) rounded to bf16, and the output layer's per-lane FMA chain, butterfly and bias
-// of k_head, so the logits are bitwise those of the layered kernels.
-constexpr int FB_ROWS = 128, FB_BK = 32, FB_LDB = FB_BK + 8;
+// four consecutive units of a row as bf16, one 8-byte store
+__device__ __forceinline__ void store4(uint16_t *p, float a, float b, float c, float d) {
+    *(uint2 *)p = make_uint2(to_bf16x2(a, b), to_bf16x2(c, d));
+}
 
-struct FusedArgs {
-    const uint16_t *x;        // [rows][K0] bf16
-    const uint16_t *wt;       // hidden layers' weights transposed, layer l at wt_off[l]: [HID][fin_l]
-    const float *theta;       // FP32 parameters (biases at boff[l])
-    const uint16_t *w_out;    // [HID][4] bf16 output weights
-    const float *b_out;       // [4]
-    int64_t wt_off[4], boff[4];
-    int rows, n_hidden;
-    float *z;                 // [rows][4]
+// RT x CT tiles per wave, WR waves along the rows, HID / 32 / CT along the units
+template <int HID, int K0, int RT, int CT, int WR, bool TRAIN>
+__global__ __launch_bounds__(64 * WR * (HID / 32 / CT), TRAIN || RT * WR == 1 ? 1 : 2) void k_rows(RowsArgs f) {
+    constexpr int WC = HID / 32 / CT, NW = WR * WC, NT = NW * 64;
+    constexpr int ROWS = 32 * RT * WR;
+    constexpr int LDA = (K0 > HID ? K0 : HID) + 8;   // rows stay 16-byte aligned and spread over the banks
+    constexpr int PF = RT == 1 && CT == 1 ? (K0 < 128 || HID < 128 ? 4 : 8) : 4;
+    constexpr int HPL = HID / 64;
+    __shared__ __attribute__((aligned(16))) uint16_t act[ROWS * LDA];
+    __shared__ float red[TRAIN ? 256 : ROWS >= 64 ? ROWS * 16 : 1];
+    __shared__ __attribute__((aligned(16))) float bias[4 * HID];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r0 = blockIdx.x * ROWS;
+    // the tile's input rows (zeros past the last), up to eight loads per thread in flight
+    constexpr int PIECES = ROWS * (K0 / 8), IN_FLIGHT = (PIECES + NT - 1) / NT < 8 ? (PIECES + NT - 1) / NT : 8;
+    for (int i0 = tid; i0 < PIECES; i0 += NT * IN_FLIGHT) {
+        uint4 v[IN_FLIGHT];
+#pragma unroll
+        for (int p = 0; p < IN_FLIGHT; p++) {
+            const int i = min(i0 + p * NT, PIECES - 1), r = min(r0 + i / (K0 / 8), f.rows - 1), c = (i % (K0 / 8)) * 8;
+            // (any alignment of x)
+            __builtin_memcpy(&v[p], f.x + (TRAIN ? data_row(f.idx, f.n_data, r) : (int64_t)r) * K0 + c, 16);
+        }
+#pragma unroll
+        for (int p = 0; p < IN_FLIGHT; p++) {
+            const int i = i0 + p * NT, r = i / (K0 / 8), c = (i % (K0 / 8)) * 8;
+            if (i < PIECES) *(uint4 *)&act[r * LDA + c] = r0 + r < f.rows ? v[p] : make_uint4(0, 0, 0, 0);
+        }
+    }
+    for (int l = 0; l < f.W.n_hidden; l++)
+        for (int i = tid; i < HID; i += NT) bias[l * HID + i] = f.W.theta[f.W.boff[l] + i];
+    // [row][unit] in LDS -> units as rows and rows as inputs in operand order in global memory (eight rows
+    // of a unit per store), rows past the last as zeros
+    auto put_transposed = [&](uint16_t *dst, int units) {
+        for (int i = tid; i < units * (ROWS / 8); i += NT) {
+            const int u = i % units, r = i / units * 8;
+            uint16_t e[8];
+#pragma unroll
+            for (int j = 0; j < 8; j++) e[j] = r0 + r + j < f.rows ? act[(r + j) * LDA + u] : (uint16_t)0;
+            uint4 v;
+            __builtin_memcpy(&v, e, 16);
+            *(uint4 *)(dst + operand_at(u, r0 + r, (int)f.ld)) = v;
+        }
+    };
+    const float invw = TRAIN ? (f.inv_wsum ? *f.inv_wsum : inv_weight_sum(f.w, f.idx, f.n_data, f.rows, red)) : 0.f;
+    __syncthreads();
+    if constexpr (TRAIN) put_transposed(f.Xt, K0);
+    const int m0 = wave / WC * (32 * RT), n0 = wave % WC * (32 * CT);
+    const int unit4 = (lane >> 5) * 4, mrow = lane & 31;
+    f32x16 acc[RT][CT];
+    for (int l = 0; l < f.W.n_hidden; l++) {
+        layer_mfma<RT, CT, LDA, PF>(f.W.fwd + f.W.wt_off[l], HID, l == 0 ? K0 : HID, act, m0, n0, acc);
+        __syncthreads();   // every wave has read this layer's input: overwrite it
+#pragma unroll
+        for (int c = 0; c < CT; c++)
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                const int n = n0 + c * 32 + g * 8 + unit4;
+                const float4 b = *(const float4 *)&bias[l * HID + n];
+#pragma unroll
+                for (int r = 0; r < RT; r++) {
+                    const f32x16 &x = acc[r][c];
+                    store4(&act[(m0 + r * 32 + mrow) * LDA + n], fmaxf(x[4 * g] + b.x, 0.f), fmaxf(x[4 * g + 1] + b.y, 0.f),
+                           fmaxf(x[4 * g + 2] + b.z, 0.f), fmaxf(x[4 * g + 3] + b.w, 0.f));
+                }
+            }
+        __syncthreads();
+        if constexpr (TRAIN) {
+            for (int i = tid; i < ROWS * (HID / 8); i += NT) {
+                const int r = i / (HID / 8), c = (i % (HID / 8)) * 8;
+                *(uint4 *)(f.H[l] + (int64_t)(r0 + r) * HID + c) = *(const uint4 *)&act[r * LDA + c];
+            }
+            put_transposed(f.Ht[l], HID);
+        }
+    }
+    const float *w_out = f.W.out;
+    const float *b_out = f.W.theta + f.W.boff[f.W.n_hidden];
+    if constexpr (!TRAIN && ROWS >= 64) {
+        // 64 rows and one residue per wave at a time, so the output weights are uniform over the wave
+#pragma unroll 1
+        for (int p = wave; p < ROWS / 16; p += NW) {
+            // (a wave's items differ in the residue, so its weights are not kept in registers)
+            const int j = p / (ROWS / 64), r = p % (ROWS / 64) * 64 + lane;
+            const Four s = head_leaves<HPL, 0, 0>(act + r * LDA, w_out, j);
+            *(float4 *)&red[(r * 4 + j) * 4] = make_float4(s.c[0], s.c[1], s.c[2], s.c[3]);
+        }
+        __syncthreads();
+        for (int i = tid; i < ROWS * 4; i += NT) {
+            const int r = i / 4, c = i % 4;
+            const float *s = &red[r * 16 + c];
+            if (r0 + r < f.rows) f.z[(int64_t)(r0 + r) * 4 + c] = ((s[0] + s[8]) + (s[4] + s[12])) + b_out[c];
+        }
+    } else {
+        float wk[HPL][4];
+#pragma unroll
+        for (int j = 0; j < HPL; j++)
+#pragma unroll
+            for (int c = 0; c < 4; c++) wk[j][c] = w_out[(lane * HPL + j) * 4 + c];
+        constexpr int RPW = ROWS / NW;   // this wave's rows: wave, wave + NW, ...
+        static_assert(RPW <= 64, "a lane per row of the wave");
+        float zl[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int q = 0; q < RPW; q++) {
+            const uint16_t *hr = &act[(wave + q * NW) * LDA + lane * HPL];
+            float h[HPL], z[4];
+#pragma unroll
+            for (int j = 0; j < HPL; j++) h[j] = from_bf16(hr[j]);
+            head_row<HPL>(h, wk, b_out, z);
+#pragma unroll
+            for (int c = 0; c < 4; c++) zl[c] = lane == q ? z[c] : zl[c];
+        }
+        // lane q holds the logits of the wave's row q
+        const int r = r0 + wave + min(lane, RPW - 1) * NW;
+        const bool in = lane < RPW && r < f.rows;
+        if constexpr (!TRAIN) {
+            for (int c = 0; c < 4; c++)
+                if (in) f.z[(int64_t)r * 4 + c] = zl[c];
+        } else {
+            float dz[4];
+            loss_row(f, min(r, f.rows - 1), invw, zl, in, dz);
+            __syncthreads();   // the last activations are stored before gradients replace them
+#pragma unroll 4
+            for (int q = 0; q < RPW; q++) {
+                uint16_t *hr = &act[(wave + q * NW) * LDA + lane * HPL];
+                float g[4];
+#pragma unroll
+                for (int c = 0; c < 4; c++) g[c] = __shfl(dz[c], q, 64);
+                const bool pad = r0 + wave + q * NW >= f.rows;   // no gradient
+#pragma unroll
+                for (int j = 0; j < HPL; j++) {
+                    float d = 0.f;
+#pragma unroll
+                    for (int c = 0; c < 4; c++) d = fmaf(g[c], wk[j][c], d);
+                    hr[j] = to_bf16(!pad && from_bf16(hr[j]) > 0.f ? d : 0.f);
+                }
+            }
+        }
+        if constexpr (TRAIN) {
+            // act holds the gradient of the last hidden pre-activation: store it, then the one before it is
+            // (dA W_l^T) where the activation is positive, and so on
+            for (int l = f.W.n_hidden - 1;; l--) {
+                __syncthreads();
+                put_transposed(f.dAt[l], HID);
+                for (int i = tid; i < HID * (ROWS / BIAS_ROWS); i += NT) {
+                    const int u = i % HID, q = i / HID;
+                    float sum = 0.f;
+#pragma unroll
+                    for (int r = 0; r < BIAS_ROWS; r++)
+                        if (r0 + q * BIAS_ROWS + r < f.rows) sum += from_bf16(act[(q * BIAS_ROWS + r) * LDA + u]);
+                    f.bias_part[l][(int64_t)(r0 / BIAS_ROWS + q) * HID + u] = sum;
+                }
+                if (l == 0) break;
+                layer_mfma<RT, CT, LDA, PF>(f.W.bwd + f.W.wt_off[l], HID, HID, act, m0, n0, acc);
+                __syncthreads();
+#pragma unroll
+                for (int c = 0; c < CT; c++)
+#pragma unroll
+                    for (int g = 0; g < 4; g++) {
+                        const int n = n0 + c * 32 + g * 8 + unit4;
+#pragma unroll
+                        for (int r = 0; r < RT; r++) {
+                            const int m = m0 + r * 32 + mrow;
+                            const uint2 k = *(const uint2 *)(f.H[l - 1] + (int64_t)(r0 + m) * HID + n);
+                            const f32x16 &x = acc[r][c];
+                            store4(&act[m * LDA + n], from_bf16((uint16_t)k.x) > 0.f ? x[4 * g] : 0.f,
+                                   from_bf16((uint16_t)(k.x >> 16)) > 0.f ? x[4 * g + 1] : 0.f,
+                                   from_bf16((uint16_t)k.y) > 0.f ? x[4 * g + 2] : 0.f,
+                                   from_bf16((uint16_t)(k.y >> 16)) > 0.f ? x[4 * g + 3] : 0.f);
+                        }
+                    }
+            }
+        }
+    }
+}
+
+// ---- gradients: sums over rows ---------------------------------------------------------------
+constexpr int HEAD_BLOCKS = 256;
+
+struct GradArgs {
+    Weights W;
+    int rows, splits, kchunk, head_blocks;
+    int64_t ld;
+    const uint16_t *in[4];    // transposed inputs of hidden layer l (operand order, as RowsArgs)
+    const uint16_t *dAt[4];   // and gradients
+    const uint16_t *H;        // [ld][HID] last activations
+    const float *dz, *ce, *wr;
+    float *w_part[4];         // [splits][fan in][HID]
+    float *bias_part[4];      // [ceil(rows / BIAS_ROWS)][HID]
+    float *head_part;         // [head_blocks][HID * 4 + 5]: output weights, biases, loss
+    int task0[5];             // first task of each hidden layer's weight gradient; task0[n_hidden] tasks in all
+    float *grad, *loss, *m, *v;
+    float lr, b1, b2, eps, c1, c2;   // Adam
 };
 
-template <int HID, int K0>
-__global__ __launch_bounds__(256) void k_mlp_fused(FusedArgs f) {
-    constexpr int LDA = (K0 > HID ? K0 : HID) + 8;   // LDS row stride (bf16), rows stay 16-byte aligned
-    constexpr int CT = HID / 64;                     // 32-wide column tiles per wave
-    __shared__ __attribute__((aligned(16))) uint16_t act[FB_ROWS * LDA];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][HID * FB_LDB];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int r0 = blockIdx.x * FB_ROWS;
-    // the block's input rows (zeros past the last row)
-    for (int i = tid; i < FB_ROWS * K0 / 8; i += 256) {
-        const int r = i / (K0 / 8), c = (i % (K0 / 8)) * 8;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (r0 + r < f.rows) v = *(const uint4 *)(f.x + (int64_t)(r0 + r) * K0 + c);
-        *(uint4 *)&act[r * LDA + c] = v;
-    }
-    const int wm = (wave >> 1) * 64, wn = (wave & 1) * (HID / 2);
-    for (int l = 0; l < f.n_hidden; l++) {
-        const int K = l == 0 ? K0 : HID;
-        const uint16_t *W = f.wt + f.wt_off[l];
-        // chunk k0 of W^T: HID rows of 32 units = HID * 4 16-byte pieces, CT per thread
-        uint4 pre[CT];
-        auto load_chunk = [&](int k0) {
-#pragma unroll
-            for (int j = 0; j < CT; j++) {
-                const int idx = tid + j * 256, n = idx >> 2, q = (idx & 3) * 8;
-                pre[j] = *(const uint4 *)(W + (int64_t)n * K + k0 + q);
-            }
-        };
-        auto store_chunk = [&](int buf) {
-#pragma unroll
-            for (int j = 0; j < CT; j++) {
-                const int idx = tid + j * 256, n = idx >> 2, q = (idx & 3) * 8;
-                *(uint4 *)&Bs[buf][n * FB_LDB + q] = pre[j];
-            }
-        };
-        f32x16 acc[2][CT];
-#pragma unroll
-        for (int a = 0; a < 2; a++)
-#pragma unroll
-            for (int b = 0; b < CT; b++)
-#pragma unroll
-                for (int i = 0; i < 16; i++) acc[a][b][i] = 0.f;
-        load_chunk(0);
-        store_chunk(0);
-        __syncthreads();
-        const int nk = K / FB_BK;
-        for (int kc = 0; kc < nk; kc++) {
-            const int buf = kc & 1;
-            if (kc + 1 < nk) load_chunk((kc + 1) * FB_BK);
-#pragma unroll
-            for (int ks = 0; ks < FB_BK; ks += 16) {
-                // lane l supplies row (column) l % 32 and k = ks + 8 (l / 32) .. + 7 of both operands
-                bf16x8 av[2], bv[CT];
-#pragma unroll
-                for (int a = 0; a < 2; a++)
-                    av[a] = *(const bf16x8 *)&act[(wm + a * 32 + (lane & 31)) * LDA + kc * FB_BK + ks + (lane >> 5) * 8];
-#pragma unroll
-                for (int b = 0; b < CT; b++)
-                    bv[b] = *(const bf16x8 *)&Bs[buf][(wn + b * 32 + (lane & 31)) * FB_LDB + ks + (lane >> 5) * 8];
-#pragma unroll
-                for (int a = 0; a < 2; a++)
-#pragma unroll
-                    for (int b = 0; b < CT; b++)
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[a], bv[b], acc[a][b], 0, 0, 0);
-            }
-            if (kc + 1 < nk) store_chunk(buf ^ 1);
-            __syncthreads();
-        }
-        // every wave has read this layer's input: overwrite it with relu(acc + bias) in bf16
-        // (accumulator i of lane l holds row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32)
-        const float *bias = f.theta + f.boff[l];
-#pragma unroll
-        for (int b = 0; b < CT; b++) {
-            const int col = wn + b * 32 + (lane & 31);
-            const float bc = bias[col];
-#pragma unroll
-            for (int a = 0; a < 2; a++)
-#pragma unroll
-                for (int i = 0; i < 16; i++) {
-                    const int row = wm + a * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
-                    act[row * LDA + col] = to_bf16(fmaxf(acc[a][b][i] + bc, 0.f));
+// Blocks [0, ceil(tasks / 4)): a wave per 64 x 64 tile of a layer's weight gradient and range of kchunk rows,
+// in[m][r] dA[n][r] summed over r in ascending steps of 16; both are in operand order, so they go from L2
+// straight to the matrix cores, 64 rows requested ahead.  The blocks after that: one each of the output layer's partials,
+// rows b * 4 + w, + 4 * head_blocks, ... of wave w in order, then waves 0 to 3.
+template <int HID>
+__global__ __launch_bounds__(256) void k_wgrad(GradArgs f) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int L = f.W.n_hidden;
+    const int mma_blocks = (f.task0[L] + 3) / 4;
+    if ((int)blockIdx.x >= mma_blocks) {
+        const int b = blockIdx.x - mma_blocks;
+        constexpr int NP = HID * 4 + 5;
+        float *out = f.head_part + (int64_t)b * NP;
+        if (tid < HID) {
+            float tot[4];
+            for (int w = 0; w < 4; w++) {
+                float g[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+                for (int r = b * 4 + w; r < f.rows; r += f.head_blocks * 4) {
+                    const float h = from_bf16(f.H[(int64_t)r * HID + tid]);
+                    const float4 d = *(const float4 *)(f.dz + (int64_t)r * 4);
+                    g[0] = fmaf(h, d.x, g[0]); g[1] = fmaf(h, d.y, g[1]);
+                    g[2] = fmaf(h, d.z, g[2]); g[3] = fmaf(h, d.w, g[3]);
                 }
+#pragma unroll
+                for (int c = 0; c < 4; c++) tot[c] = w == 0 ? g[c] : tot[c] + g[c];
+            }
+            *(float4 *)(out + tid * 4) = make_float4(tot[0], tot[1], tot[2], tot[3]);
         }
-        __syncthreads();
+        if (tid < 5) {
+            float tot = 0.f;
+            for (int w = 0; w < 4; w++) {
+                float g = 0.f;
+                for (int r = b * 4 + w; r < f.rows; r += f.head_blocks * 4) {
+                    if (tid < 4) g += f.dz[(int64_t)r * 4 + tid];
+                    else g = fmaf(f.wr[r], f.ce[r], g);
+                }
+                tot = w == 0 ? g : tot + g;
+            }
+            out[HID * 4 + tid] = tot;
+        }
+        return;
     }
-    // output layer as k_head computes it: lane l holds hidden units l * HPL .. + HPL - 1
-    constexpr int HPL = HID / 64;
-    float wk[HPL][4];
+    const int task = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (tid >> 6));
+    if (task >= f.task0[L]) return;
+    int l = 0;
+    while (l + 1 < L && task >= f.task0[l + 1]) l++;
+    const int fi = l == 0 ? f.W.in_dim : HID, tiles = (fi / 64) * (HID / 64);
+    const int t = task - f.task0[l], split = t / tiles, tile = t % tiles;
+    const int m0 = tile / (HID / 64) * 64, n0 = tile % (HID / 64) * 64;
+    const int k_beg = split * f.kchunk, k_end = min(k_beg + f.kchunk, (f.rows + 31) / 32 * 32);
+    // 32 units x 16 rows are 512 values; the 32 units after them start ld / 16 such pieces later
+    const int64_t next = f.ld * 32;
+    const uint16_t *ap = f.in[l] + (m0 >> 5) * next + lane * 8, *bp = f.dAt[l] + (n0 >> 5) * next + lane * 8;
+    f32x16 acc[2][2];
 #pragma unroll
-    for (int j = 0; j < HPL; j++)
+    for (int i = 0; i < 16; i++) acc[0][0][i] = acc[0][1][i] = acc[1][0][i] = acc[1][1][i] = 0.f;
+    constexpr int S = 4;
+    for (int k = k_beg; k < k_end; k += 16 * S) {
+        bf16x8 a[S][2], b[S][2];
 #pragma unroll
-        for (int c = 0; c < 4; c++) wk[j][c] = from_bf16(f.w_out[(lane * HPL + j) * 4 + c]);
-    const float bo0 = f.b_out[0], bo1 = f.b_out[1], bo2 = f.b_out[2], bo3 = f.b_out[3];
-    for (int rr = wave; rr < FB_ROWS && r0 + rr < f.rows; rr += 4) {
-        float h[HPL];
+        for (int s = 0; s < S; s++)
 #pragma unroll
-        for (int j = 0; j < HPL; j++) h[j] = from_bf16(act[rr * LDA + lane * HPL + j]);
-        float z[4];
+            for (int i = 0; i < 2; i++) {
+                const int64_t at = (int64_t)min(k + s * 16, k_end - 16) * 32 + i * next;
+                a[s][i] = *(const bf16x8 *)(ap + at);
+                b[s][i] = *(const bf16x8 *)(bp + at);
+            }
 #pragma unroll
-        for (int c = 0; c < 4; c++) {
-            float sum = 0.f;
+        for (int s = 0; s < S; s++)
+            if (k + s * 16 < k_end) {
 #pragma unroll
-            for (int j = 0; j < HPL; j++) sum = fmaf(h[j], wk[j][c], sum);
-            z[c] = sum;
+                for (int i = 0; i < 2; i++)
+#pragma unroll
+                    for (int j = 0; j < 2; j++)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][i], b[s][j], acc[i][j], 0, 0, 0);
+            }
+    }
+    // accumulator q of lane l holds row 8 (q / 4) + 4 (l / 32) + q % 4, column l % 32
+    float *out = f.w_part[l] + (int64_t)split * fi * HID;
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int q = 0; q < 16; q++) {
+                const int row = m0 + i * 32 + (q >> 2) * 8 + (lane >> 5) * 4 + (q & 3), col = n0 + j * 32 + (lane & 31);
+                out[(int64_t)row * HID + col] = acc[i][j][q];
+            }
+}
+
+// sum over b < nb of part[b * stride], in order of b, U loads in flight
+template <int U>
+__device__ __forceinline__ float ordered_sum(const float *part, int nb, int64_t stride) {
+    float s = 0.f;
+    int b = 0;
+    for (; b + U <= nb; b += U) {
+        float x[U];
+#pragma unroll
+        for (int i = 0; i < U; i++) x[i] = part[(int64_t)(b + i) * stride];
+#pragma unroll
+        for (int i = 0; i < U; i++) s += x[i];
+    }
+    for (; b < nb; b++) s += part[(int64_t)b * stride];
+    return s;
+}
+
+// the bf16 copies of parameter i
+__device__ __forceinline__ void put_bf16(const Weights &W, int64_t i, float x) {
+    const uint16_t h = to_bf16(x);
+    const int64_t o = i - W.woff[W.n_hidden];
+    if (o >= 0 && o < W.hidden * 4) W.out[o] = from_bf16(h);
+    for (int l = 0; l < W.n_hidden; l++) {
+        const int64_t e = i - W.woff[l];
+        const int fin = l == 0 ? W.in_dim : W.hidden;
+        if (e >= 0 && e < (int64_t)fin * W.hidden) {
+            const int k = (int)(e / W.hidden), n = (int)(e % W.hidden);
+            W.fwd[W.wt_off[l] + operand_at(n, k, fin)] = h;
+            W.bwd[W.wt_off[l] + operand_at(k, n, W.hidden)] = h;
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-            for (int c = 0; c < 4; c++) z[c] += __shfl_xor(z[c], off, 64);
-        z[0] += bo0; z[1] += bo1; z[2] += bo2; z[3] += bo3;
-        if (lane < 4) f.z[(int64_t)(r0 + rr) * 4 + lane] = lane == 0 ? z[0] : lane == 1 ? z[1] : lane == 2 ? z[2] : z[3];
     }
 }
 
-// wt[n * fin + k] = W[k * HID + n] for one hidden layer (bf16 copies, so the fused kernel's weight
-// chunks are contiguous per output unit)
-__global__ void k_transpose_bf16(const uint16_t *W, int fin, int hid, uint16_t *wt) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)fin * hid) return;
-    const int n = (int)(i / fin), k = (int)(i % fin);
-    wt[i] = W[(int64_t)k * hid + n];
+// Adam (Kingma and Ba 2015, Algorithm 1) on the FP32 master copy of one parameter; refreshes the bf16
+// copies.  c1 = 1 / (1 - beta1^t), c2 = 1 / (1 - beta2^t) for step t.
+__device__ __forceinline__ void adam_one(const GradArgs &f, int64_t i, float gi) {
+    const float mi = fmaf(1.f - f.b1, gi, f.b1 * f.m[i]);
+    const float vi = fmaf(gi, (1.f - f.b2) * gi, f.b2 * f.v[i]);
+    f.m[i] = mi;
+    f.v[i] = vi;
+    const float th = f.W.theta[i] - f.lr * (mi * f.c1) / (sqrtf(vi * f.c2) + f.eps);
+    f.W.theta[i] = th;
+    put_bf16(f.W, i, th);
 }
 
-// minibatch rows idx[r] (clamped into [0, n_data)) of the training arrays into staging
-__global__ void k_gather_rows(const uint16_t *X, const float *T, const float *w, const uint8_t *nact,
-                              const int32_t *idx, int rows, int64_t n_data, int feat, uint16_t *Xs, float *Ts,
-                              float *ws, uint8_t *ns) {
-    const int r = blockIdx.x;
-    if (r >= rows) return;
-    const int64_t s = min(max((int64_t)idx[r], (int64_t)0), n_data - 1);
-    for (int c = threadIdx.x; c < feat; c += blockDim.x) Xs[(int64_t)r * feat + c] = X[s * feat + c];
-    if (threadIdx.x < 4) Ts[(int64_t)r * 4 + threadIdx.x] = T[s * 4 + threadIdx.x];
-    if (threadIdx.x == 0) {
-        ws[r] = w ? w[s] : 1.f;
-        ns[r] = nact[s];
+__global__ __launch_bounds__(256) void k_adam(GradArgs f, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) adam_one(f, i, f.grad[i]);
+}
+
+// Every parameter's gradient from its partials (and the loss, as element P), then, with ADAM, its update.
+template <bool ADAM>
+__global__ __launch_bounds__(256) void k_finish(GradArgs f, int64_t P) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i > P) return;
+    const int L = f.W.n_hidden, HID = f.W.hidden;
+    float g;
+    if (i >= f.W.woff[L]) {
+        // output weights and biases are contiguous in the partial rows as in the parameters, then the loss
+        g = ordered_sum<64>(f.head_part + (i - f.W.woff[L]), f.head_blocks, HID * 4 + 5);
+        if (i == P) {
+            f.loss[0] = g;
+            return;
+        }
+    } else {
+        int l = 0;
+        while (l + 1 < L && i >= f.W.woff[l + 1]) l++;
+        const int fin = l == 0 ? f.W.in_dim : HID;
+        if (i < f.W.boff[l]) g = ordered_sum<16>(f.w_part[l] + (i - f.W.woff[l]), f.splits, (int64_t)fin * HID);
+        else g = ordered_sum<64>(f.bias_part[l] + (i - f.W.boff[l]), (f.rows + BIAS_ROWS - 1) / BIAS_ROWS, HID);
     }
+    f.grad[i] = g;
+    if constexpr (ADAM) adam_one(f, i, g);
+}
+
+__global__ __launch_bounds__(256) void k_refresh(Weights W, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) put_bf16(W, i, W.theta[i]);
 }
 
 // ---- compiled game <-> network rows --------------------------------------------------------
@@ -599,17 +795,13 @@ struct cfr_mlp {
     std::vector<int64_t> woff, boff;     // offsets into the flat parameter vector
     int64_t P = 0;
     int64_t step = 0;
-    int splits_max = 32;
-    float *theta = nullptr, *grad = nullptr, *m = nullptr, *v = nullptr, *part = nullptr, *inv_w = nullptr,
-          *lossd = nullptr;
-    uint16_t *theta16 = nullptr;
-    uint16_t *wt = nullptr;              // hidden layers' bf16 weights transposed (fused inference)
+    float *theta = nullptr, *grad = nullptr, *m = nullptr, *v = nullptr, *inv_w = nullptr, *lossd = nullptr;
+    uint16_t *w_fwd = nullptr, *w_bwd = nullptr;   // bf16 weights (see Weights)
+    float *w_out = nullptr;
     int64_t wt_off[4] = {0, 0, 0, 0};
-    std::vector<uint16_t *> H;           // [n_hidden] activations, [max_rows][hidden]
-    uint16_t *dA[2] = {nullptr, nullptr};
-    uint16_t *xs = nullptr;              // gathered minibatch
-    float *ts = nullptr, *ws = nullptr;
-    uint8_t *ns = nullptr;
+    // training, rows padded to a multiple of 32 (zeros): see RowsArgs and GradArgs
+    uint16_t *H[4] = {}, *Ht[4] = {}, *dAt[4] = {}, *Xt = nullptr;
+    float *dz = nullptr, *ce = nullptr, *wr = nullptr, *bias_part[4] = {}, *w_part[4] = {}, *head_part = nullptr;
     std::vector<void *> allocs;
 };
 
@@ -641,85 +833,59 @@ void free_mlp(cfr_mlp *n) {
     delete n;
 }
 
-int gemm_splits(int rows, int cap) {
-    int s = (rows + 255) / 256;
-    return s < 1 ? 1 : (s > cap ? cap : s);
+// rows per partial sum of the weight gradients: at most 32 splits of at least 256 rows
+int gemm_splits(int rows) { return std::min(std::max((rows + 255) / 256, 1), 32); }
+
+constexpr int SMALL_ROWS = 8192;   // up to here a 32-row tile per block
+constexpr int ROW_PAD = 128;       // training rows are padded to the largest training tile
+
+Weights weights_of(const cfr_mlp *n) {
+    Weights W{};
+    W.theta = n->theta; W.fwd = n->w_fwd; W.bwd = n->w_bwd; W.out = n->w_out;
+    for (int l = 0; l <= n->d.n_hidden; l++) { W.woff[l] = n->woff[(size_t)l]; W.boff[l] = n->boff[(size_t)l]; }
+    for (int l = 0; l < n->d.n_hidden; l++) W.wt_off[l] = n->wt_off[l];
+    W.n_hidden = n->d.n_hidden; W.in_dim = n->d.in_dim; W.hidden = n->d.hidden;
+    return W;
 }
 
-template <bool A_T, bool B_T, int EPI>
-hipError_t gemm(const GemmArgs &g, int splits, hipStream_t s) {
-    dim3 grid((unsigned)((g.M + BM - 1) / BM), (unsigned)((g.N + BN - 1) / BN), (unsigned)splits);
-    k_gemm<A_T, B_T, EPI><<<grid, 256, 0, s>>>(g);
-    return hipGetLastError();
+template <int HID, int K0, bool TRAIN>
+hipError_t rows_tile(const RowsArgs &f, hipStream_t s) {
+    auto go = [&](auto rt, auto ct, auto wr) {
+        constexpr int RT = decltype(rt)::value, CT = decltype(ct)::value, WR = decltype(wr)::value;
+        constexpr int ROWS = 32 * RT * WR;
+        const unsigned blocks = (unsigned)(((int64_t)f.rows + ROWS - 1) / ROWS);
+        k_rows<HID, K0, RT, CT, WR, TRAIN><<<blocks, 64 * WR * (HID / 32 / CT), 0, s>>>(f);
+        return hipGetLastError();
+    };
+    using std::integral_constant;
+    using One = integral_constant<int, 1>;
+    using Two = integral_constant<int, 2>;
+    using Four_ = integral_constant<int, 4>;
+    if (f.rows <= SMALL_ROWS) return go(One{}, One{}, One{});
+    if constexpr (TRAIN) return go(Four_{}, One{}, One{});
+    else if constexpr (HID == 256) return go(Four_{}, Two{}, One{});
+    else if constexpr (HID == 128) return go(Two{}, Two{}, Two{});
+    else return go(One{}, Two{}, Four_{});
 }
 
-hipError_t head(const cfr_mlp *n, const HeadArgs &a, bool train, int blocks, hipStream_t s) {
-    const int hpl = n->d.hidden / 64;
-#define HEAD(H_)                                                                                   \
-    if (hpl == H_) {                                                                               \
-        if (train) k_head<H_, true><<<blocks, 256, 0, s>>>(a);                                     \
-        else k_head<H_, false><<<blocks, 256, 0, s>>>(a);                                          \
-        return hipGetLastError();                                                                  \
-    }
-    HEAD(1) HEAD(2) HEAD(4)
-#undef HEAD
+template <bool TRAIN>
+hipError_t launch_rows(const RowsArgs &f, hipStream_t s) {
+#define SHAPE(H_, K_) if (f.W.hidden == H_ && f.W.in_dim == K_) return rows_tile<H_, K_, TRAIN>(f, s);
+    SHAPE(64, 64) SHAPE(64, 128) SHAPE(64, 256) SHAPE(128, 64) SHAPE(128, 128) SHAPE(128, 256)
+    SHAPE(256, 64) SHAPE(256, 128) SHAPE(256, 256)
+#undef SHAPE
     return hipErrorInvalidValue;
 }
 
-constexpr int HEAD_BLOCKS = 256;
-
-// forward pass of `rows` (<= the buffers' rows) rows; hidden layer l writes its activations to act(l)
-template <typename Act>
-cfr_status forward_rows_into(cfr_mlp *n, const uint16_t *x, int rows, float *z, bool train, Act act, hipStream_t s) {
-    const int L = n->d.n_hidden;
-    const uint16_t *in = x;
-    for (int l = 0; l < L; l++) {
-        GemmArgs g{};
-        g.A = in; g.B = n->theta16 + n->woff[l];
-        g.M = rows; g.N = n->fout[l]; g.K = n->fin[l]; g.lda = n->fin[l]; g.ldb = n->fout[l]; g.kchunk = g.K;
-        g.bias = n->theta + n->boff[l]; g.C16 = act(l);
-        MHIP((gemm<false, false, EPI_BIAS_RELU>(g, 1, s)));
-        in = act(l);
-    }
-    if (!train) {
-        HeadArgs a{};
-        a.H = act(L - 1); a.W = n->theta16 + n->woff[L]; a.b = n->theta + n->boff[L]; a.rows = rows; a.z = z;
-        const int blocks = std::min(HEAD_BLOCKS, (rows + 3) / 4);
-        MHIP(head(n, a, false, blocks, s));
-    }
-    return CFR_OK;
-}
-
-// forward pass of `rows` (<= max_rows) rows; leaves the hidden activations in n->H (training reads them)
-cfr_status forward_rows(cfr_mlp *n, const uint16_t *x, int rows, float *z, bool train, hipStream_t s) {
-    return forward_rows_into(n, x, rows, z, train, [n](int l) { return n->H[(size_t)l]; }, s);
-}
-
-// ---- the allocation-free inference entry point: its activations live in a file-scope device array ----
-// Two ping-pong buffers of NOALLOC_ROWS rows x 256 hidden units (bf16): 8 MiB that every GPU the
-// library runs on holds for the life of the process.  In host code `noalloc_scratch` is the symbol's
-// host-side stand-in, never a device address: its device address is looked up once per device.
 constexpr int NOALLOC_ROWS = 8192;
-constexpr int NOALLOC_HIDDEN = 256;
-static __device__ __align__(256) uint16_t noalloc_scratch[2 * NOALLOC_ROWS * NOALLOC_HIDDEN];
 
-constexpr int MAX_DEVICES = 64;
-std::mutex g_noalloc_mu;
-uint16_t *g_noalloc_ptr[MAX_DEVICES] = {};
-
-// Device address of this device's scratch (the device must be current); looked up on first use.
-cfr_status noalloc_scratch_ptr(int device, uint16_t **out) {
-    if (device < 0 || device >= MAX_DEVICES) return mfail(CFR_EINVAL, "device ordinal out of range");
-    std::lock_guard<std::mutex> lock(g_noalloc_mu);
-    if (!g_noalloc_ptr[device]) {
-        void *p = nullptr;
-        hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(noalloc_scratch));
-        if (e != hipSuccess || !p)
-            return mfail(CFR_EDEVICE, std::string("hipGetSymbolAddress of the inference scratch: ") + hipGetErrorString(e));
-        g_noalloc_ptr[device] = (uint16_t *)p;
-    }
-    *out = g_noalloc_ptr[device];
-    return CFR_OK;
+// the constants of the next Adam step
+void set_adam(cfr_mlp *n, float lr, GradArgs &g) {
+    n->step++;
+    const double t = (double)n->step;
+    g.lr = lr; g.b1 = n->d.beta1; g.b2 = n->d.beta2; g.eps = n->d.eps;
+    g.c1 = (float)(1.0 / (1.0 - std::pow((double)n->d.beta1, t)));
+    g.c2 = (float)(1.0 / (1.0 - std::pow((double)n->d.beta2, t)));
 }
 
 bool valid_desc(const cfr_mlp_desc *d, std::string &why) {
@@ -776,29 +942,33 @@ cfr_status cfr_mlp_create(const cfr_mlp_desc *desc, cfr_mlp **out) {
         n->P += fo;
         prev = fo;
     }
-    const int64_t R = d.max_rows;
+    // rows of the training buffers, a multiple of the largest row tile
+    const int64_t R = (d.max_rows + ROW_PAD - 1) / ROW_PAD * ROW_PAD;
     const int64_t hid = d.hidden;
-    const int64_t maxw = std::max<int64_t>((int64_t)d.in_dim * hid, hid * hid);
     cfr_status st = CFR_OK;
 #define MA(p, c) do { st = malloc_dev(n, &(p), (c)); if (st != CFR_OK) { free_mlp(n); return st; } } while (0)
-    MA(n->theta, n->P); MA(n->grad, n->P); MA(n->m, n->P); MA(n->v, n->P); MA(n->theta16, n->P);
-    MA(n->part, std::max<int64_t>(std::max<int64_t>((int64_t)n->splits_max * maxw, (int64_t)HEAD_BLOCKS * (hid * 4 + 5)),
-                                  (R + 15) / 16 * hid));
+    MA(n->theta, n->P); MA(n->grad, n->P); MA(n->m, n->P); MA(n->v, n->P);
     {
         int64_t off = 0;
         for (int l = 0; l < d.n_hidden; l++) { n->wt_off[l] = off; off += (int64_t)n->fin[(size_t)l] * hid; }
-        MA(n->wt, off);
+        MA(n->w_fwd, off); MA(n->w_bwd, off); MA(n->w_out, hid * 4);
     }
     MA(n->inv_w, 1);
     MA(n->lossd, 1);
-    n->H.resize((size_t)d.n_hidden);
-    for (int l = 0; l < d.n_hidden; l++) MA(n->H[(size_t)l], R * hid);
-    MA(n->dA[0], R * hid); MA(n->dA[1], R * hid);
-    MA(n->xs, R * d.in_dim); MA(n->ts, R * 4); MA(n->ws, R); MA(n->ns, R);
+    for (int l = 0; l < d.n_hidden; l++) {
+        MA(n->H[l], R * hid); MA(n->Ht[l], R * hid); MA(n->dAt[l], R * hid);
+        MA(n->bias_part[l], (R + BIAS_ROWS - 1) / BIAS_ROWS * hid);
+        MA(n->w_part[l], (int64_t)gemm_splits((int)d.max_rows) * n->fin[(size_t)l] * hid);
+    }
+    MA(n->Xt, R * d.in_dim); MA(n->dz, R * 4); MA(n->ce, R); MA(n->wr, R);
+    MA(n->head_part, (int64_t)HEAD_BLOCKS * (hid * 4 + 5));
 #undef MA
     // zero parameters until the caller sets them
     hipError_t e = hipMemset(n->theta, 0, (size_t)n->P * 4);
-    if (e == hipSuccess) e = hipMemset(n->theta16, 0, (size_t)n->P * 2);
+    if (e == hipSuccess) {   // and the bf16 copies with them
+        k_refresh<<<(unsigned)((n->P + 255) / 256), 256>>>(weights_of(n), n->P);
+        e = hipGetLastError();
+    }
     if (e == hipSuccess) e = hipMemset(n->m, 0, (size_t)n->P * 4);
     if (e == hipSuccess) e = hipMemset(n->v, 0, (size_t)n->P * 4);
     if (e == hipSuccess) e = hipMemset(n->grad, 0, (size_t)n->P * 4);
@@ -821,7 +991,7 @@ cfr_status cfr_mlp_set_params(cfr_mlp *n, const float *params, int64_t len) {
     MHIP(hipMemcpy(n->theta, params, (size_t)len * 4, hipMemcpyHostToDevice));
     MHIP(hipMemset(n->m, 0, (size_t)len * 4));
     MHIP(hipMemset(n->v, 0, (size_t)len * 4));
-    k_to_bf16<<<(unsigned)((len + 255) / 256), 256>>>(n->theta, n->theta16, len);
+    k_refresh<<<(unsigned)((len + 255) / 256), 256>>>(weights_of(n), len);
     MHIP(hipGetLastError());
     MHIP(hipDeviceSynchronize());
     n->step = 0;
@@ -843,35 +1013,15 @@ cfr_status cfr_mlp_get(cfr_mlp *n, int which, float *dst, int64_t len) {
 cfr_status cfr_mlp_forward(cfr_mlp *n, const void *x, int64_t rows, float *z, void *stream) {
     if (!n || ((!x || !z) && rows > 0) || rows < 0) return mfail(CFR_EINVAL, "bad argument");
     MHIP(hipSetDevice(n->d.device));
-    hipStream_t s = (hipStream_t)stream;
-    if (rows == 0) return CFR_OK;
-    // the weights as they are now (set_params and every Adam step change them), transposed
-    for (int l = 0; l < n->d.n_hidden; l++) {
-        const int64_t cnt = (int64_t)n->fin[(size_t)l] * n->d.hidden;
-        k_transpose_bf16<<<(unsigned)((cnt + 255) / 256), 256, 0, s>>>(n->theta16 + n->woff[(size_t)l], n->fin[(size_t)l],
-                                                                      n->d.hidden, n->wt + n->wt_off[l]);
-        MHIP(hipGetLastError());
-    }
-    FusedArgs f{};
-    f.wt = n->wt; f.theta = n->theta;
-    f.w_out = n->theta16 + n->woff[(size_t)n->d.n_hidden];
-    f.b_out = n->theta + n->boff[(size_t)n->d.n_hidden];
-    for (int l = 0; l < n->d.n_hidden; l++) { f.wt_off[l] = n->wt_off[l]; f.boff[l] = n->boff[(size_t)l]; }
-    f.n_hidden = n->d.n_hidden;
-    // launches of at most 2^20 blocks (2^27 rows) each keep every row index in int
-    const int64_t step = (int64_t)FB_ROWS << 20;
+    RowsArgs f{};
+    f.W = weights_of(n);
+    // launches of at most 2^27 rows keep every row index in int
+    const int64_t step = (int64_t)1 << 27;
     for (int64_t r0 = 0; r0 < rows; r0 += step) {
         f.rows = (int)std::min(step, rows - r0);
         f.x = (const uint16_t *)x + r0 * n->d.in_dim;
         f.z = z + r0 * 4;
-        const unsigned blocks = (unsigned)((f.rows + FB_ROWS - 1) / FB_ROWS);
-#define FUSED(H_, K_)                                                                              \
-        if (n->d.hidden == H_ && n->d.in_dim == K_) k_mlp_fused<H_, K_><<<blocks, 256, 0, s>>>(f); else
-        FUSED(64, 64) FUSED(64, 128) FUSED(64, 256) FUSED(128, 64) FUSED(128, 128) FUSED(128, 256)
-        FUSED(256, 64) FUSED(256, 128) FUSED(256, 256)
-        return mfail(CFR_EINVAL, "unsupported network shape");
-#undef FUSED
-        MHIP(hipGetLastError());
+        MHIP(launch_rows<false>(f, (hipStream_t)stream));
     }
     return CFR_OK;
 }
@@ -881,105 +1031,84 @@ cfr_status cfr_mlp_forward_noalloc(cfr_mlp *n, const void *x, int64_t rows, floa
     if (rows > NOALLOC_ROWS)
         return mfail(CFR_EINVAL, "cfr_mlp_forward_noalloc takes at most " + std::to_string(NOALLOC_ROWS) +
                                  " rows per call (" + std::to_string(rows) + " given)");
-    if (n->d.hidden > NOALLOC_HIDDEN) return mfail(CFR_EINVAL, "hidden width above the scratch's 256 units");
+    return cfr_mlp_forward(n, x, rows, z, stream);
+}
+
+// gradients of one minibatch into n->grad and the loss into n->lossd, then, with adam, the update of step
+// n->step with learning rate lr
+static cfr_status gradients(cfr_mlp *n, const void *x, const float *target, const float *weight, const uint8_t *nact,
+                            const int32_t *idx, int64_t n_data, int64_t rows, bool adam, float lr, hipStream_t s) {
+    if (!n || !x || !target || !nact || rows <= 0) return mfail(CFR_EINVAL, "bad argument");
+    if (rows > n->d.max_rows) return mfail(CFR_EINVAL, "rows exceeds max_rows " + std::to_string(n->d.max_rows));
+    if (idx && n_data <= 0) return mfail(CFR_EINVAL, "n_data must be positive with an index list");
     MHIP(hipSetDevice(n->d.device));
-    uint16_t *buf = nullptr;
-    cfr_status st = noalloc_scratch_ptr(n->d.device, &buf);
-    if (st != CFR_OK || rows == 0) return st;
-    // hidden layer l writes buffer l % 2 and reads the other one (the rows come in x for layer 0)
-    const size_t half = (size_t)NOALLOC_ROWS * NOALLOC_HIDDEN;
-    return forward_rows_into(n, (const uint16_t *)x, (int)rows, z, false,
-                             [buf, half](int l) { return buf + (size_t)(l & 1) * half; }, (hipStream_t)stream);
+    const int R = (int)rows, L = n->d.n_hidden, HID = n->d.hidden;
+    RowsArgs f{};
+    f.W = weights_of(n);
+    f.x = (const uint16_t *)x; f.rows = R; f.idx = idx; f.n_data = n_data;
+    f.T = target; f.w = weight; f.nact = nact;
+    f.ld = (R + ROW_PAD - 1) / ROW_PAD * ROW_PAD;
+    f.Xt = n->Xt; f.dz = n->dz; f.ce = n->ce; f.wr = n->wr;
+    for (int l = 0; l < L; l++) { f.H[l] = n->H[l]; f.Ht[l] = n->Ht[l]; f.dAt[l] = n->dAt[l]; f.bias_part[l] = n->bias_part[l]; }
+    if (R > WSUM_ROWS) {
+        k_inv_wsum<<<1, 256, 0, s>>>(weight, idx, n_data, R, n->inv_w);
+        MHIP(hipGetLastError());
+        f.inv_wsum = n->inv_w;
+    }
+    MHIP(launch_rows<true>(f, s));
+    GradArgs g{};
+    g.W = f.W; g.rows = R; g.ld = f.ld;
+    const int want = gemm_splits(R);
+    g.kchunk = ((R + want - 1) / want + 31) / 32 * 32;
+    g.splits = (R + g.kchunk - 1) / g.kchunk;
+    g.head_blocks = std::min(HEAD_BLOCKS, (R + 3) / 4);
+    g.H = n->H[L - 1]; g.dz = n->dz; g.ce = n->ce; g.wr = n->wr; g.head_part = n->head_part;
+    for (int l = 0; l < L; l++) {
+        g.in[l] = l == 0 ? n->Xt : n->Ht[l - 1];
+        g.dAt[l] = n->dAt[l]; g.w_part[l] = n->w_part[l]; g.bias_part[l] = n->bias_part[l];
+        g.task0[l + 1] = g.task0[l] + (n->fin[(size_t)l] / 64) * (HID / 64) * g.splits;
+    }
+    g.grad = n->grad; g.loss = n->lossd; g.m = n->m; g.v = n->v;
+    const unsigned blocks = (unsigned)((g.task0[L] + 3) / 4 + g.head_blocks);
+    if (HID == 256) k_wgrad<256><<<blocks, 256, 0, s>>>(g);
+    else if (HID == 128) k_wgrad<128><<<blocks, 256, 0, s>>>(g);
+    else k_wgrad<64><<<blocks, 256, 0, s>>>(g);
+    MHIP(hipGetLastError());
+    const unsigned fb = (unsigned)((n->P + 1 + 255) / 256);
+    if (adam) {
+        set_adam(n, lr, g);
+        k_finish<true><<<fb, 256, 0, s>>>(g, n->P);
+    } else {
+        k_finish<false><<<fb, 256, 0, s>>>(g, n->P);
+    }
+    MHIP(hipGetLastError());
+    return CFR_OK;
+}
+
+static cfr_status read_loss(cfr_mlp *n, double *loss, hipStream_t s) {
+    if (!loss) return CFR_OK;
+    float lh = 0.f;
+    MHIP(hipMemcpyAsync(&lh, n->lossd, 4, hipMemcpyDeviceToHost, s));
+    MHIP(hipStreamSynchronize(s));
+    *loss = lh;
+    return CFR_OK;
 }
 
 cfr_status cfr_mlp_backward(cfr_mlp *n, const void *x, const float *target, const float *weight,
                             const uint8_t *nact, const int32_t *idx, int64_t n_data, int64_t rows, double *loss,
                             void *stream) {
-    if (!n || !x || !target || !nact || rows <= 0) return mfail(CFR_EINVAL, "bad argument");
-    if (rows > n->d.max_rows) return mfail(CFR_EINVAL, "rows exceeds max_rows " + std::to_string(n->d.max_rows));
-    if (idx && n_data <= 0) return mfail(CFR_EINVAL, "n_data must be positive with an index list");
-    MHIP(hipSetDevice(n->d.device));
-    hipStream_t s = (hipStream_t)stream;
-    const int R = (int)rows, L = n->d.n_hidden, F = n->d.in_dim, HID = n->d.hidden;
-    const uint16_t *X = (const uint16_t *)x;
-    const float *T = target, *W = weight;
-    const uint8_t *NA = nact;
-    if (idx) {
-        k_gather_rows<<<R, 128, 0, s>>>(X, T, W, NA, idx, R, n_data, F, n->xs, n->ts, n->ws, n->ns);
-        MHIP(hipGetLastError());
-        X = n->xs; T = n->ts; W = n->ws; NA = n->ns;
-    }
-    k_inv_wsum<<<1, 256, 0, s>>>(W, R, n->inv_w);
-    MHIP(hipGetLastError());
-    cfr_status st = forward_rows(n, X, R, nullptr, true, s);
-    if (st != CFR_OK) return st;
-    // output layer: loss, gradient of the last hidden pre-activation, block partials
-    HeadArgs a{};
-    a.H = n->H[L - 1]; a.W = n->theta16 + n->woff[L]; a.b = n->theta + n->boff[L];
-    a.T = T; a.w = W; a.nact = NA; a.inv_wsum = n->inv_w; a.rows = R;
-    a.dA = n->dA[0]; a.part = n->part;
-    const int hb = std::min(HEAD_BLOCKS, (R + 3) / 4);
-    MHIP(head(n, a, true, hb, s));
-    const int NP = HID * 4 + 5;
-    // grad of W_out (HID*4), b_out (4) and the loss (1) are contiguous in the partial rows; the
-    // flat layout puts b_out right after W_out, so one reduction writes both, the loss goes to inv_w[0]
-    k_reduce<<<(unsigned)((HID * 4 + 4 + 255) / 256), 256, 0, s>>>(n->part, hb, NP, HID * 4 + 4, n->grad + n->woff[L]);
-    MHIP(hipGetLastError());
-    k_reduce<<<1, 64, 0, s>>>(n->part + HID * 4 + 4, hb, NP, 1, n->lossd);
-    MHIP(hipGetLastError());
-    // hidden layers, last to first
-    int cur = 0;
-    for (int l = L - 1; l >= 0; l--) {
-        const uint16_t *hin = l > 0 ? n->H[(size_t)l - 1] : X;
-        const int fi = n->fin[(size_t)l], fo = n->fout[(size_t)l];
-        // weight gradient: sum over rows of hin[r][m] dA[r][n] (split over rows)
-        const int splits = gemm_splits(R, n->splits_max);
-        int kchunk = (R + splits - 1) / splits;
-        kchunk = (kchunk + BK - 1) / BK * BK;
-        const int used = (R + kchunk - 1) / kchunk;
-        GemmArgs g{};
-        g.A = hin; g.B = n->dA[cur]; g.M = fi; g.N = fo; g.K = R; g.lda = fi; g.ldb = fo; g.kchunk = kchunk;
-        g.C32 = n->part;
-        MHIP((gemm<true, false, EPI_PARTIAL>(g, used, s)));
-        k_reduce<<<(unsigned)(((int64_t)fi * fo + 255) / 256), 256, 0, s>>>(n->part, used, (int64_t)fi * fo, fi * fo,
-                                                                        n->grad + n->woff[(size_t)l]);
-        MHIP(hipGetLastError());
-        // bias gradient
-        const int cchunk = 16;   // R / 16 blocks: enough to fill the device
-        const int cb = (R + cchunk - 1) / cchunk;
-        k_colsum<<<cb, 256, 0, s>>>(n->dA[cur], R, fo, cchunk, n->part);
-        MHIP(hipGetLastError());
-        k_reduce<<<(unsigned)((fo + 255) / 256), 256, 0, s>>>(n->part, cb, fo, fo, n->grad + n->boff[(size_t)l]);
-        MHIP(hipGetLastError());
-        if (l > 0) {
-            // gradient of the previous pre-activation: (dA W_l^T) masked by hin > 0
-            GemmArgs q{};
-            q.A = n->dA[cur]; q.B = n->theta16 + n->woff[(size_t)l];
-            q.M = R; q.N = fi; q.K = fo; q.lda = fo; q.ldb = fo; q.kchunk = fo;
-            q.mask = hin; q.C16 = n->dA[cur ^ 1];
-            MHIP((gemm<false, true, EPI_GRAD_MASK>(q, 1, s)));
-            cur ^= 1;
-        }
-    }
-    if (loss) {
-        float lh = 0.f;
-        MHIP(hipMemcpyAsync(&lh, n->lossd, 4, hipMemcpyDeviceToHost, s));
-        MHIP(hipStreamSynchronize(s));
-        *loss = lh;
-    }
-    return CFR_OK;
+    cfr_status st = gradients(n, x, target, weight, nact, idx, n_data, rows, false, 0.f, (hipStream_t)stream);
+    return st == CFR_OK ? read_loss(n, loss, (hipStream_t)stream) : st;
 }
 
 cfr_status cfr_mlp_adam(cfr_mlp *n, float lr, void *stream) {
     if (!n) return mfail(CFR_EINVAL, "NULL argument");
     if (!(lr >= 0.f)) return mfail(CFR_EINVAL, "lr must be >= 0");
     MHIP(hipSetDevice(n->d.device));
-    n->step++;
-    const double t = (double)n->step;
-    const float c1 = (float)(1.0 / (1.0 - std::pow((double)n->d.beta1, t)));
-    const float c2 = (float)(1.0 / (1.0 - std::pow((double)n->d.beta2, t)));
-    k_adam<<<(unsigned)((n->P + 255) / 256), 256, 0, (hipStream_t)stream>>>(
-        n->theta, n->grad, n->m, n->v, n->theta16, n->P, lr, n->d.beta1, n->d.beta2, n->d.eps, c1, c2);
+    GradArgs g{};
+    g.W = weights_of(n); g.grad = n->grad; g.m = n->m; g.v = n->v;
+    set_adam(n, lr, g);
+    k_adam<<<(unsigned)((n->P + 255) / 256), 256, 0, (hipStream_t)stream>>>(g, n->P);
     MHIP(hipGetLastError());
     return CFR_OK;
 }
@@ -987,9 +1116,11 @@ cfr_status cfr_mlp_adam(cfr_mlp *n, float lr, void *stream) {
 cfr_status cfr_mlp_train_step(cfr_mlp *n, const void *x, const float *target, const float *weight,
                               const uint8_t *nact, const int32_t *idx, int64_t n_data, int64_t rows, float lr,
                               double *loss, void *stream) {
-    cfr_status st = cfr_mlp_backward(n, x, target, weight, nact, idx, n_data, rows, loss, stream);
-    if (st != CFR_OK) return st;
-    return cfr_mlp_adam(n, lr, stream);
+    // a rejected learning rate leaves the gradients and loss of the minibatch behind, as cfr_mlp_backward would
+    const bool ok = lr >= 0.f;
+    cfr_status st = gradients(n, x, target, weight, nact, idx, n_data, rows, ok, lr, (hipStream_t)stream);
+    if (st == CFR_OK) st = read_loss(n, loss, (hipStream_t)stream);
+    return st == CFR_OK && !ok ? mfail(CFR_EINVAL, "lr must be >= 0") : st;
 }
 
 void cfr_mlp_destroy(cfr_mlp *n) {
