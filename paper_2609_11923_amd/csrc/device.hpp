@@ -11,6 +11,13 @@ namespace cfrx {
 // paired with the node's first edge so that no edge-offset lookup sits on the load chain.
 constexpr int32_t MEMBER_NODE_MASK = 0x7fffffff;
 constexpr int32_t MEMBER_P2 = (int32_t)0x80000000u;
+// Group header flags (DevGame::ghdr): members listed in node order, wide member records (also for every set
+// of more members than a staging chunk, the only groups that need several chunks); from GRP_ACTIONS
+// eight bits with the largest action count of the sets, from GRP_PLAYERS two with the players that own some.
+constexpr int GRP_PERM = 1, GRP_WIDE = 2, GRP_ACTIONS = 8, GRP_PLAYERS = 16;
+// Set record word (DevGame::srec): first member and first slot relative to the group's (a group of several
+// sets has at most 1,024 members, and 256 sets of 64 slots), and the player less one.
+constexpr int32_t SREC_MEMBER_MASK = 0x7ff, SREC_SLOT_SHIFT = 11, SREC_SLOT_MASK = 0x3fff, SREC_PLAYER_SHIFT = 25;
 // fields per (game, depth) in game_range: node lo/hi, group lo/hi, chance lo/hi, big chance lo/hi
 constexpr int GR_FIELDS_DEV = 8;
 // slots per workgroup of a launch of the reach pass, by whether it walks
@@ -37,13 +44,16 @@ struct DevGame {
     int affine = 0;
     int32_t group_sets = 256;     // sets per update group (128 or 256): sizes the affine update's LDS rows
     int32_t *koff = nullptr;      // [A]   child offset of each slot (affine only)
-    // member node, per update group in set-major order, or in node order where that
-    // touches far fewer cache lines (grp_perm[g] = 1; mpos then gives each member's set-major position
-    // in its group) (affine only)
-    int32_t *mnode = nullptr;     // [Ndec]
-    int32_t *mseq = nullptr;      // [Ndec] mem_seq in the order of mnode
+    // per update group two int4: first set, first member, first slot and GRP_* flags; node base, sequence
+    // base, first entry in mwide and node bits of a member record; then one more pair whose first three fields end the last group
+    int4 *ghdr = nullptr;         // [2 G + 2]
+    int2 *srec = nullptr;         // [I]   SREC_* word of each set, its own last slot
+    // members, per update group in set-major order, or in node order where that touches far fewer cache
+    // lines (GRP_PERM; mpos then gives each member's set-major position in its group): node and opponent's
+    // last slot relative to the group's bases, node bits low, or in full in mwide (GRP_WIDE)
+    uint32_t *mrec = nullptr;     // [Ndec]
+    int2 *mwide = nullptr;        // [members of wide groups]
     uint16_t *mpos = nullptr;     // [Ndec]
-    int8_t *grp_perm = nullptr;   // [G]
     int32_t *slot_map = nullptr;  // [A]   canonical slot -> device slot (nullptr: identity)
     int32_t *slot_off = nullptr;  // [I+1]
     int32_t *mem_off = nullptr;   // [I+1]
@@ -77,6 +87,7 @@ struct DevGame {
     void *pred = nullptr;         // [A]   PCFR+ prediction (the latest instantaneous regret), else nullptr
     double *sbar = nullptr;       // [A]   strategy sums (FP64)
     int32_t *t = nullptr;         // [1]   iterations started (device counter)
+    double *weights = nullptr;    // [4]   average weight and discounts of the iteration under way (level launches)
     // evaluation (FP64): node values under the average profile and under each player's best response to
     // it; terminals hold pi_c(z) u(z) in val[0] only
     double *val[3] = {nullptr, nullptr, nullptr};   // [N] each
@@ -94,8 +105,9 @@ struct IterFlags {
 };
 
 // launch k of the reach pass: slots [lo, hi), walk where some parents are among them; tick != nullptr
-// bumps the counter
-hipError_t launch_reach(const DevGame &g, int k, int32_t lo, int32_t hi, bool walk, int32_t *tick, hipStream_t s);
+// bumps the counter and writes the new iteration's weights
+hipError_t launch_reach(const DevGame &g, int k, int32_t lo, int32_t hi, bool walk, int32_t *tick, IterFlags f,
+                        hipStream_t s);
 // one level of the backward value pass fused with the update of the information sets on it
 // (regrets, clamp, average, regret matching of the next strategy)
 hipError_t launch_level(const DevGame &g, int d, IterFlags f, hipStream_t s);

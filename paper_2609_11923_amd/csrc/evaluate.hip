@@ -86,10 +86,12 @@ __global__ void __launch_bounds__(BLOCK) k_gather(int32_t n, const int32_t *__re
 }
 
 struct EvalArgs {
-    const int32_t *grp_iset_off, *slot_off, *mem_off, *mem_seq, *kid_off, *kid, *koff, *mnode, *mseq;
+    const int32_t *grp_iset_off, *slot_off, *mem_off, *mem_seq, *kid_off, *kid, *koff;
+    const int4 *ghdr;
+    const int2 *mwide;
+    const uint32_t *mrec;
     const int2 *mem;
     const uint16_t *mpos;
-    const int8_t *grp_perm;
     const int8_t *iset_player;
     const uint8_t *slot_kids;            // KIDS_* bits of the children below each slot
     const int32_t *chance_node, *bigc_node;
@@ -238,18 +240,33 @@ __global__ void __launch_bounds__(BLOCK) k_eval_level(int32_t gbeg, int32_t ngro
 #pragma unroll
     for (int w = 0; w < BLOCK / 64; w++) wide = max(wide, L.wide[w]);
     const bool mixed = L.mixed != 0;
-    const bool perm = ADDR == ADDR_OFFSET && a.grp_perm[g] != 0;
-    // the member listed at m: its node (and first edge) and its set-major position in the group
-    auto member = [&](int32_t m) -> int2 {
-        if constexpr (ADDR == ADDR_OFFSET) return make_int2(a.mnode[m], 0);
-        else return make_int2(a.mem[m].x & MEMBER_NODE_MASK, a.mem[m].y);
+    int4 hf = make_int4(0, 0, 0, 0), hb = hf;
+    if constexpr (ADDR == ADDR_OFFSET) {
+        hf = a.ghdr[2 * g];
+        hb = a.ghdr[2 * g + 1];
+    }
+    const bool perm = (hf.w & GRP_PERM) != 0, wide_rec = (hf.w & GRP_WIDE) != 0;
+    // the member listed at m: its node, the opponent's last sequence and its first edge; its set-major
+    // position in the group
+    auto member = [&](int32_t m) -> int3 {
+        if constexpr (ADDR == ADDR_OFFSET) {
+            if (wide_rec) {
+                const int2 x = a.mwide[hb.z + (m - mbeg)];
+                return make_int3(x.x, x.y, 0);
+            }
+            const uint32_t x = a.mrec[m];
+            return make_int3(hb.x + (int32_t)(x & ((1u << hb.w) - 1)), hb.y + (int32_t)(x >> hb.w), 0);
+        } else {
+            const int2 x = a.mem[m];
+            return make_int3(x.x & MEMBER_NODE_MASK, a.mem_seq[m], x.y);
+        }
     };
     auto place = [&](int32_t m) { return perm ? (int32_t)a.mpos[m] : m - mbeg; };
     auto set_at = [&](int32_t pos) { return pos < GROUP_MEMBERS_MAX ? (int32_t)L.mset[pos] : 0; };
-    auto child = [&](const int2 &x, int32_t q, int32_t k) -> int32_t {
+    auto child = [&](const int3 &x, int32_t q, int32_t k) -> int32_t {
         if constexpr (ADDR == ADDR_OFFSET) return x.x + a.koff[q];
-        else if constexpr (ADDR == ADDR_LIST) return a.kid[x.y + k];
-        else return x.y + k;
+        else if constexpr (ADDR == ADDR_LIST) return a.kid[x.z + k];
+        else return x.z + k;
     };
     double Q[MAXA];
 #pragma unroll
@@ -269,8 +286,8 @@ __global__ void __launch_bounds__(BLOCK) k_eval_level(int32_t gbeg, int32_t ngro
 #pragma unroll
             for (int u0 = 0; u0 < MPT; u0 += P) {
                 bool in[P], one[P];
-                int32_t pos[P], s0[P], nA[P], sq[P];
-                int2 x[P];
+                int32_t pos[P], s0[P], nA[P];
+                int3 x[P];
 #pragma unroll
                 for (int u = 0; u < P; u++) {
                     const int32_t j = (u0 + u) * BLOCK + tid;
@@ -278,7 +295,6 @@ __global__ void __launch_bounds__(BLOCK) k_eval_level(int32_t gbeg, int32_t ngro
                     const int32_t m = in[u] ? cb + j : cb;
                     pos[u] = place(m);
                     x[u] = member(m);
-                    sq[u] = ADDR == ADDR_OFFSET ? a.mseq[m] : a.mem_seq[m];
                 }
                 double q[P], sg[P][NA];
                 int32_t c[P][NA];
@@ -289,7 +305,7 @@ __global__ void __launch_bounds__(BLOCK) k_eval_level(int32_t gbeg, int32_t ngro
                     s0[u] = L.slot[st];
                     nA[u] = L.slot[st + 1] - s0[u];
                     one[u] = L.pl[st] == 1;
-                    q[u] = a.seqbar[sq[u]];
+                    q[u] = a.seqbar[x[u].y];
 #pragma unroll
                     for (int k = 0; k < NA; k++) {
                         const int32_t kk = min(k, nA[u] - 1);
@@ -324,8 +340,8 @@ __global__ void __launch_bounds__(BLOCK) k_eval_level(int32_t gbeg, int32_t ngro
             for (int32_t m = cb + tid; m < ce; m += BLOCK) {
                 const int32_t pos = place(m), st = set_at(pos), s0 = L.slot[st], nA = L.slot[st + 1] - s0;
                 const bool one = L.pl[st] == 1;
-                const int2 x = member(m);
-                const double q = a.seqbar[ADDR == ADDR_OFFSET ? a.mseq[m] : a.mem_seq[m]], w = one ? q : -q;
+                const int3 x = member(m);
+                const double q = a.seqbar[x.y], w = one ? q : -q;
                 double va = 0.0, vo = 0.0;
 #pragma unroll 4
                 for (int k = 0; k < nA; k++) {
@@ -384,7 +400,7 @@ __global__ void __launch_bounds__(BLOCK) k_eval_level(int32_t gbeg, int32_t ngro
     __syncthreads();
     for (int32_t m = mbeg + tid; m < mend; m += BLOCK) {
         const int32_t st = set_at(place(m)), k = L.best[st], s = L.slot[st] + k;
-        const int2 x = member(m);
+        const int3 x = member(m);
         const int32_t c = child(x, s, k);
         const bool one = L.pl[st] == 1;
         double *own = one ? a.v1 : a.v2;
@@ -404,8 +420,8 @@ __global__ void __launch_bounds__(BLOCK) k_eval_roots(int32_t n, const int32_t *
 EvalArgs eval_args(const DevGame &g) {
     EvalArgs a;
     a.grp_iset_off = g.grp_iset_off; a.slot_off = g.slot_off; a.mem_off = g.mem_off; a.mem_seq = g.mem_seq;
-    a.kid_off = g.kid_off; a.kid = g.kid; a.koff = g.koff; a.mnode = g.mnode; a.mseq = g.mseq; a.mpos = g.mpos;
-    a.grp_perm = g.grp_perm; a.mem = g.mem; a.iset_player = g.iset_player;
+    a.kid_off = g.kid_off; a.kid = g.kid; a.koff = g.koff; a.ghdr = g.ghdr; a.mwide = g.mwide; a.mrec = g.mrec;
+    a.mpos = g.mpos; a.mem = g.mem; a.iset_player = g.iset_player;
     a.slot_kids = g.slot_kids; a.chance_node = g.chance_node; a.bigc_node = g.bigc_node;
     a.chance_kids = g.chance_kids; a.bigc_kids = g.bigc_kids; a.sigbar = g.sigbar; a.seqbar = g.seqbar;
     a.v0 = g.val[0]; a.v1 = g.val[1]; a.v2 = g.val[2];

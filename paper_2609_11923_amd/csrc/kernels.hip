@@ -93,6 +93,31 @@ __device__ __forceinline__ T seq_reach(int32_t p, int32_t S0, const int32_t *slo
     return acc;
 }
 
+// What the update of iteration t does (paper Sec. 6, update rules; see cfr.h).
+struct RuleArgs {
+    int rule;          // CFR_RULE_*
+    int upd;           // players whose sets are updated: bit 0 player 1, bit 1 player 2
+    double w;          // average weight (t or 1 for CFR and CFR+, t^2 for PCFR+, 1 for DCFR)
+    double pos, neg;   // DCFR: discounts of positive and of other regrets
+    double sdisc;      // DCFR: strategy-sum discount
+};
+
+__device__ __forceinline__ RuleArgs rule_args(int rule, int linear, int upd, int32_t t) {
+    RuleArgs r;
+    r.rule = rule;
+    r.upd = upd;
+    const double td = (double)t;
+    r.w = rule == CFR_RULE_DCFR ? 1.0 : rule == CFR_RULE_PCFR_PLUS ? td * td : linear ? td : 1.0;
+    r.pos = r.neg = r.sdisc = 1.0;
+    if (rule == CFR_RULE_DCFR) {
+        const double ta = pow(td, DCFR_ALPHA), tb = pow(td, DCFR_BETA);
+        r.pos = ta / (ta + 1.0);
+        r.neg = tb / (tb + 1.0);
+        r.sdisc = pow(td / (td + 1.0), DCFR_GAMMA);
+    }
+    return r;
+}
+
 // The reach of slots [lo, hi), SPT per thread (strided by the block size, so each wave's accesses stay
 // contiguous).  Bound by memory: 12 bytes per slot in FP32, and the parents' reaches, which siblings and
 // neighbouring sets share.  WALK launches hold depths that depend on one another (plan_reach) and are
@@ -103,9 +128,17 @@ __device__ __forceinline__ T seq_reach(int32_t p, int32_t S0, const int32_t *slo
 template <typename T, bool WALK>
 __global__ void __launch_bounds__(BLOCK) k_reach(int32_t lo, int32_t hi, int32_t S0,
                                                  const int32_t *__restrict__ slot_par, const T *__restrict__ sigma,
-                                                 T *seq, int32_t *tick, const int32_t *__restrict__ tiles) {
+                                                 T *seq, int32_t *tick, double *weights, int rule, int linear,
+                                                 const int32_t *__restrict__ tiles) {
     constexpr int SPT = reach_tile(WALK) / BLOCK;
-    if (tick && blockIdx.x == 0 && threadIdx.x == 0) tick[0] += 1;
+    if (tick && blockIdx.x == 0 && threadIdx.x == 0) {
+        // the iteration's weight and discounts, for its levels (DCFR's powers cost a level's blocks more than
+        // the loads they wait for)
+        const int32_t t = tick[0] + 1;
+        tick[0] = t;
+        const RuleArgs r = rule_args(rule, linear, 3, t);
+        weights[0] = r.w; weights[1] = r.pos; weights[2] = r.neg; weights[3] = r.sdisc;
+    }
     if (hi <= lo) return;
     // with retired games only the listed tiles run (a tile shared with a retired game rewrites that
     // game's reach with the same values: its strategy no longer changes)
@@ -139,10 +172,11 @@ struct LevelArgs {
     const int32_t *grp_list, *chance_list, *bigc_list;   // batches with retired games (nullptr: all)
     const int32_t *iset_seq, *slot_par;  // last own slot before a set, and before the set of a slot
     const int32_t *mem_seq;        // the other player's last slot before each member (order of mem)
-    const int32_t *koff, *mnode;   // affine layouts: per-slot child offset, compact member list
-    const int32_t *mseq;           // affine layouts: mem_seq in the order of mnode
-    const uint16_t *mpos;          // affine layouts: set-major position of each member of a node-order group
-    const int8_t *grp_perm;        // affine layouts: 1 where a group's member list is in node order
+    const int32_t *koff;           // affine layouts: per-slot child offset, and DevGame's group headers,
+    const int4 *ghdr;              // set records and member records
+    const int2 *srec, *mwide;
+    const uint32_t *mrec;
+    const uint16_t *mpos;
     T *v;
     T *seq;       // reach of every slot's sequence; seq[-1] = 1
     T *R;
@@ -150,31 +184,6 @@ struct LevelArgs {
     T *sigma;
     T *pred;      // PCFR+ prediction buffer, nullptr for the other rules
 };
-
-// What the update of iteration t does (paper Sec. 6, update rules; see cfr.h).
-struct RuleArgs {
-    int rule;          // CFR_RULE_*
-    int upd;           // players whose sets are updated: bit 0 player 1, bit 1 player 2
-    double w;          // average weight (t or 1 for CFR and CFR+, t^2 for PCFR+, 1 for DCFR)
-    double pos, neg;   // DCFR: discounts of positive and of other regrets
-    double sdisc;      // DCFR: strategy-sum discount
-};
-
-__device__ __forceinline__ RuleArgs rule_args(int rule, int linear, int upd, int32_t t) {
-    RuleArgs r;
-    r.rule = rule;
-    r.upd = upd;
-    const double td = (double)t;
-    r.w = rule == CFR_RULE_DCFR ? 1.0 : rule == CFR_RULE_PCFR_PLUS ? td * td : linear ? td : 1.0;
-    r.pos = r.neg = r.sdisc = 1.0;
-    if (rule == CFR_RULE_DCFR) {
-        const double ta = pow(td, DCFR_ALPHA), tb = pow(td, DCFR_BETA);
-        r.pos = ta / (ta + 1.0);
-        r.neg = tb / (tb + 1.0);
-        r.sdisc = pow(td / (td + 1.0), DCFR_GAMMA);
-    }
-    return r;
-}
 
 // Value of an internal chance node: the sum of its children (chance folded into the template).
 template <typename T, bool EXPLICIT>
@@ -468,219 +477,295 @@ __device__ void group_update(int32_t g, const RuleArgs &ru, const LevelArgs<T> &
     set_update<T, MAXA, EXT>(ru, a, s0, nA, pl, (double)a.seq[a.iset_seq[i0 + tid]], r);
 }
 
-// LDS staging of one update group in an affine layout: the slot offsets of its sets, the set of each
-// member of the chunk and (FP32 state, up to 16 actions) each set's child offsets and strategy row,
-// besides the member values of group_update.  The rows hold GS sets, the game's group bound (128 or
-// 256): with 128 an FP32 block's LDS fits six per compute unit instead of five.  For FP64 the rows
-// would cost a resident block per compute unit (measured slower), so members read them through the
-// cache instead.
+// LDS staging of one update group in an affine layout: the member values of group_update, each set's first
+// slot and each member's set, and (FP32 state, up to 16 actions) the child offsets and strategy of the
+// group's slots.  These hold GS sets, the game's group bound (128 or 256): with 128 an FP32 block's LDS fits
+// six per compute unit instead of five.  For FP64 they would cost a resident block per compute unit
+// (measured slower), so members read them through the cache instead.
 template <typename T, int MAXA, int MPT, int GS>
 struct GroupLdsA {
     static constexpr bool ROWS = MAXA <= 16 && sizeof(T) == 4;
-    static constexpr int RA = ROWS ? MAXA : 1;
+    static constexpr int SLOTS = ROWS ? GS * MAXA : 1;
     T po[MPT * BLOCK];
     alignas(16) T diff[MPT * BLOCK * MAXA];
-    alignas(16) int32_t ko[GS * RA];
-    alignas(16) T sg[GS * RA];
-    int32_t slot[GS + 1];
-    int32_t wmax[BLOCK / 64];
-    uint8_t mset[MPT * BLOCK];
+    alignas(16) int32_t ko[SLOTS];
+    T sg[SLOTS];
+    uint16_t slot[GS + 1];
+    alignas(4) uint8_t mset[MPT * BLOCK];
 };
 
+// set tid's first slot and members [m0, m1) (relative to the group's) into LDS: the member -> set map covers
+// one chunk (a group of several sets fits it, and a larger one is a single set)
+template <typename T, int MAXA, int MPT, int GS>
+__device__ __forceinline__ void map_set(GroupLdsA<T, MAXA, MPT, GS> &L, int tid, int32_t nsets, int32_t slot,
+                                        int32_t nslots, int32_t m0, int32_t m1) {
+    L.slot[tid] = (uint16_t)slot;
+    if (tid == nsets - 1) L.slot[nsets] = (uint16_t)nslots;
+    int32_t m = m0;
+    const int32_t e = min(m1, MPT * BLOCK);
+    for (; m < e && (m & 3); m++) L.mset[m] = (uint8_t)tid;
+    for (; m + 4 <= e; m += 4) *(uint32_t *)&L.mset[m] = (uint32_t)tid * 0x01010101u;
+    for (; m < e; m++) L.mset[m] = (uint8_t)tid;
+}
+
 // group_update for affine layouts (child a of member h is h + koff[slot a]): the same arithmetic
-// in the same order, so the results are bitwise those of group_update.  What changes is how the
-// loads are issued.  The vector-memory pipeline (address and data units at ~90 % busy) bounds
-// this pass, so the per-slot child offsets and strategy, the same for every member of a set, are
-// loaded once per set (by its thread, into an LDS row) instead of once per member; a member then
-// loads only its record, its opponent reach and its child values.  The opponent's reach is that of his
-// last sequence, which the members of his sets there share: a gather from a compact per-slot array
-// through a 4-byte index per member.  Loads are unconditional: past
-// a set's last action they repeat its last child (an address already read), lanes past the
-// chunk's end repeat its first member, so a chunk's loads are in flight together; only stores
-// and arithmetic are masked.  (A guard that skips a load no lane needs compiles to a branch with
+// in the same order, so the results are bitwise those of group_update.  What changes is what is loaded
+// and when.  Large levels are bound by memory traffic, small ones by the chain of dependent loads (a
+// launch holds a few groups per compute unit at most), so both are kept short:
+//  * the group's header gives its sets, members and slots, so every further load but two depends on the
+//    header alone: set records, member records, and the child offsets and strategy of its slots (into LDS,
+//    coalesced) are requested together; the opponent's reach follows the member record (requested before the
+//    first barrier as well) and the child values follow the offsets;
+//  * a member record is four bytes: its node and the opponent's last sequence relative to the group's
+//    bases, split where the group's nodes need it (GRP_WIDE groups, whose spans need more than 32 bits
+//    together or whose single set has more members than a chunk, keep them in eight);
+//  * a set record is eight bytes: its first member, first slot and player in one word, its own sequence;
+//  * the slots' regrets and strategy sums are requested before the members are reduced, when the registers
+//    of the member pass are free, and used after it.
+// Loads are unconditional: past a set's last action they repeat its last child (an address already read),
+// lanes past the chunk's end repeat its first member, so a chunk's loads are in flight together; only
+// stores and arithmetic are masked.  (A guard that skips a load no lane needs compiles to a branch with
 // a full wait at its join, which costs more than the load.)  The number of child loads per member
 // is the group's widest set, bucketed (with_action_bound; the public-state layout orders states by
-// action count, so most groups are uniform): a block-uniform choice made once per group, outside
-// the loops.  Where a group's sets interleave -- a player-2 set's members are strided by the
-// opponent's hand count -- the host lists the group's members in node order instead (grp_perm) with
-// each one's set-major position: consecutive lanes then touch consecutive nodes, children and values
-// instead of one cache line each, and the staging stays set-major, so the reduction, and every
-// result, is unchanged.  The two orders are separate instantiations of the member pass, chosen per
-// group.
-template <typename T, int MAXA, int MPT, bool EXT, int GS>
-__device__ void group_update_affine(int32_t g, const RuleArgs &ru, const LevelArgs<T> &a,
-                                    GroupLdsA<T, MAXA, MPT, GS> &L) {
-    constexpr int CHUNK = MPT * BLOCK;
+// action count, so most groups are uniform), and where a group's sets interleave -- a player-2 set's
+// members are strided by the opponent's hand count -- the host lists the group's members in node order
+// (GRP_PERM) with each one's set-major position: consecutive lanes then touch consecutive nodes, children
+// and values instead of one cache line each, and the staging stays set-major, so the reduction, and every
+// result, is unchanged.  Both are choices of the header, made once per group.  In alternating order a group
+// without sets of the updated player only needs its values.
+// Measured, FP32 state, all levels of an iteration, against set and member arrays read one after another (8-byte
+// members, 13-byte sets, slots loaded after the reduction): 220M-node card game 0.74 -> 0.63 ms (2.75 GB of
+// design bytes, 4.4 TB/s), 256 subgames 103 -> 97 us, 26-card Leduc 61 -> 56 us in 11 launches; DCFR in FP64
+// on the 10.0M-node card game, with the discounts' powers out of the blocks, 12.7 -> 11.2 us per launch.
+template <typename T, int MAXA, int MPT, bool EXT, int GS, int NA, bool PERM>
+__device__ __forceinline__ void group_body(const int4 &h0, const int4 &hb, const int4 &h1, const RuleArgs &ru,
+                                           const LevelArgs<T> &a, GroupLdsA<T, MAXA, MPT, GS> &L) {
     constexpr bool ROWS = GroupLdsA<T, MAXA, MPT, GS>::ROWS;
+    constexpr bool SLOT_PASS = ROWS && MAXA <= 4;
+    constexpr int SPT = (GS * MAXA + BLOCK - 1) / BLOCK;   // slots per thread
     const int tid = threadIdx.x;
-    const int32_t i0 = a.grp_iset_off[g], i1 = a.grp_iset_off[g + 1];
-    const int32_t nsets = i1 - i0;
-    const int32_t mbeg = a.mem_off[i0], mend = a.mem_off[i1];
+    const int32_t i0 = h0.x, nsets = h1.x - i0, mbeg = h0.y, mend = h1.y, S0 = h0.z, nslots = h1.z - S0;
+    const bool update = (h0.w >> GRP_PLAYERS) & ru.upd;
     const bool has_set = tid < nsets;
+    int32_t h[MPT], ms[MPT], pj[MPT];
+#pragma unroll
+    for (int u = 0; u < MPT; u++) {
+        const int32_t j = u * BLOCK + tid, jj = mbeg + j < mend ? j : 0;
+        const uint32_t x = a.mrec[mbeg + jj];
+        h[u] = hb.x + (int32_t)(x & ((1u << hb.w) - 1));
+        ms[u] = hb.y + (int32_t)(x >> hb.w);
+        if constexpr (PERM) pj[u] = a.mpos[mbeg + jj];
+        else pj[u] = jj;
+    }
     const int32_t ti = i0 + (has_set ? tid : nsets - 1);
-    const int32_t m0 = a.mem_off[ti], m1 = a.mem_off[ti + 1];
-    const int32_t s0 = a.slot_off[ti], nA = a.slot_off[ti + 1] - s0;
-    const int pl = a.iset_player[ti];
-    const bool perm = a.grp_perm[g] != 0;
-    const T *__restrict__ seq = a.seq;
-    const int32_t sq = a.iset_seq[ti];
-    const T *__restrict__ sig = a.sigma;
-    const int32_t *__restrict__ koff = a.koff;
-    // the widest set of this wave, then (after the barrier) of the group
-    int32_t wa = has_set ? nA : 0;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) wa = max(wa, __shfl_xor(wa, off));
-    wa = __builtin_amdgcn_readfirstlane(wa);
+    const int2 sr = a.srec[ti];
+    const int32_t next = a.srec[min(ti + 1, h1.x - 1)].x;
     if constexpr (ROWS) {
-        // row k of a set holds slot min(k, nA - 1): every column a member may read is filled
-        with_action_bound<MAXA>(wa, [&](auto nb) {
-            constexpr int NB = decltype(nb)::value;
-            int32_t kr[NB];
-            T sr[NB];
-#pragma unroll
-            for (int k = 0; k < NB; k++) {
-                const int32_t q = s0 + min(k, nA - 1);
-                kr[k] = koff[q];
-                sr[k] = sig[q];
+        constexpr int UNROLL = SLOT_PASS ? SPT : 1;
+#pragma unroll UNROLL
+        for (int u = 0; u < SPT; u++) {
+            const int32_t q = u * BLOCK + tid;
+            const int32_t k = a.koff[S0 + min(q, nslots - 1)];
+            const T s = a.sigma[S0 + min(q, nslots - 1)];
+            if (q < nslots) {
+                L.ko[q] = k;
+                L.sg[q] = s;
             }
-            if (has_set) {
+        }
+    }
+    const bool last = ti + 1 == h1.x;
+    const int32_t m0 = mbeg + (sr.x & SREC_MEMBER_MASK), m1 = last ? mend : mbeg + (next & SREC_MEMBER_MASK);
+    const int32_t sl = (sr.x >> SREC_SLOT_SHIFT) & SREC_SLOT_MASK;
+    const int32_t nA = (last ? nslots : (next >> SREC_SLOT_SHIFT) & SREC_SLOT_MASK) - sl;
+    const int pl = (sr.x >> SREC_PLAYER_SHIFT) + 1;
+    T po[MPT];
+    if (update) {
 #pragma unroll
-                for (int k = 0; k < MAXA; k++) {
-                    L.ko[tid * MAXA + k] = kr[min(k, NB - 1)];
-                    L.sg[tid * MAXA + k] = sr[min(k, NB - 1)];
-                }
-            }
-        });
+        for (int u = 0; u < MPT; u++) po[u] = a.seq[ms[u]];
     }
-    if ((tid & 63) == 0) L.wmax[tid >> 6] = wa;
-    if (has_set) {
-        L.slot[tid] = s0;
-        if (tid == nsets - 1) L.slot[nsets] = s0 + nA;
-        // member -> set map of the first chunk: a group of several sets fits one chunk, and a group
-        // that needs more chunks holds a single set (index 0 throughout)
-        const int32_t e = min(m1, mbeg + CHUNK);
-        for (int32_t m = m0; m < e; m++) L.mset[m - mbeg] = (uint8_t)tid;
-    }
+    const T pown = a.seq[sr.y];
+    if (has_set) map_set<T, MAXA, MPT, GS>(L, tid, nsets, sl, nslots, m0 - mbeg, m1 - mbeg);
     __syncthreads();
-    int32_t ga = 0;
+    {
+        T cv[MPT][NA], sg[MPT][ROWS ? 1 : NA];
+        int32_t sb[MPT], na[MPT];
 #pragma unroll
-    for (int w = 0; w < BLOCK / 64; w++) ga = max(ga, L.wmax[w]);
-    const T pown = seq[sq];
-    T r[MAXA];
+        for (int u = 0; u < MPT; u++) {
+            const int32_t st = L.mset[pj[u]];
+            sb[u] = L.slot[st];
+            na[u] = L.slot[st + 1] - sb[u];
+            int32_t ko[NA];
 #pragma unroll
-    for (int k = 0; k < MAXA; k++) r[k] = T(0);
-    auto member_pass = [&](auto nag, auto permc) {
-        constexpr int NA = decltype(nag)::value;
-        constexpr bool PERM = decltype(permc)::value;
-        for (int32_t cb = mbeg; cb < mend; cb += CHUNK) {
-            const int32_t ce = min(cb + CHUNK, mend);
-            bool in[MPT];
-            int32_t hn[MPT], ms[MPT], pj[MPT], st[MPT], sb[MPT], na[MPT];
-#pragma unroll
-            for (int u = 0; u < MPT; u++) {
-                const int32_t j = u * BLOCK + tid;
-                in[u] = cb + j < ce;
-                const int32_t jj = in[u] ? j : 0;
-                // thread j takes the group's j-th listed member; in a node-order group pj is its
-                // slot in the set-major staging
-                hn[u] = a.mnode[cb + jj];
-                ms[u] = a.mseq[cb + jj];
-                if constexpr (PERM) pj[u] = a.mpos[cb + jj];
-                else pj[u] = jj;
-                st[u] = L.mset[pj[u]];
-                sb[u] = L.slot[st[u]];
-                na[u] = L.slot[st[u] + 1] - sb[u];
-            }
-            T po[MPT], cv[MPT][NA], sg[MPT][ROWS ? 1 : NA];
-#pragma unroll
-            for (int u = 0; u < MPT; u++) {
-                const int32_t h = hn[u];
-                po[u] = seq[ms[u]];
-                int32_t ko[NA];
-#pragma unroll
-                for (int k = 0; k < NA; k++) {
-                    if constexpr (ROWS) {
-                        ko[k] = L.ko[st[u] * MAXA + k];
-                    } else {
-                        const int32_t q = sb[u] + min(k, na[u] - 1);
-                        ko[k] = koff[q];
-                        sg[u][k] = sig[q];
-                    }
+            for (int k = 0; k < NA; k++) {
+                const int32_t q = sb[u] + min(k, na[u] - 1);
+                if constexpr (ROWS) {
+                    ko[k] = L.ko[q];
+                } else {
+                    ko[k] = a.koff[S0 + q];
+                    sg[u][k] = a.sigma[S0 + q];
                 }
-#pragma unroll
-                for (int k = 0; k < NA; k++) cv[u][k] = a.v[h + ko[k]];
             }
 #pragma unroll
-            for (int u = 0; u < MPT; u++) {
-                T vh = T(0);
+            for (int k = 0; k < NA; k++) cv[u][k] = a.v[h[u] + ko[k]];
+        }
 #pragma unroll
-                for (int k = 0; k < NA; k++) {
-                    T sk;
-                    if constexpr (ROWS) sk = L.sg[st[u] * MAXA + k];
-                    else sk = sg[u][k];
-                    vh = k < na[u] ? fma_t(sk, cv[u][k], vh) : vh;
-                }
-                if (!in[u]) continue;
-                const int32_t j = pj[u];
-                a.v[hn[u]] = vh;
+        for (int u = 0; u < MPT; u++) {
+            T vh = T(0);
+#pragma unroll
+            for (int k = 0; k < NA; k++) {
+                T sk;
+                if constexpr (ROWS) sk = L.sg[sb[u] + min(k, na[u] - 1)];
+                else sk = sg[u][k];
+                vh = k < na[u] ? fma_t(sk, cv[u][k], vh) : vh;
+            }
+            if (mbeg + u * BLOCK + tid >= mend) continue;
+            const int32_t j = pj[u];
+            a.v[h[u]] = vh;
+            if (update) {
                 L.po[j] = po[u];
 #pragma unroll
                 for (int k = 0; k < NA; k++) L.diff[j * MAXA + k] = cv[u][k] - vh;
             }
-            __syncthreads();
-            if (has_set) reduce_members<T, MAXA, NA>(L.po, L.diff, max(m0, cb) - cb, min(m1, ce) - cb, r);
-            __syncthreads();
         }
-    };
-    with_action_bound<MAXA>(ga, [&](auto nag) {
-        if (perm) member_pass(nag, std::true_type{});
-        else member_pass(nag, std::false_type{});
-    });
-    if constexpr (ROWS && MAXA <= 4) {
-        // The group's slots [S0, S1) are contiguous: move their regrets, strategy sums and strategy
-        // through LDS (the member staging is free now) with coalesced passes of the whole block,
-        // instead of each set thread loading and storing its few slots.  Slots of sets this half
-        // leaves alone are written back unchanged.
-        const int32_t S0 = L.slot[0], S1 = L.slot[nsets];
-        double *sbs = reinterpret_cast<double *>(L.diff);            // [<= CHUNK]
-        T *Rs = reinterpret_cast<T *>(sbs + CHUNK), *Ss = Rs + CHUNK; // [<= CHUNK] each
-        for (int32_t q = tid; q < S1 - S0; q += BLOCK) {
-            sbs[q] = a.sbar[S0 + q];
-            Rs[q] = a.R[S0 + q];
-            Ss[q] = sig[S0 + q];
+    }
+    if (!update) return;
+    double sbp[SLOT_PASS ? SPT : 1];
+    T Rp[SLOT_PASS ? SPT : 1];
+    if constexpr (SLOT_PASS) {
+#pragma unroll
+        for (int u = 0; u < SPT; u++) {
+            const int32_t q = S0 + min(u * BLOCK + tid, nslots - 1);
+            sbp[u] = a.sbar[q];
+            Rp[u] = a.R[q];
+        }
+    }
+    __syncthreads();
+    T r[MAXA];
+#pragma unroll
+    for (int k = 0; k < MAXA; k++) r[k] = T(0);
+    if (has_set) reduce_members<T, MAXA, NA>(L.po, L.diff, m0 - mbeg, m1 - mbeg, r);
+    if constexpr (SLOT_PASS) {
+        // The group's slots are contiguous: their regrets, strategy sums and strategy move through LDS (the
+        // member staging is free now) with coalesced passes of the whole block, instead of each set thread
+        // loading and storing its few slots.  Slots of sets this half leaves alone are written back
+        // unchanged.
+        constexpr int CHUNK = MPT * BLOCK;
+        double *sbs = reinterpret_cast<double *>(L.diff);   // [<= CHUNK]
+        T *Rs = reinterpret_cast<T *>(sbs + CHUNK);         // [<= CHUNK]
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < SPT; u++) {
+            const int32_t q = u * BLOCK + tid;
+            if (q < nslots) {
+                sbs[q] = sbp[u];
+                Rs[q] = Rp[u];
+            }
         }
         __syncthreads();
         if (has_set && ((ru.upd >> (pl - 1)) & 1)) {
-            const int32_t b = s0 - S0;
             T Rk[MAXA], sk[MAXA], sn[MAXA];
             double sb[MAXA];
 #pragma unroll
             for (int k = 0; k < MAXA; k++) {
-                const int32_t q = b + min(k, nA - 1);
+                const int32_t q = sl + min(k, nA - 1);
                 Rk[k] = Rs[q];
-                sk[k] = Ss[q];
+                sk[k] = L.sg[q];
                 sb[k] = sbs[q];
             }
-            set_update_compute<T, MAXA, EXT>(ru, a, s0, nA, pl, (double)pown, r, Rk, sk, sb, sn);
+            set_update_compute<T, MAXA, EXT>(ru, a, S0 + sl, nA, pl, (double)pown, r, Rk, sk, sb, sn);
 #pragma unroll
             for (int k = 0; k < MAXA; k++)
                 if (k < nA) {
-                    Rs[b + k] = Rk[k];
-                    sbs[b + k] = sb[k];
-                    Ss[b + k] = sn[k];
+                    Rs[sl + k] = Rk[k];
+                    sbs[sl + k] = sb[k];
+                    L.sg[sl + k] = sn[k];
                 }
         }
         __syncthreads();
-        for (int32_t q = tid; q < S1 - S0; q += BLOCK) {
-            a.sbar[S0 + q] = sbs[q];
-            a.R[S0 + q] = Rs[q];
-            a.sigma[S0 + q] = Ss[q];
+#pragma unroll
+        for (int u = 0; u < SPT; u++) {
+            const int32_t q = u * BLOCK + tid;
+            if (q < nslots) {
+                a.sbar[S0 + q] = sbs[q];
+                a.R[S0 + q] = Rs[q];
+                a.sigma[S0 + q] = L.sg[q];
+            }
         }
-    } else {
-        if (!has_set) return;
-        if (!((ru.upd >> (pl - 1)) & 1)) return;
-        set_update<T, MAXA, EXT>(ru, a, s0, nA, pl, (double)pown, r);
+    } else if (has_set && ((ru.upd >> (pl - 1)) & 1)) {
+        set_update<T, MAXA, EXT>(ru, a, S0 + sl, nA, pl, (double)pown, r);
     }
+}
+
+// group_body for GRP_WIDE groups: full member records, a chunk of members at a time (only a group of a
+// single set has several), a member of each thread after another.
+template <typename T, int MAXA, int MPT, bool EXT, int GS>
+__device__ void group_wide(const int4 &h0, const int4 &hb, const int4 &h1, const RuleArgs &ru, const LevelArgs<T> &a,
+                           GroupLdsA<T, MAXA, MPT, GS> &L) {
+    constexpr int CHUNK = MPT * BLOCK;
+    const int tid = threadIdx.x;
+    const int32_t i0 = h0.x, nsets = h1.x - i0, mbeg = h0.y, mend = h1.y, S0 = h0.z, nslots = h1.z - S0;
+    const bool has_set = tid < nsets;
+    const int32_t ti = i0 + (has_set ? tid : nsets - 1);
+    const int2 sr = a.srec[ti];
+    const int32_t next = a.srec[min(ti + 1, h1.x - 1)].x;
+    const bool last = ti + 1 == h1.x;
+    const int32_t m0 = mbeg + (sr.x & SREC_MEMBER_MASK), m1 = last ? mend : mbeg + (next & SREC_MEMBER_MASK);
+    const int32_t sl = (sr.x >> SREC_SLOT_SHIFT) & SREC_SLOT_MASK;
+    const int32_t nA = (last ? nslots : (next >> SREC_SLOT_SHIFT) & SREC_SLOT_MASK) - sl;
+    const int pl = (sr.x >> SREC_PLAYER_SHIFT) + 1;
+    if (has_set) map_set<T, MAXA, MPT, GS>(L, tid, nsets, sl, nslots, m0 - mbeg, m1 - mbeg);
+    __syncthreads();
+    T r[MAXA];
+#pragma unroll
+    for (int k = 0; k < MAXA; k++) r[k] = T(0);
+    for (int32_t cb = mbeg; cb < mend; cb += CHUNK) {
+        const int32_t ce = min(cb + CHUNK, mend);
+#pragma unroll 1
+        for (int32_t m = cb + tid; m < ce; m += BLOCK) {
+            const int2 x = a.mwide[hb.z + (m - mbeg)];
+            const int32_t pos = nsets == 1 ? m - cb : a.mpos[m], st = nsets == 1 ? 0 : L.mset[pos];
+            const int32_t q0 = S0 + L.slot[st], na = S0 + L.slot[st + 1] - q0;
+            T cv[MAXA], sg[MAXA];
+            const T po = a.seq[x.y];
+#pragma unroll
+            for (int k = 0; k < MAXA; k++) {
+                const int32_t q = q0 + min(k, na - 1);
+                cv[k] = a.v[x.x + a.koff[q]];
+                sg[k] = a.sigma[q];
+            }
+            T vh = T(0);
+#pragma unroll
+            for (int k = 0; k < MAXA; k++) vh = k < na ? fma_t(sg[k], cv[k], vh) : vh;
+            a.v[x.x] = vh;
+            L.po[pos] = po;
+#pragma unroll
+            for (int k = 0; k < MAXA; k++) L.diff[pos * MAXA + k] = cv[k] - vh;
+        }
+        __syncthreads();
+        if (has_set) reduce_members<T, MAXA>(L.po, L.diff, max(m0, cb) - cb, min(m1, ce) - cb, r);
+        __syncthreads();
+    }
+    if (has_set && ((ru.upd >> (pl - 1)) & 1))
+        set_update<T, MAXA, EXT>(ru, a, S0 + sl, nA, pl, (double)a.seq[sr.y], r);
+}
+
+// Must be called by every thread of the block; a block that updates several groups synchronises between
+// them.
+template <typename T, int MAXA, int MPT, bool EXT, int GS>
+__device__ void group_update_affine(int32_t g, const RuleArgs &ru, const LevelArgs<T> &a,
+                                    GroupLdsA<T, MAXA, MPT, GS> &L) {
+    const int4 h0 = a.ghdr[2 * g], hb = a.ghdr[2 * g + 1], h1 = a.ghdr[2 * g + 2];
+    if (h0.w & GRP_WIDE) {
+        group_wide<T, MAXA, MPT, EXT, GS>(h0, hb, h1, ru, a, L);
+        return;
+    }
+    // (the positions of a set-major list are the identity, so the node-order form is right for any group:
+    // those of more than four actions, which are rare, have only that)
+    with_action_bound<MAXA>((h0.w >> GRP_ACTIONS) & 0xff, [&](auto na) {
+        constexpr int NA = decltype(na)::value;
+        if (MAXA > 4 || (h0.w & GRP_PERM)) group_body<T, MAXA, MPT, EXT, GS, NA, true>(h0, hb, h1, ru, a, L);
+        else group_body<T, MAXA, MPT, EXT, GS, NA, false>(h0, hb, h1, ru, a, L);
+    });
 }
 
 // AF: 0 the child-list update, 1 the affine update with rows for 256 sets per group, 2 the affine
@@ -701,12 +786,16 @@ __device__ __forceinline__ void update_group(int32_t g, const RuleArgs &ru, cons
 // spills; the LDS of 6 workgroups fits) instead of the 5 that 86 registers allow.  The discounted and
 // predictive tails would spill under that bound.  FP32 needs no bound: its registers allow 6 and its
 // LDS too with 128-set groups (5 with 256).
-template <typename T, int MAXA, bool EXT>
-constexpr int level_min_waves() { return (sizeof(T) == 8 && MAXA <= 4 && !EXT) ? 6 : 1; }
+template <typename T, int MAXA, bool EXT, int AF>
+constexpr int level_min_waves() {
+    if (MAXA > 4) return 1;
+    if (sizeof(T) == 8) return EXT ? 1 : 6;
+    return AF == 2 ? (EXT ? 5 : 6) : AF == 1 ? 5 : 1;
+}
 template <typename T, int MAXA, int MPT, bool EXPLICIT, bool EXT, int AF>
-__global__ void __launch_bounds__(BLOCK, (level_min_waves<T, MAXA, EXT>())) k_level(int32_t gbeg, int32_t ngroups, int32_t bbeg, int32_t nbig,
+__global__ void __launch_bounds__(BLOCK, (level_min_waves<T, MAXA, EXT, AF>())) k_level(int32_t gbeg, int32_t ngroups, int32_t bbeg, int32_t nbig,
                                                  int32_t cbeg, int32_t nchance, LevelArgs<T> a,
-                                                 const int32_t *__restrict__ tcount, int rule, int linear, int upd) {
+                                                 const double *__restrict__ weights, int rule, int upd) {
     __shared__ LevelLds<T, MAXA, MPT, EXPLICIT, AF> L;
     const int32_t blk = (int32_t)blockIdx.x;
     // with retired games in a batch the ranges index lists of the work that still runs (a retired
@@ -723,7 +812,7 @@ __global__ void __launch_bounds__(BLOCK, (level_min_waves<T, MAXA, EXT>())) k_le
     }
     const int32_t x = gbeg + xcd_tile(blk, ngroups);
     const int32_t grp = a.grp_list ? a.grp_list[x] : x;
-    const RuleArgs ru = rule_args(rule, linear, upd, tcount[0]);
+    const RuleArgs ru{rule, upd, weights[0], weights[1], weights[2], weights[3]};
     update_group<T, MAXA, MPT, EXPLICIT, EXT, AF>(grp, ru, a, L);
 }
 
@@ -795,7 +884,10 @@ __device__ bool persistent_game(int32_t gm, int32_t rank, int32_t W, const int32
             if (!game_barrier(barrier + gm, W, epoch, err, timeout_ticks)) return false;
             for (int32_t d = Ds - 1; d >= 0; d--) {
                 const int32_t *r = gr + d * GR_FIELDS_DEV;
-                for (int32_t g = r[2] + rank; g < r[3]; g += W) update_group<T, MAXA, MPT, EXPLICIT, EXT, AF>(g, ru, a, L);
+                for (int32_t g = r[2] + rank; g < r[3]; g += W) {
+                    update_group<T, MAXA, MPT, EXPLICIT, EXT, AF>(g, ru, a, L);
+                    __syncthreads();
+                }
                 for (int32_t b = r[6] + rank; b < r[7]; b += W) big_chance_value<T, EXPLICIT>(a.bigc_node[b], a, L.po);
                 for (int32_t j = r[4] + rank * BLOCK + tid; j < r[5]; j += W * BLOCK) chance_value<T, EXPLICIT>(a.chance_node[j], a);
                 if (!game_barrier(barrier + gm, W, epoch, err, timeout_ticks)) return false;
@@ -1019,27 +1111,28 @@ __global__ void __launch_bounds__(BLOCK) k_template(int64_t lo, int64_t hi, cons
 
 #if CFR_PART == 0
 template <typename T>
-static hipError_t reach_t(const DevGame &g, int32_t lo, int32_t hi, bool walk, int32_t *tick, const int32_t *tiles,
-                          int64_t n_tiles, hipStream_t s) {
+static hipError_t reach_t(const DevGame &g, int32_t lo, int32_t hi, bool walk, int32_t *tick, IterFlags f,
+                          const int32_t *tiles, int64_t n_tiles, hipStream_t s) {
     // one block still runs the counter bump
     if (tiles && n_tiles == 0) hi = lo;
     const int32_t tile = reach_tile(walk);
     const unsigned blocks = hi <= lo ? 1u : tiles ? (unsigned)n_tiles : (unsigned)(((int64_t)hi - lo + tile - 1) / tile);
     if (walk)
         hipLaunchKernelGGL((k_reach<T, true>), dim3(blocks), dim3(BLOCK), 0, s, lo, hi, lo, g.slot_par,
-                           (const T *)g.sigma, (T *)g.seq, tick, tiles);
+                           (const T *)g.sigma, (T *)g.seq, tick, g.weights, f.rule, f.linear, tiles);
     else
         hipLaunchKernelGGL((k_reach<T, false>), dim3(blocks), dim3(BLOCK), 0, s, lo, hi, lo, g.slot_par,
-                           (const T *)g.sigma, (T *)g.seq, tick, tiles);
+                           (const T *)g.sigma, (T *)g.seq, tick, g.weights, f.rule, f.linear, tiles);
     return hipGetLastError();
 }
 
-hipError_t launch_reach(const DevGame &g, int k, int32_t lo, int32_t hi, bool walk, int32_t *tick, hipStream_t s) {
+hipError_t launch_reach(const DevGame &g, int k, int32_t lo, int32_t hi, bool walk, int32_t *tick, IterFlags f,
+                        hipStream_t s) {
     if (hi <= lo && !tick) return hipSuccess;
     const int32_t *tiles = g.use_lists ? g.reach_list + g.reach_off[k] : nullptr;
     const int64_t nt = g.use_lists ? g.reach_off[k + 1] - g.reach_off[k] : 0;
     if (g.use_lists && nt == 0 && !tick) return hipSuccess;
-    return g.fp64 ? reach_t<double>(g, lo, hi, walk, tick, tiles, nt, s) : reach_t<float>(g, lo, hi, walk, tick, tiles, nt, s);
+    return g.fp64 ? reach_t<double>(g, lo, hi, walk, tick, f, tiles, nt, s) : reach_t<float>(g, lo, hi, walk, tick, f, tiles, nt, s);
 }
 #endif
 
@@ -1050,10 +1143,10 @@ hipError_t launch_reach_average(const DevGame &g, int32_t lo, int32_t hi, bool w
     const unsigned blocks = (unsigned)(((int64_t)hi - lo + reach_tile(walk) - 1) / reach_tile(walk));
     if (walk)
         hipLaunchKernelGGL((k_reach<double, true>), dim3(blocks), dim3(BLOCK), 0, s, lo, hi, lo, g.slot_par, g.sigbar,
-                           g.seqbar, nullptr, nullptr);
+                           g.seqbar, nullptr, nullptr, 0, 0, nullptr);
     else
         hipLaunchKernelGGL((k_reach<double, false>), dim3(blocks), dim3(BLOCK), 0, s, lo, hi, lo, g.slot_par, g.sigbar,
-                           g.seqbar, nullptr, nullptr);
+                           g.seqbar, nullptr, nullptr, 0, 0, nullptr);
     return hipGetLastError();
 }
 #endif
@@ -1064,8 +1157,8 @@ static LevelArgs<T> level_args(const DevGame &g) {
     a.grp_iset_off = g.grp_iset_off; a.slot_off = g.slot_off; a.mem_off = g.mem_off; a.mem = g.mem;
     a.iset_player = g.iset_player; a.kid_off = g.kid_off; a.kid = g.kid; a.chance_node = g.chance_node;
     a.bigc_node = g.bigc_node;
-    a.iset_seq = g.iset_seq; a.slot_par = g.slot_par; a.mem_seq = g.mem_seq; a.mseq = g.mseq;
-    a.koff = g.koff; a.mnode = g.mnode; a.mpos = g.mpos; a.grp_perm = g.grp_perm;
+    a.iset_seq = g.iset_seq; a.slot_par = g.slot_par; a.mem_seq = g.mem_seq;
+    a.koff = g.koff; a.ghdr = g.ghdr; a.srec = g.srec; a.mwide = g.mwide; a.mrec = g.mrec; a.mpos = g.mpos;
     a.grp_list = g.use_lists ? g.grp_list : nullptr;
     a.chance_list = g.use_lists ? g.chance_list : nullptr;
     a.bigc_list = g.use_lists ? g.bigc_list : nullptr;
@@ -1088,7 +1181,7 @@ static hipError_t level_t(const DevGame &g, int d, IterFlags f, hipStream_t s) {
     const unsigned blocks = (unsigned)ng + (unsigned)nb + grid_for(nc);
     if (blocks == 0) return hipSuccess;
     hipLaunchKernelGGL((k_level<T, MAXA, MPT, EX, XT, AF>), dim3(blocks), dim3(BLOCK), 0, s,
-                       gbeg, ng, bbeg, nb, cbeg, nc, level_args<T>(g), g.t, f.rule, f.linear, f.upd);
+                       gbeg, ng, bbeg, nb, cbeg, nc, level_args<T>(g), g.weights, f.rule, f.upd);
     return hipGetLastError();
 }
 

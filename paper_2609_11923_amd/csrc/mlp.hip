@@ -64,7 +64,7 @@ constexpr float LOG_CUT = -30.f;  // below: log softplus(z) = z, sigmoid(z) / so
 // weight reads (0.3 MB per tile in inference) are shared by more rows.  In inference four waves of
 // up to 4 x 2 tiles (half an LDS read and a quarter of a KB of weights per MFMA) leave room for two blocks per
 // compute unit, which hide each other's loads, stores and output layers.
-// Measured: 240,930 rows through 128 -> 3 x 256 -> 4, 377 -> 98 us (810 TFLOP/s; its products alone at the rate of
+// Measured: 240,930 rows through 128 -> 3 x 256 -> 4, 377 -> 86 us (920 TFLOP/s; its products alone at the rate of
 // a large library GEMM: 66 us).  A training step on 4,096 rows, 190 -> 60 us (23 launches before): this
 // kernel 39, k_wgrad 12, k_finish 9.
 //

@@ -86,7 +86,7 @@ struct cfr_handle {
     int64_t E = 0, Z = 0;
     double pot = 1.0;
     int64_t device_bytes = 0;
-    std::vector<double> perm_members;  // per depth: members of update groups listed in node order
+    std::vector<double> perm_members, wide_members;   // per depth (GroupRecords)
     // batches: per-game activity (cfr_set_active); the tiles of the reach launches (first tile per launch,
     // each tile's first and last game) and the lists of the work that still runs
     std::vector<int8_t> active;
@@ -157,22 +157,32 @@ static void parallel_games(int n, F &&fn) {
     for (auto &t : pool) t.join();
 }
 
-// The affine update's member list (mnode).  A group keeps its members in set-major order, unless
-// listing them in node order makes a wave's 64 consecutive members touch at most half as many
-// 32-node spans (cache lines of FP32 values) -- the case where the group's sets interleave, as a
-// player-2 set's members, strided by the opponent's hand count, do.  Such a group is flagged in
-// perm[g] and mpos gives each listed member's set-major position in its group (groups of several
-// sets hold at most one staging chunk, so it fits 16 bits).  perm_members[d] counts the members of
-// flagged groups of depth d (their extra position reads are design bytes).
-static void member_lists(const DeviceLayout &D, std::vector<int32_t> &mnode, std::vector<int32_t> &mseq,
-                         std::vector<uint16_t> &mpos, std::vector<int8_t> &perm, std::vector<double> &perm_members) {
+// The affine update's group headers, set records and member records (DevGame).  A group keeps its members
+// in set-major order, unless listing them in node order makes a wave's 64 consecutive members touch at
+// most half as many 32-node spans (cache lines of FP32 values) -- the case where the group's sets
+// interleave, as a player-2 set's members, strided by the opponent's hand count, do.  Such a group is
+// flagged and mpos gives each listed member's set-major position in its group (groups of several sets hold
+// at most one staging chunk, so it fits 16 bits).
+struct GroupRecords {
+    std::vector<int4> hdr;
+    std::vector<int2> srec, wide;
+    std::vector<uint32_t> mrec;
+    std::vector<uint16_t> mpos;
+    std::vector<double> perm_members;   // per depth: members of node-order groups (their positions are design bytes)
+    std::vector<double> wide_members;   // per depth: members of wide groups
+    int32_t perm_groups = 0;
+};
+
+static GroupRecords group_records(const DeviceLayout &D) {
+    GroupRecords R;
     const int64_t Ndec = (int64_t)D.mem_node.size();
-    mnode = D.mem_node;
-    mseq = D.mem_seq;
-    mpos.assign((size_t)Ndec, 0);
     const int32_t G = (int32_t)D.grp_iset_off.size() - 1;
-    perm.assign((size_t)std::max(G, 1), 0);
+    R.mrec.resize((size_t)Ndec);
+    R.mpos.assign((size_t)Ndec, 0);
+    R.hdr.assign((size_t)2 * G + 2, make_int4(0, 0, 0, 0));
+    R.srec.resize(D.iset_player.size());
     constexpr int32_t SPAN = 4096;   // groups per task
+    std::vector<std::vector<int2>> wides((size_t)((G + SPAN - 1) / SPAN));
     parallel_games((G + SPAN - 1) / SPAN, [&](int task) {
         std::vector<int32_t> idx;
         auto spans = [](const int32_t *nodes, int32_t n) {
@@ -194,34 +204,76 @@ static void member_lists(const DeviceLayout &D, std::vector<int32_t> &mnode, std
         for (int32_t g = task * SPAN; g < std::min(G, (task + 1) * SPAN); g++) {
             const int32_t i0 = D.grp_iset_off[(size_t)g], i1 = D.grp_iset_off[(size_t)g + 1];
             const int32_t mb = D.mem_off[(size_t)i0], me = D.mem_off[(size_t)i1], n = me - mb;
-            for (int32_t k = 0; k < n; k++) {
-                mpos[(size_t)(mb + k)] = (uint16_t)(k & 0xffff);
-                mnode[(size_t)(mb + k)] &= MEMBER_NODE_MASK;
+            const int32_t S0 = D.slot_off[(size_t)i0];
+            int flags = 0, widest = 0;
+            for (int32_t i = i0; i < i1; i++) {
+                const int pl = D.iset_player[(size_t)i];
+                widest = std::max(widest, D.slot_off[(size_t)i + 1] - D.slot_off[(size_t)i]);
+                flags |= 1 << (GRP_PLAYERS + pl - 1);
+                R.srec[(size_t)i] = make_int2((D.mem_off[(size_t)i] - mb) | (D.slot_off[(size_t)i] - S0) << SREC_SLOT_SHIFT |
+                                                  (pl - 1) << SREC_PLAYER_SHIFT,
+                                              D.iset_seq[(size_t)i]);
             }
-            if (i1 - i0 == 1) continue;
+            flags |= widest << GRP_ACTIONS;
             const int32_t *list = D.mem_node.data() + mb;
             idx.resize((size_t)n);
             for (int32_t k = 0; k < n; k++) idx[(size_t)k] = k;
-            std::sort(idx.begin(), idx.end(), [&](int32_t x, int32_t y) {
-                return (list[x] & MEMBER_NODE_MASK) < (list[y] & MEMBER_NODE_MASK);
-            });
-            sorted_nodes.resize((size_t)n);
-            for (int32_t k = 0; k < n; k++) sorted_nodes[(size_t)k] = list[idx[(size_t)k]];
-            if (2 * spans(sorted_nodes.data(), n) > spans(list, n)) continue;
-            perm[(size_t)g] = 1;
+            if (i1 - i0 > 1) {
+                std::sort(idx.begin(), idx.end(), [&](int32_t x, int32_t y) {
+                    return (list[x] & MEMBER_NODE_MASK) < (list[y] & MEMBER_NODE_MASK);
+                });
+                sorted_nodes.resize((size_t)n);
+                for (int32_t k = 0; k < n; k++) sorted_nodes[(size_t)k] = list[idx[(size_t)k]];
+                if (2 * spans(sorted_nodes.data(), n) > spans(list, n))
+                    for (int32_t k = 0; k < n; k++) idx[(size_t)k] = k;
+                else flags |= GRP_PERM;
+            }
+            auto node = [&](int32_t k) { return list[idx[(size_t)k]] & MEMBER_NODE_MASK; };
+            auto seq = [&](int32_t k) { return D.mem_seq[(size_t)(mb + idx[(size_t)k])]; };
+            int32_t n0 = INT32_MAX, n1 = 0, q0 = INT32_MAX, q1 = -1;
             for (int32_t k = 0; k < n; k++) {
-                mnode[(size_t)(mb + k)] = sorted_nodes[(size_t)k] & MEMBER_NODE_MASK;
-                mseq[(size_t)(mb + k)] = D.mem_seq[(size_t)(mb + idx[(size_t)k])];
-                mpos[(size_t)(mb + k)] = (uint16_t)idx[(size_t)k];
+                n0 = std::min(n0, node(k)); n1 = std::max(n1, node(k));
+                q0 = std::min(q0, seq(k)); q1 = std::max(q1, seq(k));
+            }
+            auto bits = [](int32_t x) {
+                int b = 0;
+                while (b < 31 && x >> b) b++;
+                return b;
+            };
+            // the word's low bits hold the node, the others the sequence
+            const int node_bits = bits(n1 - n0);
+            const bool wide = node_bits + bits(q1 - q0) > 32 || n > D.group_cap;
+            if (wide) flags |= GRP_WIDE;
+            R.hdr[(size_t)2 * g] = make_int4(i0, mb, S0, flags);
+            R.hdr[(size_t)2 * g + 1] = make_int4(n0, q0, (int32_t)wides[(size_t)task].size(), node_bits);
+            for (int32_t k = 0; k < n; k++) {
+                R.mpos[(size_t)(mb + k)] = (uint16_t)(idx[(size_t)k] & 0xffff);
+                if (wide) wides[(size_t)task].push_back(make_int2(node(k), seq(k)));
+                else R.mrec[(size_t)(mb + k)] = (uint32_t)(node(k) - n0) | (uint32_t)((uint64_t)(uint32_t)(seq(k) - q0) << node_bits);
             }
         }
     });
+    // the tasks' wide records one after another
+    for (int32_t task = 0; task < (int32_t)wides.size(); task++) {
+        const int32_t base = (int32_t)R.wide.size();
+        for (int32_t g = task * SPAN; g < std::min(G, (task + 1) * SPAN); g++) R.hdr[(size_t)2 * g + 1].z += base;
+        R.wide.insert(R.wide.end(), wides[(size_t)task].begin(), wides[(size_t)task].end());
+    }
+    const size_t I = D.iset_player.size();
+    R.hdr[(size_t)2 * G] = make_int4((int32_t)I, D.mem_off[I], D.slot_off[I], 0);
     const int md = (int)D.grp_depth_off.size() - 2;
-    perm_members.assign((size_t)std::max(md + 1, 1), 0.0);
+    R.perm_members.assign((size_t)std::max(md + 1, 1), 0.0);
+    R.wide_members.assign((size_t)std::max(md + 1, 1), 0.0);
     for (int d = 0; d <= md; d++)
-        for (int32_t g = D.grp_depth_off[(size_t)d]; g < D.grp_depth_off[(size_t)d + 1]; g++)
-            if (perm[(size_t)g])
-                perm_members[(size_t)d] += D.mem_off[(size_t)D.grp_iset_off[(size_t)g + 1]] - D.mem_off[(size_t)D.grp_iset_off[(size_t)g]];
+        for (int32_t g = D.grp_depth_off[(size_t)d]; g < D.grp_depth_off[(size_t)d + 1]; g++) {
+            const double m = R.hdr[(size_t)2 * g + 2].y - R.hdr[(size_t)2 * g].y;
+            if (R.hdr[(size_t)2 * g].w & GRP_PERM) {
+                R.perm_members[(size_t)d] += m;
+                R.perm_groups++;
+            }
+            if (R.hdr[(size_t)2 * g].w & GRP_WIDE) R.wide_members[(size_t)d] += m;
+        }
+    return R;
 }
 
 // Per-launch event timing for cfr_profile: class 0 tick, 1 forward, 2 level.
@@ -303,7 +355,7 @@ cfr_status enqueue_iteration(cfr_handle *h, hipStream_t s, int64_t *count, Launc
         else if (kind == 1)
             HIP_TRY(launch_reach(g, d, h->reach_slot[(size_t)d], h->reach_slot[(size_t)d + 1],
                                  h->reach_walk[(size_t)d] != 0,
-                                 d == 0 && half == 0 ? g.t : nullptr, s));
+                                 d == 0 && half == 0 ? g.t : nullptr, f, s));
         else HIP_TRY(launch_level(g, d, f, s));
         if (tm) {
             tm->cls.push_back(-1);
@@ -339,11 +391,11 @@ void model_bytes(cfr_handle *h, const DeviceLayout &D) {
         // the sequences' reach, once per slot;
         // sets: member and slot offsets, player, own reach; slots: sigma read + write, R read + write,
         // sbar read + write
-        // (affine layouts: a 4-byte member record, plus a 2-byte staging position in node-order
-        // groups; no child index per edge, one offset per slot)
+        // (affine layouts: a 4-byte member record, 8 in wide groups, plus a 2-byte staging position in
+        // node-order groups; an 8-byte set record; no child index per edge, one offset per slot)
         if (h->g.affine)
-            lv += (8 + es) * Md[d] + es * Ed[d] + (13 + es) * Id[d] + (5 * es + 20) * Ad[d] +
-                  2.0 * ((size_t)d < h->perm_members.size() ? h->perm_members[(size_t)d] : 0.0);
+            lv += (4 + es) * Md[d] + es * Ed[d] + (8 + es) * Id[d] + (5 * es + 20) * Ad[d] +
+                  2.0 * h->perm_members[(size_t)d] + 4.0 * h->wide_members[(size_t)d];
         else lv += (12 + es) * Md[d] + (kb + es) * Ed[d] + (13 + es) * Id[d] + (5 * es + 16) * Ad[d];
         // chance nodes: list entry, edge offset, value write; edges: child (index), value
         for (int32_t j = D.chance_off[d]; j < D.chance_off[d + 1]; j++) {
@@ -856,6 +908,8 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     std::vector<int32_t> koff;
     g.affine = o.affine && slot_child_offsets(DL, koff) ? 1 : 0;
     g.group_sets = DL.group_sets;
+    GroupRecords rec;
+    if (g.affine) rec = group_records(DL);
 
 #define ALLOC(ptr, cnt) do { st = dev_alloc(h, &(ptr), (cnt)); if (st != CFR_OK) { free_handle(h); return st; } } while (0)
     ALLOC(g.kid_off, N + 1);
@@ -866,10 +920,11 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     ALLOC(g.mem, Ndec);
     if (g.affine) {
         ALLOC(g.koff, A > 0 ? A : 1);
-        ALLOC(g.mnode, Ndec > 0 ? Ndec : 1);
-        ALLOC(g.mseq, Ndec > 0 ? Ndec : 1);
-        ALLOC(g.mpos, Ndec > 0 ? Ndec : 1);
-        ALLOC(g.grp_perm, std::max<int64_t>((int64_t)DL.grp_iset_off.size() - 1, 1));
+        ALLOC(g.ghdr, (int64_t)rec.hdr.size());
+        ALLOC(g.srec, I);
+        ALLOC(g.mrec, Ndec);
+        ALLOC(g.mwide, (int64_t)rec.wide.size());
+        ALLOC(g.mpos, Ndec);
     }
     ALLOC(g.iset_player, I);
     ALLOC(g.iset_seq, I);
@@ -897,6 +952,7 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     }
     ALLOC(g.sbar, A);
     ALLOC(g.t, 1);
+    ALLOC(g.weights, 4);
     for (double *&v : g.val) ALLOC(v, N);
     ALLOC(g.sigbar, A);
     {
@@ -932,16 +988,15 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     }
     if (g.affine) {
         UP(g.koff, koff);
-        std::vector<int32_t> mnode, mseq;
-        std::vector<uint16_t> mpos;
-        std::vector<int8_t> perm;
-        member_lists(DL, mnode, mseq, mpos, perm, h->perm_members);
-        for (int8_t f : perm) h->node_order_groups += f;
-        for (double m : h->perm_members) h->node_order_members += (int64_t)m;
-        UP(g.mnode, mnode);
-        UP(g.mseq, mseq);
-        UP(g.mpos, mpos);
-        UP(g.grp_perm, perm);
+        for (double m : rec.perm_members) h->node_order_members += (int64_t)m;
+        h->node_order_groups = rec.perm_groups;
+        h->perm_members = rec.perm_members;
+        h->wide_members = rec.wide_members;
+        UP(g.ghdr, rec.hdr);
+        UP(g.srec, rec.srec);
+        UP(g.mrec, rec.mrec);
+        UP(g.mwide, rec.wide);
+        UP(g.mpos, rec.mpos);
     }
     UP(g.iset_player, DL.iset_player);
     UP(g.iset_seq, DL.iset_seq);
