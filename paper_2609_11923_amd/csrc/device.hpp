@@ -32,8 +32,9 @@ constexpr double BARRIER_TIMEOUT_S = 2.0;
 constexpr double DCFR_ALPHA = 1.5, DCFR_BETA = 0.0, DCFR_GAMMA = 2.0;
 
 struct DevGame {
-    int32_t N = 0, I = 0, A = 0, Ndec = 0, max_depth = 0, max_actions = 0;
+    int32_t N = 0, I = 0, A = 0, Ndec = 0, E = 0, max_depth = 0, max_actions = 0;
     int fp64 = 0;                 // state type: 0 float (paper's configured dtype), 1 double
+    int32_t lds_limit = 0;        // LDS bytes a workgroup may have
     int rule = 0;                 // CFR_RULE_* (selects the update's instantiation)
     // structure (read-only after compile)
     int explicit_kids = 0;        // 1: child a of n is kid[kid_off[n] + a]; 0: it is kid_off[n] + a

@@ -183,6 +183,7 @@ struct LevelArgs {
     double *sbar;
     T *sigma;
     T *pred;      // PCFR+ prediction buffer, nullptr for the other rules
+    const int32_t *mem_words, *player_words;   // mem and iset_player as words (games staged whole in LDS)
 };
 
 // Value of an internal chance node: the sum of its children (chance folded into the template).
@@ -940,18 +941,19 @@ __global__ void __launch_bounds__(BLOCK) k_persistent(const int4 *__restrict__ t
 // One workgroup runs n_iter whole iterations of a game whose state fits in LDS: the values (with
 // the terminal template), the slots' reach, strategy, regrets, strategy sums and (PCFR+) the
 // prediction are staged in, every level of every iteration runs between block barriers, and the
-// state is written back at the end.  No launch per level and no trip to HBM inside the loop.  The
-// structure arrays stay in global memory (read-only and small, so cache-resident).  One thread
+// state is written back at the end.  No launch per level and no trip to HBM inside the loop.  Where the
+// structure arrays fit as well they are staged too (STAGED), since each level is a chain of dependent
+// lookups in them.  One thread
 // per information set walks its members in ascending order with the level kernels' arithmetic,
 // so the iterates are bitwise those of the level launches.
 
 // The update of one set by one thread: member values v(h) = sum_a sigma v(h.a), the set's
 // instantaneous regrets summed over its members in ascending order, then set_update.
-template <typename T, int MAXA, bool EXPLICIT, bool EXT>
+template <typename T, int MAXA, bool EXPLICIT, bool EXT, bool STAGED>
 __device__ void set_serial(int32_t i, const RuleArgs &ru, const LevelArgs<T> &a) {
     const int32_t s0 = a.slot_off[i], nA = a.slot_off[i + 1] - s0;
     const int32_t m0 = a.mem_off[i], m1 = a.mem_off[i + 1];
-    const int pl = a.iset_player[i];
+    const int pl = STAGED ? a.player_words[i] : (int)a.iset_player[i];
     T sg[MAXA], r[MAXA];
 #pragma unroll
     for (int k = 0; k < MAXA; k++) {
@@ -959,7 +961,7 @@ __device__ void set_serial(int32_t i, const RuleArgs &ru, const LevelArgs<T> &a)
         r[k] = T(0);
     }
     for (int32_t m = m0; m < m1; m++) {
-        const int2 x = a.mem[m];
+        const int2 x = STAGED ? make_int2(a.mem_words[2 * m], a.mem_words[2 * m + 1]) : a.mem[m];
         const int32_t h = x.x & MEMBER_NODE_MASK;
         const T po = a.seq[a.mem_seq[m]];
         T cv[MAXA];
@@ -987,11 +989,18 @@ size_t lds_schedule_bytes(int32_t N, int32_t A, int fp64, int pred) {
 }
 #endif
 
-template <typename T, int MAXA, bool EXPLICIT, bool EXT>
+// Sizes of the structure arrays that a staged game keeps in LDS, in 4-byte words.
+struct LdsSizes {
+    int32_t I, Ndec, E, C, B;   // sets, members, listed children, chance nodes, big chance nodes
+};
+__host__ __device__ inline size_t lds_structure_words(const LdsSizes &z, int32_t N, int32_t A, int32_t D) {
+    return (size_t)A + 2 * ((size_t)z.I + 1) + 2 * (size_t)z.I + 3 * (size_t)z.Ndec + z.E + (N + 1) + z.C + z.B + 6 * (size_t)D;
+}
+
+template <typename T, int MAXA, bool EXPLICIT, bool EXT, bool STAGED>
 __global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, int32_t D, int32_t N, int32_t A,
-                                               int32_t n_iter, LevelArgs<T> g,
-                                               const int32_t *__restrict__ tcount, int rule, int linear,
-                                               int alternating) {
+                                               LdsSizes z, int32_t n_iter, LevelArgs<T> g, int32_t *tcount, int rule,
+                                               int linear, int alternating) {
     extern __shared__ __align__(16) unsigned char smem[];
     double *sb = reinterpret_cast<double *>(smem);
     T *v = reinterpret_cast<T *>(sb + A);
@@ -999,6 +1008,48 @@ __global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, i
     T *pred = g.pred ? R + A : nullptr;
     T *red = R + A + (g.pred ? A : 0);
     const int tid = threadIdx.x;
+    const int32_t t0 = tcount[0];
+    LevelArgs<T> a = g;
+    // per depth: first set and the end, chance and big chance node ranges
+    const int32_t *lv = nullptr;
+    if constexpr (STAGED) {
+        int32_t *w = reinterpret_cast<int32_t *>(red + BLOCK);
+        auto take = [&](const int32_t *src, int32_t n) {
+            int32_t *dst = w;
+            for (int32_t i = tid; i < n; i += BLOCK) dst[i] = src[i];
+            w += n;
+            return dst;
+        };
+        int32_t *ranges = w;
+        for (int32_t d = tid; d < D; d += BLOCK) {
+            const int32_t *r = gr + d * GR_FIELDS_DEV;
+            ranges[6 * d] = g.grp_iset_off[r[2]];
+            ranges[6 * d + 1] = g.grp_iset_off[r[3]];
+            for (int k = 0; k < 4; k++) ranges[6 * d + 2 + k] = r[4 + k];
+        }
+        w += 6 * D;
+        lv = ranges;
+        a.slot_par = take(g.slot_par, A);
+        a.slot_off = take(g.slot_off, z.I + 1);
+        a.mem_off = take(g.mem_off, z.I + 1);
+        a.iset_seq = take(g.iset_seq, z.I);
+        a.mem_seq = take(g.mem_seq, z.Ndec);
+        a.kid_off = take(g.kid_off, N + 1);
+        if (EXPLICIT) a.kid = take(g.kid, z.E);
+        a.chance_node = take(g.chance_node, z.C);
+        a.bigc_node = take(g.bigc_node, z.B);
+        // members as two words each, players as one
+        int32_t *mw = w;
+        for (int32_t m = tid; m < z.Ndec; m += BLOCK) {
+            const int2 x = g.mem[m];
+            mw[2 * m] = x.x;
+            mw[2 * m + 1] = x.y;
+        }
+        w += 2 * z.Ndec;
+        for (int32_t i = tid; i < z.I; i += BLOCK) w[i] = g.iset_player[i];
+        a.mem_words = mw;
+        a.player_words = w;
+    }
     for (int32_t i = tid; i < N; i += BLOCK) v[i] = g.v[i];
     if (tid == 0) seq[-1] = T(1);
     for (int32_t q = tid; q < A; q += BLOCK) {
@@ -1008,9 +1059,7 @@ __global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, i
         if (pred) pred[q] = g.pred[q];
     }
     __syncthreads();
-    LevelArgs<T> a = g;
     a.v = v; a.seq = seq; a.sigma = sig; a.R = R; a.sbar = sb; a.pred = pred;
-    const int32_t t0 = tcount[0];
     const int halves = alternating ? 2 : 1;
     for (int32_t it = 1; it <= n_iter; it++) {
         for (int half = 0; half < halves; half++) {
@@ -1019,15 +1068,23 @@ __global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, i
                 seq[q] = seq_reach<T>(a.slot_par[q], 0, a.slot_par, sig, seq) * sig[q];
             __syncthreads();
             for (int32_t d = D - 1; d >= 0; d--) {
-                const int32_t *r = gr + d * GR_FIELDS_DEV;
-                const int32_t ib = a.grp_iset_off[r[2]], ie = a.grp_iset_off[r[3]];
-                for (int32_t i = ib + tid; i < ie; i += BLOCK) set_serial<T, MAXA, EXPLICIT, EXT>(i, ru, a);
-                for (int32_t j = r[4] + tid; j < r[5]; j += BLOCK) chance_value<T, EXPLICIT>(a.chance_node[j], a);
-                for (int32_t b = r[6]; b < r[7]; b++) big_chance_value<T, EXPLICIT>(a.bigc_node[b], a, red);
+                int32_t ib, ie, cb, ce, bb, be;
+                if constexpr (STAGED) {
+                    const int32_t *r = lv + 6 * d;
+                    ib = r[0]; ie = r[1]; cb = r[2]; ce = r[3]; bb = r[4]; be = r[5];
+                } else {
+                    const int32_t *r = gr + d * GR_FIELDS_DEV;
+                    ib = g.grp_iset_off[r[2]]; ie = g.grp_iset_off[r[3]];
+                    cb = r[4]; ce = r[5]; bb = r[6]; be = r[7];
+                }
+                for (int32_t i = ib + tid; i < ie; i += BLOCK) set_serial<T, MAXA, EXPLICIT, EXT, STAGED>(i, ru, a);
+                for (int32_t j = cb + tid; j < ce; j += BLOCK) chance_value<T, EXPLICIT>(a.chance_node[j], a);
+                for (int32_t b = bb; b < be; b++) big_chance_value<T, EXPLICIT>(a.bigc_node[b], a, red);
                 __syncthreads();
             }
         }
     }
+    if (tid == 0) tcount[0] = t0 + n_iter;
     for (int32_t i = tid; i < N; i += BLOCK) g.v[i] = v[i];
     for (int32_t q = tid; q < A; q += BLOCK) {
         g.sbar[q] = sb[q];
@@ -1254,12 +1311,20 @@ struct LdsLaunch {
     hipError_t operator()() const {
         if constexpr (MAXA > 16) {
             return hipErrorInvalidValue;
+        } else if (MAXA == 4 && g.max_actions <= 2) {
+            // a tiny game is bound by the instructions of its few busy waves: half the columns take Kuhn's 20
+            // iterations from 84 to 73 us
+            return operator()<T, 2, MPT, EX, XT, AF>();
         } else {
-            auto fn = k_lds<T, MAXA, EX, XT>;
+            const LdsSizes z{g.I, g.Ndec, EX ? g.E : 0, g.chance_off[g.max_depth + 1], g.bigc_off[g.max_depth + 1]};
+            const size_t whole = bytes + 4 * lds_structure_words(z, g.N, g.A, g.max_depth);
+            const bool staged = whole <= (size_t)g.lds_limit;
+            auto fn = staged ? k_lds<T, MAXA, EX, XT, true> : k_lds<T, MAXA, EX, XT, false>;
             if (prepare)
                 return hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-            hipLaunchKernelGGL(fn, dim3(1), dim3(BLOCK), bytes, s, gr, g.max_depth, g.N, g.A, T_,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)(staged ? whole : bytes));
+            hipLaunchKernelGGL(fn, dim3(1), dim3(BLOCK), staged ? whole : bytes, s, gr, g.max_depth, g.N, g.A, z, T_,
                                level_args<T>(g), g.t, f.rule, f.linear, alt);
             return hipGetLastError();
         }
@@ -1318,11 +1383,8 @@ hipError_t prepare_lds(const DevGame &g, int rule, size_t *bytes) {
 
 hipError_t launch_lds(const DevGame &g, const int32_t *game_range, int32_t T_, IterFlags f, int alt, hipStream_t s) {
     const size_t bytes = lds_schedule_bytes(g.N, g.A, g.fp64, g.pred != nullptr);
-    hipError_t e = g.fp64 ? lds_f64(g, game_range, T_, f, alt, s, bytes, false)
-                          : lds_f32(g, game_range, T_, f, alt, s, bytes, false);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_add_counter, dim3(1), dim3(64), 0, s, g.t, T_);
-    return hipGetLastError();
+    return g.fp64 ? lds_f64(g, game_range, T_, f, alt, s, bytes, false)
+                  : lds_f32(g, game_range, T_, f, alt, s, bytes, false);
 }
 
 // the instantiation launch_persistent uses for this game

@@ -899,7 +899,7 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     h->br_ok = true;
     h->E = E; h->Z = Z; h->pot = games[0].pot;
     DevGame &g = h->g;
-    g.N = (int32_t)N; g.I = (int32_t)I; g.A = (int32_t)A; g.Ndec = (int32_t)Ndec;
+    g.N = (int32_t)N; g.I = (int32_t)I; g.A = (int32_t)A; g.Ndec = (int32_t)Ndec; g.E = (int32_t)E;
     g.max_depth = max_depth; g.max_actions = max_actions;
     g.fp64 = o.precision == CFR_PRECISION_FP64 ? 1 : 0;
     g.rule = o.rule;
@@ -1577,6 +1577,7 @@ static cfr_status set_lds_schedule(cfr_handle *h) {
     size_t bytes = lds_schedule_bytes(h->g.N, h->g.A, h->g.fp64, h->g.pred != nullptr);
     int limit = 0;
     HIP_TRY(hipDeviceGetAttribute(&limit, hipDeviceAttributeMaxSharedMemoryPerBlock, h->opt.device));
+    h->g.lds_limit = limit;
     if (bytes > (size_t)limit)
         return fail(CFR_EINVAL, "the game needs " + std::to_string(bytes) + " bytes of LDS for the LDS schedule; "
                                 "a workgroup has " + std::to_string(limit));
