@@ -272,7 +272,8 @@ cfr_status cfr_batch_exploitability(cfr_handle *h, void *stream, double *expl, d
  * forward reach pass and the backward value pass level by level with the regret, clamp and average
  * updates fused into the backward levels (Algorithm 'alg:iteration'; Table 'tab:opsteps').  The first
  * call captures the iteration body into a hipGraph (after one direct iteration that counts toward n)
- * and later calls replay it (Sec. 4, "CUDA-graph execution").  n == 0 is a no-op.  Returns CFR_ESTATE
+ * and later calls replay it (Sec. 4, "CUDA-graph execution"); with one iteration per graph a handle in
+ * steady use also captures a run of a few iterations and replays that.  n == 0 is a no-op.  Returns CFR_ESTATE
  * if a persistent buffer recorded at capture time has changed, or after a persistent launch stopped
  * part-way (until cfr_reset or cfr_set_state).  Under the persistent schedule the call is one launch
  * that runs all n iterations and synchronises `stream`, so that a per-game barrier time-out
