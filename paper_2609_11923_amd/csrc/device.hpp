@@ -161,6 +161,17 @@ hipError_t launch_gather_payoffs(int64_t lo, int64_t hi, const int32_t *in, cons
                                  hipStream_t s);
 hipError_t launch_template(const DevGame &g, int64_t lo, int64_t hi, const int32_t *node, const int32_t *branch,
                            const double *u, const double *pic, const double *root, hipStream_t s);
+// the same from new root ranges: root child b of the game (n of them) deals the hands hands[b], its chance is
+// p(b) = r1 r2 / total, written to root as well.  The ranges travel in the launch's arguments.
+constexpr int RANGE_MAX = 256;
+struct RangeArgs {
+    double total;
+    int32_t n1, n2;          // n1 + n2 <= RANGE_MAX
+    double r[RANGE_MAX];     // r1, then r2
+};
+hipError_t launch_template_ranges(const DevGame &g, int64_t lo, int64_t hi, const int32_t *node, const int32_t *branch,
+                                  const double *u, const double *pic, const int2 *hands, int64_t n,
+                                  const RangeArgs &ranges, double *root, hipStream_t s);
 // evaluation: the reach pass on the average strategy (slots [lo, hi) of one launch), one level of the
 // sweep, the root values into out[3 * n] (average profile, best response of player 1, of player 2)
 hipError_t launch_reach_average(const DevGame &g, int32_t lo, int32_t hi, bool walk, hipStream_t s);

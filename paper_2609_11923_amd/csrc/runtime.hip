@@ -135,6 +135,7 @@ struct cfr_handle {
     // (lc_hand1[k], lc_hand2[k]), k = lc_hand_off[s] + a; lc_nh1/lc_nh2 are the range lengths
     std::vector<int64_t> lc_hand_off;
     std::vector<int32_t> lc_hand1, lc_hand2, lc_nh1, lc_nh2;
+    int2 *lc_hands = nullptr;          // device: the pairs (lc_hand1[k], lc_hand2[k])
     // canonical arrays of every game (options.keep_layout), for cfr_get_layout
     std::vector<Layout> layouts;
 };
@@ -1073,7 +1074,11 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
 #define LA(ptr, cnt) do { st = dev_alloc(h, &(ptr), (cnt)); if (st != CFR_OK) { free_handle(h); return st; } } while (0)
         LA(h->lc_node, nt); LA(h->lc_in, nt); LA(h->lc_branch, nt); LA(h->lc_u, nt); LA(h->lc_pic, nt);
         LA(h->lc_root, nr); LA(h->lc_stage, maxn);
+        std::vector<int2> hands;
+        for (size_t k = 0; k < h->lc_hand1.size(); k++) hands.push_back(make_int2(h->lc_hand1[k], h->lc_hand2[k]));
+        LA(h->lc_hands, (int64_t)hands.size());
 #undef LA
+        UP(h->lc_hands, hands);
         UP(h->lc_node, lc.node); UP(h->lc_in, lc.in); UP(h->lc_branch, lc.branch); UP(h->lc_u, lc.u);
         UP(h->lc_pic, lc.pic); UP(h->lc_root, lc.root);
         h->lc_term_off = lc.term_off;
@@ -1816,10 +1821,25 @@ cfr_status cfr_set_root_ranges(cfr_handle *h, int32_t game, const double *r1, in
         if (!(r2[i] >= 0.0) || !std::isfinite(r2[i])) return fail(CFR_EINVAL, "invalid range weight for player 2");
     // p(a) = r1(h1(a)) r2(h2(a)) / W, W the sum of the products over the root's children in child order
     const int64_t n = k1 - k0;
-    std::vector<double> prob((size_t)n);
     double W = 0.0;
     for (int64_t a = 0; a < n; a++) W += r1[h->lc_hand1[(size_t)(k0 + a)]] * r2[h->lc_hand2[(size_t)(k0 + a)]];
     if (!(W > 0.0) || !std::isfinite(W)) return fail(CFR_EINVAL, "the ranges give no dealt pair a positive weight");
+    if (n1 + n2 <= RANGE_MAX) {
+        RangeArgs ra;
+        ra.total = W;
+        ra.n1 = (int32_t)n1;
+        ra.n2 = (int32_t)n2;
+        std::copy(r1, r1 + n1, ra.r);
+        std::copy(r2, r2 + n2, ra.r + n1);
+        hipStream_t s = (hipStream_t)stream;
+        HIP_TRY(hipSetDevice(h->opt.device));
+        HIP_TRY(launch_template_ranges(h->g, h->lc_term_off[(size_t)game], h->lc_term_off[(size_t)game + 1], h->lc_node,
+                                       h->lc_branch, h->lc_u, h->lc_pic, h->lc_hands + k0, n, ra,
+                                       h->lc_root + h->lc_root_off[(size_t)game], s));
+        HIP_TRY(hipStreamSynchronize(s));
+        return CFR_OK;
+    }
+    std::vector<double> prob((size_t)n);
     for (int64_t a = 0; a < n; a++)
         prob[(size_t)a] = r1[h->lc_hand1[(size_t)(k0 + a)]] * r2[h->lc_hand2[(size_t)(k0 + a)]] / W;
     return write_root_chance(h, game, prob.data(), n, (hipStream_t)stream);
