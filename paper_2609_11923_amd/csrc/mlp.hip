@@ -802,7 +802,7 @@ struct cfr_mlp {
     // training, rows padded to a multiple of 32 (zeros): see RowsArgs and GradArgs
     uint16_t *H[4] = {}, *Ht[4] = {}, *dAt[4] = {}, *Xt = nullptr;
     float *dz = nullptr, *ce = nullptr, *wr = nullptr, *bias_part[4] = {}, *w_part[4] = {}, *head_part = nullptr;
-    std::vector<void *> allocs;
+    void *memory = nullptr;
 };
 
 namespace {
@@ -817,19 +817,20 @@ cfr_status mfail(cfr_status s, const std::string &m) {
         if (e_ != hipSuccess) return mfail(CFR_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
-template <typename T>
-cfr_status malloc_dev(cfr_mlp *n, T **p, int64_t count) {
-    void *q = nullptr;
-    const size_t bytes = (size_t)(count > 0 ? count : 1) * sizeof(T);
-    hipError_t e = hipMalloc(&q, bytes);
-    if (e != hipSuccess) return mfail(CFR_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
-    n->allocs.push_back(q);
-    *p = (T *)q;
-    return CFR_OK;
-}
+// The network's buffers are placed one after another, each on a 256-byte line of its own, in one allocation:
+// the device takes 10 to 40 us for each, and a network of three layers has 28.
+struct Placement {
+    std::vector<std::pair<void **, size_t>> at;
+    size_t bytes = 0;
+    template <typename T>
+    void add(T **p, int64_t count) {
+        at.push_back({(void **)p, bytes});
+        bytes += ((size_t)(count > 0 ? count : 1) * sizeof(T) + 255) / 256 * 256;
+    }
+};
 
 void free_mlp(cfr_mlp *n) {
-    for (void *p : n->allocs) (void)hipFree(p);
+    if (n->memory) (void)hipFree(n->memory);
     delete n;
 }
 
@@ -945,8 +946,8 @@ cfr_status cfr_mlp_create(const cfr_mlp_desc *desc, cfr_mlp **out) {
     // rows of the training buffers, a multiple of the largest row tile
     const int64_t R = (d.max_rows + ROW_PAD - 1) / ROW_PAD * ROW_PAD;
     const int64_t hid = d.hidden;
-    cfr_status st = CFR_OK;
-#define MA(p, c) do { st = malloc_dev(n, &(p), (c)); if (st != CFR_OK) { free_mlp(n); return st; } } while (0)
+    Placement place;
+#define MA(p, c) place.add(&(p), (c))
     MA(n->theta, n->P); MA(n->grad, n->P); MA(n->m, n->P); MA(n->v, n->P);
     {
         int64_t off = 0;
@@ -963,8 +964,14 @@ cfr_status cfr_mlp_create(const cfr_mlp_desc *desc, cfr_mlp **out) {
     MA(n->Xt, R * d.in_dim); MA(n->dz, R * 4); MA(n->ce, R); MA(n->wr, R);
     MA(n->head_part, (int64_t)HEAD_BLOCKS * (hid * 4 + 5));
 #undef MA
+    hipError_t e = hipMalloc(&n->memory, place.bytes);
+    if (e != hipSuccess) {
+        free_mlp(n);
+        return mfail(CFR_ENOMEM, "hipMalloc of " + std::to_string(place.bytes) + " bytes failed");
+    }
+    for (auto &[p, off] : place.at) *p = (char *)n->memory + off;
     // zero parameters until the caller sets them
-    hipError_t e = hipMemset(n->theta, 0, (size_t)n->P * 4);
+    e = hipMemset(n->theta, 0, (size_t)n->P * 4);
     if (e == hipSuccess) {   // and the bf16 copies with them
         k_refresh<<<(unsigned)((n->P + 255) / 256), 256>>>(weights_of(n), n->P);
         e = hipGetLastError();
