@@ -521,12 +521,13 @@ __device__ __forceinline__ void map_set(GroupLdsA<T, MAXA, MPT, GS> &L, int tid,
 //    bases, split where the group's nodes need it (GRP_WIDE groups, whose spans need more than 32 bits
 //    together or whose single set has more members than a chunk, keep them in eight);
 //  * a set record is eight bytes: its first member, first slot and player in one word, its own sequence;
-//  * the slots' regrets and strategy sums are requested before the members are reduced, when the registers
-//    of the member pass are free, and used after it.
-// Loads are unconditional: past a set's last action they repeat its last child (an address already read),
-// lanes past the chunk's end repeat its first member, so a chunk's loads are in flight together; only
-// stores and arithmetic are masked.  (A guard that skips a load no lane needs compiles to a branch with
-// a full wait at its join, which costs more than the load.)  The number of child loads per member
+//  * the slots' regrets and strategy sums are requested right after the child values, so that nothing waits
+//    for them before the reduction is done.
+// The member pass has no branch: past a set's last action loads repeat its last child (an address already
+// read), lanes past the group's end repeat its first member and store what that member's lane stores, slots
+// past the last one repeat it into rows nobody reads, and a group that updates nothing reads the empty
+// sequence's reach.  A guard compiles to a branch, and what a branch holds is neither issued with the loads
+// around it nor waited for apart from them.  The number of child loads per member
 // is the group's widest set, bucketed (with_action_bound; the public-state layout orders states by
 // action count, so most groups are uniform), and where a group's sets interleave -- a player-2 set's
 // members are strided by the opponent's hand count -- the host lists the group's members in node order
@@ -538,6 +539,9 @@ __device__ __forceinline__ void map_set(GroupLdsA<T, MAXA, MPT, GS> &L, int tid,
 // members, 13-byte sets, slots loaded after the reduction): 220M-node card game 0.74 -> 0.63 ms (2.75 GB of
 // design bytes, 4.4 TB/s), 256 subgames 103 -> 97 us, 26-card Leduc 61 -> 56 us in 11 launches; DCFR in FP64
 // on the 10.0M-node card game, with the discounts' powers out of the blocks, 12.7 -> 11.2 us per launch.
+// The guards taken out: five iterations of the 37.6M-node card game 1.40 -> 1.29 ms, ten of 256 subgames
+// 1.00 -> 0.95 ms, ten of Leduc with 3 ranks in FP64 0.43 -> 0.41 ms.  (Requesting the slots' state with the
+// group's records instead makes the child values wait for it: 1.44 ms for the first.)
 template <typename T, int MAXA, int MPT, bool EXT, int GS, int NA, bool PERM>
 __device__ __forceinline__ void group_body(const int4 &h0, const int4 &hb, const int4 &h1, const RuleArgs &ru,
                                            const LevelArgs<T> &a, GroupLdsA<T, MAXA, MPT, GS> &L) {
@@ -563,14 +567,20 @@ __device__ __forceinline__ void group_body(const int4 &h0, const int4 &hb, const
     const int32_t next = a.srec[min(ti + 1, h1.x - 1)].x;
     if constexpr (ROWS) {
         constexpr int UNROLL = SLOT_PASS ? SPT : 1;
-#pragma unroll UNROLL
-        for (int u = 0; u < SPT; u++) {
-            const int32_t q = u * BLOCK + tid;
-            const int32_t k = a.koff[S0 + min(q, nslots - 1)];
-            const T s = a.sigma[S0 + min(q, nslots - 1)];
-            if (q < nslots) {
-                L.ko[q] = k;
-                L.sg[q] = s;
+        int32_t k[UNROLL];
+        T s[UNROLL];
+#pragma unroll 1
+        for (int u0 = 0; u0 < SPT; u0 += UNROLL) {
+#pragma unroll
+            for (int u = 0; u < UNROLL; u++) {
+                const int32_t q = S0 + min((u0 + u) * BLOCK + tid, nslots - 1);
+                k[u] = a.koff[q];
+                s[u] = a.sigma[q];
+            }
+#pragma unroll
+            for (int u = 0; u < UNROLL; u++) {
+                L.ko[(u0 + u) * BLOCK + tid] = k[u];
+                L.sg[(u0 + u) * BLOCK + tid] = s[u];
             }
         }
     }
@@ -580,13 +590,13 @@ __device__ __forceinline__ void group_body(const int4 &h0, const int4 &hb, const
     const int32_t nA = (last ? nslots : (next >> SREC_SLOT_SHIFT) & SREC_SLOT_MASK) - sl;
     const int pl = (sr.x >> SREC_PLAYER_SHIFT) + 1;
     T po[MPT];
-    if (update) {
 #pragma unroll
-        for (int u = 0; u < MPT; u++) po[u] = a.seq[ms[u]];
-    }
+    for (int u = 0; u < MPT; u++) po[u] = a.seq[update ? ms[u] : -1];
     const T pown = a.seq[sr.y];
     if (has_set) map_set<T, MAXA, MPT, GS>(L, tid, nsets, sl, nslots, m0 - mbeg, m1 - mbeg);
     __syncthreads();
+    double sbp[SLOT_PASS ? SPT : 1];
+    T Rp[SLOT_PASS ? SPT : 1];
     {
         T cv[MPT][NA], sg[MPT][ROWS ? 1 : NA];
         int32_t sb[MPT], na[MPT];
@@ -609,6 +619,15 @@ __device__ __forceinline__ void group_body(const int4 &h0, const int4 &hb, const
 #pragma unroll
             for (int k = 0; k < NA; k++) cv[u][k] = a.v[h[u] + ko[k]];
         }
+        if constexpr (SLOT_PASS) {
+            const int32_t last_slot = update ? nslots - 1 : 0;
+#pragma unroll
+            for (int u = 0; u < SPT; u++) {
+                const int32_t q = S0 + min(u * BLOCK + tid, last_slot);
+                sbp[u] = a.sbar[q];
+                Rp[u] = a.R[q];
+            }
+        }
 #pragma unroll
         for (int u = 0; u < MPT; u++) {
             T vh = T(0);
@@ -619,27 +638,14 @@ __device__ __forceinline__ void group_body(const int4 &h0, const int4 &hb, const
                 else sk = sg[u][k];
                 vh = k < na[u] ? fma_t(sk, cv[u][k], vh) : vh;
             }
-            if (mbeg + u * BLOCK + tid >= mend) continue;
             const int32_t j = pj[u];
             a.v[h[u]] = vh;
-            if (update) {
-                L.po[j] = po[u];
+            L.po[j] = po[u];
 #pragma unroll
-                for (int k = 0; k < NA; k++) L.diff[j * MAXA + k] = cv[u][k] - vh;
-            }
+            for (int k = 0; k < NA; k++) L.diff[j * MAXA + k] = cv[u][k] - vh;
         }
     }
     if (!update) return;
-    double sbp[SLOT_PASS ? SPT : 1];
-    T Rp[SLOT_PASS ? SPT : 1];
-    if constexpr (SLOT_PASS) {
-#pragma unroll
-        for (int u = 0; u < SPT; u++) {
-            const int32_t q = S0 + min(u * BLOCK + tid, nslots - 1);
-            sbp[u] = a.sbar[q];
-            Rp[u] = a.R[q];
-        }
-    }
     __syncthreads();
     T r[MAXA];
 #pragma unroll
@@ -656,11 +662,8 @@ __device__ __forceinline__ void group_body(const int4 &h0, const int4 &hb, const
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < SPT; u++) {
-            const int32_t q = u * BLOCK + tid;
-            if (q < nslots) {
-                sbs[q] = sbp[u];
-                Rs[q] = Rp[u];
-            }
+            sbs[u * BLOCK + tid] = sbp[u];
+            Rs[u * BLOCK + tid] = Rp[u];
         }
         __syncthreads();
         if (has_set && ((ru.upd >> (pl - 1)) & 1)) {
