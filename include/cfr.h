@@ -4,7 +4,7 @@
  * to static, depth-sorted arrays (paper: Section 4 "Compiling CFR onto
  * Accelerators", Algorithm 'alg:iteration'; compiler passes: Appendix H,
  * Algorithm 'alg:compile'):
- *   regret matching (eq. rm) -> forward reach pass per depth level (eqs.
+ *   regret matching (eq. rm) -> reach pass over the sequences (eqs.
  *   reach, lanes) -> backward counterfactual-value pass per depth level
  *   (eq. cfv with chance folded into a values template, eq. template) ->
  *   per-information-set regret accumulation (eqs. regret, instregret) with
@@ -269,7 +269,7 @@ cfr_status cfr_batch_exploitability(cfr_handle *h, void *stream, double *expl, d
                                     double *value_avg, int32_t n);
 
 /* Run n CFR iterations on `stream` (asynchronous): per iteration, regret matching (eq. rm), the
- * forward reach pass and the backward value pass level by level with the regret, clamp and average
+ * reach pass over the sequences and the backward value pass level by level with the regret, clamp and average
  * updates fused into the backward levels (Algorithm 'alg:iteration'; Table 'tab:opsteps').  The first
  * call captures the iteration body into a hipGraph (after one direct iteration that counts toward n)
  * and later calls replay it (Sec. 4, "CUDA-graph execution"); with one iteration per graph a handle in
@@ -368,7 +368,7 @@ cfr_status cfr_set_root_ranges(cfr_handle *h, int32_t game, const double *r1, in
 /* Retire games of a batch, or bring them back (the batched form is not in the paper; its concluding
  * remarks motivate repeated subgame solves, and a solve stops once its subgame is good enough):
  * active[n] (host, n = the number of games) 0 retires a game.  cfr_iterate then launches only the
- * active games' update groups and chance nodes and the forward tiles that hold an active game (lists
+ * active games' update groups and chance nodes and the reach tiles that hold an active game (lists
  * built here; the iteration graphs are captured again on the next cfr_iterate), so a retired game's
  * state (regrets, strategy sums, strategy, values) stays as it was while the other games iterate,
  * bitwise as if it were not in the batch; the shared counter still advances, so a game brought back
