@@ -638,17 +638,17 @@ cfr_status build_forest(std::vector<Layout> &Ls, std::vector<DeviceLayout> &Ds, 
         F.grp_depth_off[MD + 1] = (int32_t)G; F.chance_off[MD + 1] = (int32_t)C; F.bigc_off[MD + 1] = (int32_t)B;
         if (N > 0x7fffffffLL) { err = "batch too large"; return CFR_EINVAL; }
         // per game: depth of each node and of each set, to remap ids
-        std::vector<std::vector<int8_t>> ndep(n), idep(n);
+        std::vector<std::vector<int32_t>> ndep(n), idep(n);
         std::vector<std::vector<int32_t>> slot_set(n);
         for (int s = 0; s < n; s++) {
             const DeviceLayout &D = Ds[s];
             ndep[s].resize(D.depth_off.back());
             for (int d = 0; d <= md_of(s); d++)
-                for (int32_t x = D.depth_off[d]; x < D.depth_off[d + 1]; x++) ndep[s][x] = (int8_t)d;
+                for (int32_t x = D.depth_off[d]; x < D.depth_off[d + 1]; x++) ndep[s][x] = d;
             const int32_t Is = D.iset_depth_off.back();
             idep[s].resize(Is);
             for (int d = 0; d <= md_of(s); d++)
-                for (int32_t i = D.iset_depth_off[d]; i < D.iset_depth_off[d + 1]; i++) idep[s][i] = (int8_t)d;
+                for (int32_t i = D.iset_depth_off[d]; i < D.iset_depth_off[d + 1]; i++) idep[s][i] = d;
             slot_set[s].resize(D.slot_off.empty() ? 0 : D.slot_off.back());
             for (int32_t i = 0; i < Is; i++)
                 for (int32_t q = D.slot_off[i]; q < D.slot_off[i + 1]; q++) slot_set[s][q] = i;
