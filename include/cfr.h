@@ -448,7 +448,8 @@ typedef struct {
 
 /* 128 -> 3 x 256 -> 4, max_rows 4096, device 0, Adam 0.9 / 0.999 / 1e-8. */
 void cfr_mlp_default_desc(cfr_mlp_desc *d);
-/* Allocate a network (all device memory is owned by it); parameters start at zero. */
+/* Allocate a network (all device memory is owned by it); parameters start at zero.  Returns once the network
+ * is ready: its first use may be on any stream. */
 cfr_status cfr_mlp_create(const cfr_mlp_desc *d, cfr_mlp **out);
 cfr_status cfr_mlp_num_params(cfr_mlp *n, int64_t *count);
 /* Load the flat parameter vector from host memory; clears the Adam moments and step count.

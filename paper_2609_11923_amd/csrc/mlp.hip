@@ -979,7 +979,9 @@ cfr_status cfr_mlp_create(const cfr_mlp_desc *desc, cfr_mlp **out) {
     if (e == hipSuccess) e = hipMemset(n->m, 0, (size_t)n->P * 4);
     if (e == hipSuccess) e = hipMemset(n->v, 0, (size_t)n->P * 4);
     if (e == hipSuccess) e = hipMemset(n->grad, 0, (size_t)n->P * 4);
-    if (e != hipSuccess) { free_mlp(n); return mfail(CFR_EDEVICE, std::string("hipMemset: ") + hipGetErrorString(e)); }
+    // the first call may come on a stream that the null stream does not order
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) { free_mlp(n); return mfail(CFR_EDEVICE, std::string("network setup: ") + hipGetErrorString(e)); }
     *out = n;
     return CFR_OK;
 }
