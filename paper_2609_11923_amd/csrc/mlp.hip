@@ -305,7 +305,7 @@ __global__ __launch_bounds__(64 * WR * (HID / 32 / CT), TRAIN || RT * WR == 1 ? 
     constexpr int PF = RT == 1 && CT == 1 ? (K0 < 128 || HID < 128 ? 4 : 8) : 4;
     constexpr int HPL = HID / 64;
     __shared__ __attribute__((aligned(16))) uint16_t act[ROWS * LDA];
-    __shared__ float red[TRAIN ? 256 : ROWS >= 64 ? ROWS * 16 : 1];
+    __shared__ __attribute__((aligned(16))) float red[TRAIN ? 256 : ROWS >= 64 ? ROWS * 16 : 1];
     __shared__ __attribute__((aligned(16))) float bias[4 * HID];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r0 = blockIdx.x * ROWS;
@@ -474,6 +474,11 @@ __global__ __launch_bounds__(64 * WR * (HID / 32 / CT), TRAIN || RT * WR == 1 ? 
 // ---- gradients: sums over rows ---------------------------------------------------------------
 constexpr int HEAD_BLOCKS = 256;
 
+// floats from one row of the output layer's partials to the next (HID * 4 weights, 4 biases, the loss): a multiple
+// of four, so that every row starts on a 16-byte line for the vector stores
+__host__ __device__ constexpr int head_row(int hid) { return hid * 4 + 8; }
+static_assert(head_row(64) % 4 == 0 && head_row(128) % 4 == 0 && head_row(256) % 4 == 0, "float4 stores of a partial row");
+
 struct GradArgs {
     Weights W;
     int rows, splits, kchunk, head_blocks;
@@ -484,7 +489,7 @@ struct GradArgs {
     const float *dz, *ce, *wr;
     float *w_part[4];         // [splits][fan in][HID]
     float *bias_part[4];      // [ceil(rows / BIAS_ROWS)][HID]
-    float *head_part;         // [head_blocks][HID * 4 + 5]: output weights, biases, loss
+    float *head_part;         // [head_blocks][head_row(HID)]: output weights, biases, loss
     int task0[5];             // first task of each hidden layer's weight gradient; task0[n_hidden] tasks in all
     float *grad, *loss, *m, *v;
     float lr, b1, b2, eps, c1, c2;   // Adam
@@ -501,8 +506,7 @@ __global__ __launch_bounds__(256) void k_wgrad(GradArgs f) {
     const int mma_blocks = (f.task0[L] + 3) / 4;
     if ((int)blockIdx.x >= mma_blocks) {
         const int b = blockIdx.x - mma_blocks;
-        constexpr int NP = HID * 4 + 5;
-        float *out = f.head_part + (int64_t)b * NP;
+        float *out = f.head_part + (int64_t)b * head_row(HID);
         if (tid < HID) {
             float tot[4];
             for (int w = 0; w < 4; w++) {
@@ -639,7 +643,7 @@ __global__ __launch_bounds__(256) void k_finish(GradArgs f, int64_t P) {
     float g;
     if (i >= f.W.woff[L]) {
         // output weights and biases are contiguous in the partial rows as in the parameters, then the loss
-        g = ordered_sum<64>(f.head_part + (i - f.W.woff[L]), f.head_blocks, HID * 4 + 5);
+        g = ordered_sum<64>(f.head_part + (i - f.W.woff[L]), f.head_blocks, head_row(HID));
         if (i == P) {
             f.loss[0] = g;
             return;
@@ -962,7 +966,7 @@ cfr_status cfr_mlp_create(const cfr_mlp_desc *desc, cfr_mlp **out) {
         MA(n->w_part[l], (int64_t)gemm_splits((int)d.max_rows) * n->fin[(size_t)l] * hid);
     }
     MA(n->Xt, R * d.in_dim); MA(n->dz, R * 4); MA(n->ce, R); MA(n->wr, R);
-    MA(n->head_part, (int64_t)HEAD_BLOCKS * (hid * 4 + 5));
+    MA(n->head_part, (int64_t)HEAD_BLOCKS * head_row(d.hidden));
 #undef MA
     hipError_t e = hipMalloc(&n->memory, place.bytes);
     if (e != hipSuccess) {
