@@ -133,7 +133,8 @@ typedef struct {
                               nodes before terminals inside each depth) */
     int use_graph;         /* 1: hipGraph replay (default); 0: direct kernel launches */
     int device;            /* HIP device ordinal (default 0) */
-    int test_fail_capture; /* test hook: treat graph capture as failed (warns once, launches directly) */
+    int test_fail_capture; /* test hook: 1 treats graph capture as failed (warns once, launches directly); 2 lets HIP
+                              fail the capture of several iterations (with one per graph, single ones go on) */
     int precision;         /* CFR_PRECISION_*: type of reach, values, regrets and strategy (default FP32);
                               strategy sums are FP64 in both */
     int persistent;        /* schedule, CFR_SCHEDULE_* (default LEVEL); LDS fails with CFR_EINVAL when the

@@ -489,7 +489,11 @@ void model_bytes(cfr_handle *h, const DeviceLayout &D) {
     h->method_lvl = (ml + pred_bytes) * halves;
 }
 
-cfr_status capture(cfr_handle *h, int iters, hipGraph_t *graph, hipGraphExec_t *exec) {
+cfr_status capture_graph(cfr_handle *h, int iters, hipGraph_t *graph, hipGraphExec_t *exec) {
+    if (h->opt.test_fail_capture == 2 && iters > 1) {   // a failure that HIP reports: nothing is being captured
+        hipGraph_t none = nullptr;
+        return fail(CFR_EGRAPH, std::string("test hook: ") + hipGetErrorString(hipStreamEndCapture(h->cap_stream, &none)));
+    }
     hipError_t e = hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return fail(CFR_EGRAPH, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
     cfr_status st = CFR_OK;
@@ -504,6 +508,12 @@ cfr_status capture(cfr_handle *h, int iters, hipGraph_t *graph, hipGraphExec_t *
     *graph = gr;
     *exec = ex;
     return CFR_OK;
+}
+
+cfr_status capture(cfr_handle *h, int iters, hipGraph_t *graph, hipGraphExec_t *exec) {
+    const cfr_status st = capture_graph(h, iters, graph, exec);
+    if (st != CFR_OK) (void)hipGetLastError();   // the caller goes on without the graph: later launches must not report it
+    return st;
 }
 
 // Destroy the captured iteration graphs; the next cfr_iterate captures them again.
@@ -726,6 +736,7 @@ static cfr_status persistent_iterate(cfr_handle *h, int64_t n, hipStream_t s) {
                 (void)hipGraphDestroy(gr);
             }
         }
+        if (!h->pexec) (void)hipGetLastError();   // launched directly below; a failed capture's error stays here
     }
     if (h->pexec && h->pgraph_n == n) {
         hipError_t e = hipGraphLaunch(h->pexec, s);
@@ -1300,7 +1311,7 @@ cfr_status cfr_iterate(cfr_handle *h, int64_t n, void *stream) {
         if (st != CFR_OK) return st;
         h->iters++;
         n--;
-        if (h->opt.test_fail_capture) st = fail(CFR_EGRAPH, "capture failure injected by test hook");
+        if (h->opt.test_fail_capture && h->opt.test_fail_capture != 2) st = fail(CFR_EGRAPH, "capture failure injected by test hook");
         else st = capture(h, 1, &h->graph1, &h->exec1);
         if (st == CFR_OK && h->opt.iters_per_graph > 1) st = capture(h, h->opt.iters_per_graph, &h->graphk, &h->execk);
         if (st != CFR_OK) {

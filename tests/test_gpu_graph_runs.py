@@ -37,3 +37,18 @@ def test_runs_of_iterations_equal_direct_launches(games, order):
                 a.iterate(n)
                 b.iterate(n)
                 assert same(a, b), (active, n)
+
+
+@pytest.mark.parametrize("per_graph", [1, 5])
+def test_a_failed_capture_of_several_iterations_stays_inside(per_graph):
+    """HIP keeps a failed call's error until it is read: a capture that fails, where single iterations (or direct
+    launches) go on, must not make the calls after it fail."""
+    game = gg.random_game(7, 4, 3, 6)
+    a = cfr.Solver(game, iters_per_graph=per_graph, test_fail_capture=2)
+    b = cfr.Solver(game, use_graph=False)
+    for n in (40, 12, 6, 40):
+        a.iterate(n)
+        b.iterate(n)
+        assert np.array_equal(a.strategy(), b.strategy())
+        assert same(a, b), n
+    assert a.exploitability() == b.exploitability()
