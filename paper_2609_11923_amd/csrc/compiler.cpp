@@ -545,6 +545,34 @@ void plan_reach(const DeviceLayout &D, std::vector<int32_t> &first, std::vector<
     first.push_back(md + 1);
 }
 
+std::vector<int32_t> slot_ranges(const DeviceLayout &D) {
+    std::vector<int32_t> R = D.game_range;
+    const int64_t I = (int64_t)D.slot_off.size() - 1;
+    std::vector<uint8_t> walk((size_t)(I > 0 ? D.slot_off[I] : 0), 0);   // per slot, within its part
+    const size_t stride = R.size() / (size_t)D.n_games;
+    for (int s = 0; s < D.n_games; s++) {
+        int32_t S0 = 0;   // first slot of the part (a game's slots of later depths lie above it)
+        for (int d = 0; d <= D.game_depth[s]; d++) {
+            int32_t *r = &R[(size_t)s * stride + (size_t)d * GR_FIELDS];
+            const int32_t b = D.grp_iset_off[r[2]], e = D.grp_iset_off[r[3]];
+            r[0] = D.slot_off[b];
+            r[1] = D.slot_off[e];
+            int w = 0;
+            for (int32_t i = b; i < e; i++)
+                if (D.iset_seq[i] >= S0) w = std::max(w, walk[D.iset_seq[i]] + 1);
+            if (w > REACH_WALK) {
+                S0 = r[0];
+                r[1] |= REACH_CUT;
+            }
+            for (int32_t i = b; i < e; i++) {
+                const int k = D.iset_seq[i] >= S0 ? walk[D.iset_seq[i]] + 1 : 0;
+                for (int32_t q = D.slot_off[i]; q < D.slot_off[i + 1]; q++) walk[q] = (uint8_t)k;
+            }
+        }
+    }
+    return R;
+}
+
 bool plan_persistent(const std::vector<int64_t> &nodes, int32_t wg_nodes, int32_t max_w, int n_queues,
                      PersistentWork &P, std::string &err) {
     const int n = (int)nodes.size();

@@ -154,6 +154,12 @@ constexpr int REACH_WALK = 8;
 constexpr int32_t REACH_WIDE = 1 << 18;
 void plan_reach(const DeviceLayout &D, std::vector<int32_t> &first, std::vector<int8_t> &walk);
 
+// D.game_range as the one-launch schedules read it: the node range of a (game, depth) is replaced by its slot
+// range, with REACH_CUT set in the end where the game's reach pass starts a new part.  A part ends before a
+// walk in it would get longer than REACH_WALK (REACH_WIDE does not count: within one launch a part costs a barrier).
+constexpr int32_t REACH_CUT = 1 << 30;   // above any slot (at most 2^28)
+std::vector<int32_t> slot_ranges(const DeviceLayout &D);
+
 // Work plan of the persistent schedule.  Game g gets W_g = max(1, ceil(nodes_g / wg_nodes)) workgroups
 // ("ranks"); games are placed largest first on the least loaded of n_queues queues (one per XCD) and a
 // game's ranks are consecutive tickets of its queue.  Workgroups claim tickets in order at run time, so

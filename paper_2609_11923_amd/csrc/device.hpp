@@ -18,7 +18,7 @@ constexpr int GRP_PERM = 1, GRP_WIDE = 2, GRP_ACTIONS = 8, GRP_PLAYERS = 16;
 // Set record word (DevGame::srec): first member and first slot relative to the group's (a group of several
 // sets has at most 1,024 members, and 256 sets of 64 slots), and the player less one.
 constexpr int32_t SREC_MEMBER_MASK = 0x7ff, SREC_SLOT_SHIFT = 11, SREC_SLOT_MASK = 0x3fff, SREC_PLAYER_SHIFT = 25;
-// fields per (game, depth) in game_range: node lo/hi, group lo/hi, chance lo/hi, big chance lo/hi
+// fields per (game, depth) in the device's ranges (slot_ranges): slot lo/hi, group lo/hi, chance lo/hi, big chance lo/hi
 constexpr int GR_FIELDS_DEV = 8;
 // slots per workgroup of a launch of the reach pass, by whether it walks
 constexpr int32_t reach_tile(bool walk) { return walk ? 256 : 1024; }
@@ -139,7 +139,7 @@ hipError_t persistent_occupancy(const DevGame &g, int *blocks_per_cu);
 // more than 16 actions per set.
 size_t lds_schedule_bytes(int32_t N, int32_t A, int fp64, int pred);
 hipError_t prepare_lds(const DevGame &g, int rule, size_t *bytes);
-hipError_t launch_lds(const DevGame &g, const int32_t *game_range, int32_t T, IterFlags f, int alternating,
+hipError_t launch_lds(const DevGame &g, const int32_t *ranges, int32_t n_cuts, int32_t T, IterFlags f, int alternating,
                       hipStream_t s);
 // counter bump for games without edges
 hipError_t launch_tick(const DevGame &g, hipStream_t s);

@@ -33,10 +33,10 @@ hipError_t persistent_f32(const DevGame &g, const PersistentPlan &p, int32_t T_,
 hipError_t persistent_f64(const DevGame &g, const PersistentPlan &p, int32_t T_, IterFlags f, int alt, hipStream_t s);
 const void *persistent_fn_f32(const DevGame &g);
 const void *persistent_fn_f64(const DevGame &g);
-hipError_t lds_f32(const DevGame &g, const int32_t *gr, int32_t T_, IterFlags f, int alt, hipStream_t s, size_t bytes,
-                   bool prepare);
-hipError_t lds_f64(const DevGame &g, const int32_t *gr, int32_t T_, IterFlags f, int alt, hipStream_t s, size_t bytes,
-                   bool prepare);
+hipError_t lds_f32(const DevGame &g, const int32_t *gr, int32_t n_cuts, int32_t T_, IterFlags f, int alt, hipStream_t s,
+                   size_t bytes, bool prepare);
+hipError_t lds_f64(const DevGame &g, const int32_t *gr, int32_t n_cuts, int32_t T_, IterFlags f, int alt, hipStream_t s,
+                   size_t bytes, bool prepare);
 #if CFR_PART == 1 || CFR_PART == 3
 using PartT = float;
 #define LEVEL_OF level_f32
@@ -57,13 +57,12 @@ static_assert(GROUP_SETS_MAX <= BLOCK && GROUP_SETS_MAX <= 256, "update group se
 
 // The reach of the sequence that ends in slot p: the strategies along it multiplied from the root on,
 // as ((1 * s1) * s2) * ....  Slots below S0 are finished (seq holds their reach; seq[-1] = 1 is the empty
-// sequence); above, the walk collects the strategies on the way up.  Walks of at most REACH_WALK slots
-// stay in registers; a longer one looks every strategy up from the bottom again.
+// sequence); above, the walk collects the strategies on the way up: at most REACH_WALK of them, which stay
+// in registers (plan_reach and slot_ranges choose S0 so that no walk is longer).
 template <typename T>
 __device__ __forceinline__ T seq_reach(int32_t p, int32_t S0, const int32_t *slot_par, const T *sigma, const T *seq) {
     T s[REACH_WALK];
     int n = 0;
-    const int32_t p0 = p;
 #pragma unroll
     for (int k = 0; k < REACH_WALK; k++) {
         s[k] = T(1);
@@ -72,19 +71,6 @@ __device__ __forceinline__ T seq_reach(int32_t p, int32_t S0, const int32_t *slo
             p = slot_par[p];
             n = k + 1;
         }
-    }
-    if (p >= S0) {
-        while (p >= S0) {
-            p = slot_par[p];
-            n++;
-        }
-        T acc = seq[p];
-        for (int k = n - 1; k >= 0; k--) {
-            int32_t x = p0;
-            for (int j = 0; j < k; j++) x = slot_par[x];
-            acc = acc * sigma[x];
-        }
-        return acc;
     }
     T acc = seq[p];
 #pragma unroll
@@ -878,12 +864,22 @@ __device__ bool persistent_game(int32_t gm, int32_t rank, int32_t W, const int32
     for (int32_t it = 1; it <= n_iter; it++) {
         for (int half = 0; half < halves; half++) {
             const RuleArgs ru = rule_args(rule, linear, alternating ? 1 << half : 3, t0 + it);
-            // every slot walks its whole sequence, so the pass needs no barrier between depths
+            // A slot walks its sequence up to the start of its part.  Several workgroups meet at a barrier of about
+            // 2 us between parts, so a part holds all depths that REACH_WALK lets it (slot_ranges); a game's
+            // only workgroup synchronises for less than a walk's first step costs, and every depth is a part.
+            // Measured, FP32, 8 games of one workgroup in which each player moves m times in a row: m = 8 54 us an
+            // iteration against 57 with the longer parts, m = 50 312 against 327 (2,720 when every
+            // slot walked its whole sequence).
+            int32_t S0 = 0;
             for (int32_t d = 0; d < Ds; d++) {
                 const int32_t *r = gr + d * GR_FIELDS_DEV;
-                const int32_t lo = a.slot_off[a.grp_iset_off[r[2]]], hi = a.slot_off[a.grp_iset_off[r[3]]];
+                const int32_t lo = r[0], hi = r[1] & ~REACH_CUT;
+                if (W == 1 ? d > 0 && lo < hi : (r[1] & REACH_CUT) != 0) {
+                    if (!game_barrier(barrier + gm, W, epoch, err, timeout_ticks)) return false;
+                    S0 = lo;
+                }
                 for (int32_t q = lo + rank * BLOCK + tid; q < hi; q += W * BLOCK)
-                    a.seq[q] = seq_reach<T>(a.slot_par[q], 0, a.slot_par, a.sigma, a.seq) * a.sigma[q];
+                    a.seq[q] = seq_reach<T>(a.slot_par[q], S0, a.slot_par, a.sigma, a.seq) * a.sigma[q];
             }
             if (!game_barrier(barrier + gm, W, epoch, err, timeout_ticks)) return false;
             for (int32_t d = Ds - 1; d >= 0; d--) {
@@ -1001,8 +997,8 @@ __host__ __device__ inline size_t lds_structure_words(const LdsSizes &z, int32_t
 }
 
 template <typename T, int MAXA, bool EXPLICIT, bool EXT, bool STAGED>
-__global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, int32_t D, int32_t N, int32_t A,
-                                               LdsSizes z, int32_t n_iter, LevelArgs<T> g, int32_t *tcount, int rule,
+__global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, int32_t n_cuts, int32_t D, int32_t N,
+                                               int32_t A, LdsSizes z, int32_t n_iter, LevelArgs<T> g, int32_t *tcount, int rule,
                                                int linear, int alternating) {
     extern __shared__ __align__(16) unsigned char smem[];
     double *sb = reinterpret_cast<double *>(smem);
@@ -1064,11 +1060,21 @@ __global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, i
     __syncthreads();
     a.v = v; a.seq = seq; a.sigma = sig; a.R = R; a.sbar = sb; a.pred = pred;
     const int halves = alternating ? 2 : 1;
+    const int32_t *cuts = gr + (D + 1) * GR_FIELDS_DEV;
     for (int32_t it = 1; it <= n_iter; it++) {
         for (int half = 0; half < halves; half++) {
             const RuleArgs ru = rule_args(rule, linear, alternating ? 1 << half : 3, t0 + it);
-            for (int32_t q = tid; q < A; q += BLOCK)
-                seq[q] = seq_reach<T>(a.slot_par[q], 0, a.slot_par, sig, seq) * sig[q];
+            // one part, unless sequences are longer than a walk
+            int32_t S0 = 0;
+            for (int32_t c = 0; c < n_cuts; c++) {
+                const int32_t S1 = cuts[c];
+                for (int32_t q = S0 + tid; q < S1; q += BLOCK)
+                    seq[q] = seq_reach<T>(a.slot_par[q], S0, a.slot_par, sig, seq) * sig[q];
+                __syncthreads();
+                S0 = S1;
+            }
+            for (int32_t q = S0 + tid; q < A; q += BLOCK)
+                seq[q] = seq_reach<T>(a.slot_par[q], S0, a.slot_par, sig, seq) * sig[q];
             __syncthreads();
             for (int32_t d = D - 1; d >= 0; d--) {
                 int32_t ib, ie, cb, ce, bb, be;
@@ -1336,7 +1342,7 @@ hipError_t PERSISTENT_OF(const DevGame &g, const PersistentPlan &p, int32_t T_, 
 #endif
 
 struct LdsLaunch {
-    const DevGame &g; const int32_t *gr; int32_t T_; IterFlags f; int alt; hipStream_t s; size_t bytes;
+    const DevGame &g; const int32_t *gr; int32_t n_cuts, T_; IterFlags f; int alt; hipStream_t s; size_t bytes;
     bool prepare;   // true: only raise the kernel's dynamic LDS limit to bytes
     template <typename T, int MAXA, int MPT, bool EX, bool XT, int AF>
     hipError_t operator()() const {
@@ -1355,7 +1361,7 @@ struct LdsLaunch {
                 return hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)(staged ? whole : bytes));
-            hipLaunchKernelGGL(fn, dim3(1), dim3(BLOCK), staged ? whole : bytes, s, gr, g.max_depth, g.N, g.A, z, T_,
+            hipLaunchKernelGGL(fn, dim3(1), dim3(BLOCK), staged ? whole : bytes, s, gr, n_cuts, g.max_depth, g.N, g.A, z, T_,
                                level_args<T>(g), g.t, f.rule, f.linear, alt);
             return hipGetLastError();
         }
@@ -1372,9 +1378,9 @@ static hipError_t lds_dispatch(const DevGame &g, const LdsLaunch &L) {
 }
 
 #if CFR_PART == 3 || CFR_PART == 4
-hipError_t LDS_OF(const DevGame &g, const int32_t *gr, int32_t T_, IterFlags f, int alt, hipStream_t s, size_t bytes,
-                  bool prepare) {
-    return lds_dispatch<PartT>(g, LdsLaunch{g, gr, T_, f, alt, s, bytes, prepare});
+hipError_t LDS_OF(const DevGame &g, const int32_t *gr, int32_t n_cuts, int32_t T_, IterFlags f, int alt, hipStream_t s,
+                  size_t bytes, bool prepare) {
+    return lds_dispatch<PartT>(g, LdsLaunch{g, gr, n_cuts, T_, f, alt, s, bytes, prepare});
 }
 #endif
 
@@ -1409,13 +1415,14 @@ hipError_t prepare_lds(const DevGame &g, int rule, size_t *bytes) {
     *bytes = lds_schedule_bytes(g.N, g.A, g.fp64, g.pred != nullptr);
     if (g.max_actions > 16) return hipErrorInvalidValue;
     const IterFlags f{rule, 0, 3};
-    return g.fp64 ? lds_f64(g, nullptr, 0, f, 0, nullptr, *bytes, true) : lds_f32(g, nullptr, 0, f, 0, nullptr, *bytes, true);
+    return g.fp64 ? lds_f64(g, nullptr, 0, 0, f, 0, nullptr, *bytes, true) : lds_f32(g, nullptr, 0, 0, f, 0, nullptr, *bytes, true);
 }
 
-hipError_t launch_lds(const DevGame &g, const int32_t *game_range, int32_t T_, IterFlags f, int alt, hipStream_t s) {
+hipError_t launch_lds(const DevGame &g, const int32_t *ranges, int32_t n_cuts, int32_t T_, IterFlags f, int alt,
+                      hipStream_t s) {
     const size_t bytes = lds_schedule_bytes(g.N, g.A, g.fp64, g.pred != nullptr);
-    return g.fp64 ? lds_f64(g, game_range, T_, f, alt, s, bytes, false)
-                  : lds_f32(g, game_range, T_, f, alt, s, bytes, false);
+    return g.fp64 ? lds_f64(g, ranges, n_cuts, T_, f, alt, s, bytes, false)
+                  : lds_f32(g, ranges, n_cuts, T_, f, alt, s, bytes, false);
 }
 
 // the instantiation launch_persistent uses for this game

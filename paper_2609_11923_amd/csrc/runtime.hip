@@ -73,15 +73,18 @@ struct cfr_handle {
     int32_t n_games = 1;
     std::vector<int64_t> game_slot_base;
     std::vector<int32_t> game_depth, game_range;
+    std::vector<int32_t> slot_range;   // game_range as the one-launch schedules read it
     std::vector<double> game_pot;
     // persistent schedule
     bool persistent = false;
     // set when a persistent launch stopped part-way (a barrier timed out): the state is partial, so
     // cfr_iterate refuses until cfr_reset starts over
     bool broken = false;
-    // LDS-resident schedule (one tiny game, one workgroup): per-depth ranges on the device
+    // LDS-resident schedule (one tiny game, one workgroup): per-depth ranges on the device, then the first slots
+    // of the reach pass's parts after the first
     bool lds = false;
     int32_t *lds_range = nullptr;
+    int32_t lds_cuts = 0;
     int32_t wg_nodes = 16384;
     PersistentPlan pp{};
     std::vector<void *> pp_allocs;
@@ -679,7 +682,7 @@ static cfr_status build_persistent_plan(cfr_handle *h, int32_t wg_nodes) {
     cfr_status st;
     if ((st = alloc((void **)&pp.tickets, table.size() * sizeof(int4))) != CFR_OK) return st;
     if ((st = alloc((void **)&pp.q_off, P.q_off.size() * sizeof(int32_t))) != CFR_OK) return st;
-    if ((st = alloc((void **)&pp.game_range, h->game_range.size() * sizeof(int32_t))) != CFR_OK) return st;
+    if ((st = alloc((void **)&pp.game_range, h->slot_range.size() * sizeof(int32_t))) != CFR_OK) return st;
     if ((st = alloc((void **)&pp.game_depth, (size_t)n * sizeof(int32_t))) != CFR_OK) return st;
     // barrier counters of the games, then the queues' claim counters (zeroed together per launch)
     if ((st = alloc((void **)&pp.barrier, ((size_t)n + PERSISTENT_QUEUES) * sizeof(int32_t))) != CFR_OK) return st;
@@ -687,7 +690,7 @@ static cfr_status build_persistent_plan(cfr_handle *h, int32_t wg_nodes) {
     pp.claim = pp.barrier + n;
     HIP_TRY(hipMemcpy(pp.tickets, table.data(), table.size() * sizeof(int4), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(pp.q_off, P.q_off.data(), P.q_off.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(pp.game_range, h->game_range.data(), h->game_range.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(pp.game_range, h->slot_range.data(), h->slot_range.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(pp.game_depth, h->game_depth.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice));
     HIP_TRY(hipMemset(pp.err, 0, sizeof(int32_t)));
     {
@@ -721,7 +724,7 @@ static cfr_status persistent_iterate(cfr_handle *h, int64_t n, hipStream_t s) {
         h->pgraph_n = -1;
         hipError_t e = hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess) {
-            hipError_t le = h->lds ? launch_lds(h->g, h->lds_range, (int32_t)n, f, alt, h->cap_stream)
+            hipError_t le = h->lds ? launch_lds(h->g, h->lds_range, h->lds_cuts, (int32_t)n, f, alt, h->cap_stream)
                                    : launch_persistent(h->g, h->pp, (int32_t)n, f, alt, h->cap_stream);
             hipGraph_t gr = nullptr;
             e = hipStreamEndCapture(h->cap_stream, &gr);
@@ -742,7 +745,7 @@ static cfr_status persistent_iterate(cfr_handle *h, int64_t n, hipStream_t s) {
         hipError_t e = hipGraphLaunch(h->pexec, s);
         if (e != hipSuccess) return fail(CFR_EGRAPH, std::string("hipGraphLaunch: ") + hipGetErrorString(e));
     } else if (h->lds) {
-        HIP_TRY(launch_lds(h->g, h->lds_range, (int32_t)n, f, alt, s));
+        HIP_TRY(launch_lds(h->g, h->lds_range, h->lds_cuts, (int32_t)n, f, alt, s));
     } else {
         HIP_TRY(launch_persistent(h->g, h->pp, (int32_t)n, f, alt, s));
     }
@@ -951,6 +954,7 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     h->game_slot_base = DL.game_slot_base;
     h->game_depth = DL.game_depth;
     h->game_range = DL.game_range;
+    h->slot_range = slot_ranges(DL);
     for (int s = 0; s < n; s++) h->game_pot.push_back(games[s].pot);
     h->lc_hand_off = std::move(hand_off);
     h->lc_hand1 = std::move(hand1);
@@ -1664,10 +1668,14 @@ static cfr_status set_lds_schedule(cfr_handle *h) {
     if (prepare_lds(h->g, h->opt.rule, &bytes) != hipSuccess)
         return fail(CFR_EINVAL, "the LDS schedule supports at most 16 actions per information set");
     if (!h->lds_range) {
-        cfr_status st = dev_alloc(h, &h->lds_range, (int64_t)h->game_range.size());
+        std::vector<int32_t> ranges = h->slot_range;
+        for (size_t d = 0; d < h->slot_range.size() / GR_FIELDS; d++)
+            if (h->slot_range[d * GR_FIELDS + 1] & REACH_CUT) ranges.push_back(h->slot_range[d * GR_FIELDS]);
+        cfr_status st = dev_alloc(h, &h->lds_range, (int64_t)ranges.size());
         if (st != CFR_OK) return st;
-        st = upload(h, h->lds_range, h->game_range.data(), h->game_range.size());
+        st = upload(h, h->lds_range, ranges.data(), ranges.size());
         if (st != CFR_OK) return st;
+        h->lds_cuts = (int32_t)(ranges.size() - h->slot_range.size());
     }
     if (h->pexec) { (void)hipGraphExecDestroy(h->pexec); h->pexec = nullptr; }
     if (h->pgraph) { (void)hipGraphDestroy(h->pgraph); h->pgraph = nullptr; }

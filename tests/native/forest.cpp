@@ -95,6 +95,44 @@ int main(int argc, char **argv) {
                 CHECK((F.mem_seq[(size_t)m] >= 0) == (d >= 1));
             }
         }
+    // the one-launch schedules' slot ranges: a game's slots per depth, and parts in which no slot walks more
+    // than REACH_WALK slots up, none of them longer than it could be
+    const std::vector<int32_t> R = slot_ranges(F);
+    CHECK(R.size() == F.game_range.size());
+    int32_t slots = 0;
+    for (int s = 0; s < n; s++) {
+        std::vector<int32_t> starts(1, 0);
+        for (int d = 0; d <= depth[(size_t)s]; d++) {
+            const int32_t *r = &R[((size_t)s * (md + 1) + d) * GR_FIELDS], *old = &F.game_range[((size_t)s * (md + 1) + d) * GR_FIELDS];
+            for (int k = 2; k < GR_FIELDS; k++) CHECK(r[k] == old[k]);
+            const int32_t lo = r[0], hi = r[1] & ~REACH_CUT;
+            CHECK(hi - lo == (d < depth[(size_t)s] ? 2 : 0));
+            CHECK(lo == hi || lo == F.slot_off[(size_t)F.grp_iset_off[(size_t)r[2]]]);
+            slots += hi - lo;
+            auto longest = [&](int32_t S0) {
+                int w = 0;
+                for (int32_t q = lo; q < hi; q++) {
+                    int32_t i = 0;
+                    while (F.slot_off[(size_t)i + 1] <= q) i++;
+                    int k = 0;
+                    for (int32_t p = F.iset_seq[(size_t)i]; p >= S0; k++) {
+                        int32_t j = 0;
+                        while (F.slot_off[(size_t)j + 1] <= p) j++;
+                        p = F.iset_seq[(size_t)j];
+                    }
+                    w = std::max(w, k);
+                }
+                return w;
+            };
+            if (r[1] & REACH_CUT) {
+                CHECK(longest(starts.back()) == REACH_WALK + 1);
+                starts.push_back(lo);
+            }
+            CHECK(longest(starts.back()) <= REACH_WALK);
+        }
+        CHECK((int)starts.size() == (depth[(size_t)s] + 1) / 2 / (REACH_WALK + 1) + ((depth[(size_t)s] + 1) / 2 % (REACH_WALK + 1) > 0));
+    }
+    CHECK(slots == F.slot_off.back());
     std::printf("ok\n");
     return 0;
 }
