@@ -545,18 +545,25 @@ void plan_reach(const DeviceLayout &D, std::vector<int32_t> &first, std::vector<
     first.push_back(md + 1);
 }
 
-std::vector<int32_t> slot_ranges(const DeviceLayout &D) {
-    std::vector<int32_t> R = D.game_range;
+std::vector<int32_t> one_launch_ranges(const DeviceLayout &D) {
+    const size_t rows = D.game_range.size() / GR_FIELDS;
+    std::vector<int32_t> R(rows * DR_FIELDS, 0);
     const int64_t I = (int64_t)D.slot_off.size() - 1;
     std::vector<uint8_t> walk((size_t)(I > 0 ? D.slot_off[I] : 0), 0);   // per slot, within its part
-    const size_t stride = R.size() / (size_t)D.n_games;
     for (int s = 0; s < D.n_games; s++) {
         int32_t S0 = 0;   // first slot of the part (a game's slots of later depths lie above it)
         for (int d = 0; d <= D.game_depth[s]; d++) {
-            int32_t *r = &R[(size_t)s * stride + (size_t)d * GR_FIELDS];
-            const int32_t b = D.grp_iset_off[r[2]], e = D.grp_iset_off[r[3]];
+            const size_t row = (size_t)s * (rows / (size_t)D.n_games) + (size_t)d;
+            const int32_t *g = &D.game_range[row * GR_FIELDS];
+            int32_t *r = &R[row * DR_FIELDS];
+            std::copy(g + 2, g + GR_FIELDS, r + 2);
+            const int32_t b = D.grp_iset_off[g[2]], e = D.grp_iset_off[g[3]];
+            const bool last = std::all_of(D.slot_kids.begin() + D.slot_off[b], D.slot_kids.begin() + D.slot_off[e],
+                                          [](uint8_t k) { return k == KIDS_TERMINAL; });
             r[0] = D.slot_off[b];
-            r[1] = D.slot_off[e];
+            r[1] = last ? r[0] : D.slot_off[e];
+            r[8] = b;
+            r[9] = last ? b : e;
             int w = 0;
             for (int32_t i = b; i < e; i++)
                 if (D.iset_seq[i] >= S0) w = std::max(w, walk[D.iset_seq[i]] + 1);

@@ -154,11 +154,14 @@ constexpr int REACH_WALK = 8;
 constexpr int32_t REACH_WIDE = 1 << 18;
 void plan_reach(const DeviceLayout &D, std::vector<int32_t> &first, std::vector<int8_t> &walk);
 
-// D.game_range as the one-launch schedules read it: the node range of a (game, depth) is replaced by its slot
-// range, with REACH_CUT set in the end where the game's reach pass starts a new part.  A part ends before a
-// walk in it would get longer than REACH_WALK (REACH_WIDE does not count: within one launch a part costs a barrier).
+// The ranges of every (game, depth) as the one-launch schedules read them, stride DR_FIELDS: the slots of the reach
+// pass, then update groups, chance nodes and big chance nodes as in game_range, then the sets of the reach pass.
+// The pass leaves out depths whose slots all lead to terminals, whose reach nothing reads.  REACH_CUT is set in the
+// end of the slots where the game's pass starts a new part, which it does before a walk gets longer than REACH_WALK
+// (REACH_WIDE does not count: within one launch a part costs a barrier).
+constexpr int DR_FIELDS = 10;
 constexpr int32_t REACH_CUT = 1 << 30;   // above any slot (at most 2^28)
-std::vector<int32_t> slot_ranges(const DeviceLayout &D);
+std::vector<int32_t> one_launch_ranges(const DeviceLayout &D);
 
 // Work plan of the persistent schedule.  Game g gets W_g = max(1, ceil(nodes_g / wg_nodes)) workgroups
 // ("ranks"); games are placed largest first on the least loaded of n_queues queues (one per XCD) and a

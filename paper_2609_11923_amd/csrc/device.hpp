@@ -18,8 +18,6 @@ constexpr int GRP_PERM = 1, GRP_WIDE = 2, GRP_ACTIONS = 8, GRP_PLAYERS = 16;
 // Set record word (DevGame::srec): first member and first slot relative to the group's (a group of several
 // sets has at most 1,024 members, and 256 sets of 64 slots), and the player less one.
 constexpr int32_t SREC_MEMBER_MASK = 0x7ff, SREC_SLOT_SHIFT = 11, SREC_SLOT_MASK = 0x3fff, SREC_PLAYER_SHIFT = 25;
-// fields per (game, depth) in the device's ranges (slot_ranges): slot lo/hi, group lo/hi, chance lo/hi, big chance lo/hi
-constexpr int GR_FIELDS_DEV = 8;
 // slots per workgroup of a launch of the reach pass, by whether it walks
 constexpr int32_t reach_tile(bool walk) { return walk ? 256 : 1024; }
 // elements before seq[0] in its allocation: seq[-1] = 1, the reach of the empty sequence

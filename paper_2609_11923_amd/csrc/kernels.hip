@@ -58,7 +58,7 @@ static_assert(GROUP_SETS_MAX <= BLOCK && GROUP_SETS_MAX <= 256, "update group se
 // The reach of the sequence that ends in slot p: the strategies along it multiplied from the root on,
 // as ((1 * s1) * s2) * ....  Slots below S0 are finished (seq holds their reach; seq[-1] = 1 is the empty
 // sequence); above, the walk collects the strategies on the way up: at most REACH_WALK of them, which stay
-// in registers (plan_reach and slot_ranges choose S0 so that no walk is longer).
+// in registers (plan_reach and one_launch_ranges choose S0 so that no walk is longer).
 template <typename T>
 __device__ __forceinline__ T seq_reach(int32_t p, int32_t S0, const int32_t *slot_par, const T *sigma, const T *seq) {
     T s[REACH_WALK];
@@ -171,6 +171,25 @@ struct LevelArgs {
     T *pred;      // PCFR+ prediction buffer, nullptr for the other rules
     const int32_t *mem_words, *player_words;   // mem and iset_player as words (games staged whole in LDS)
 };
+
+// The reach of set i's slots, all of which continue the same sequence: a walk per set, where k_reach has one per slot
+// to keep its accesses contiguous.
+template <typename T, int MAXA>
+__device__ __forceinline__ void set_reach(int32_t i, int32_t S0, const LevelArgs<T> &a) {
+    const int32_t s0 = a.slot_off[i], nA = a.slot_off[i + 1] - s0, p = a.iset_seq[i];
+    constexpr int U = MAXA < 4 ? MAXA : 4;
+    T own = T(0);
+    for (int32_t k0 = 0; k0 < nA; k0 += U) {
+        T x[U];
+#pragma unroll
+        for (int k = 0; k < U; k++) x[k] = a.sigma[s0 + min(k0 + k, nA - 1)];
+        if (k0 == 0) own = seq_reach<T>(p, S0, a.slot_par, a.sigma, a.seq);
+#pragma unroll
+        for (int k = 0; k < U; k++)
+            if (k0 + k < nA) a.seq[s0 + k0 + k] = own * x[k];
+        if constexpr (MAXA <= 4) break;
+    }
+}
 
 // Value of an internal chance node: the sum of its children (chance folded into the template).
 template <typename T, bool EXPLICIT>
@@ -861,7 +880,7 @@ __device__ bool persistent_game(int32_t gm, int32_t rank, int32_t W, const int32
                                 const LevelArgs<T> &a, int32_t t0, int32_t *barrier,
                                 int32_t *err, int64_t timeout_ticks, int rule, int linear, int alternating,
                                 LevelLds<T, MAXA, MPT, EXPLICIT, AF> &L) {
-    const int32_t *gr = game_range + (size_t)gm * (MD + 1) * GR_FIELDS_DEV;
+    const int32_t *gr = game_range + (size_t)gm * (MD + 1) * DR_FIELDS;
     const int32_t Ds = game_depth[gm];
     const int tid = threadIdx.x;
     int32_t epoch = 0;
@@ -869,26 +888,34 @@ __device__ bool persistent_game(int32_t gm, int32_t rank, int32_t W, const int32
     for (int32_t it = 1; it <= n_iter; it++) {
         for (int half = 0; half < halves; half++) {
             const RuleArgs ru = rule_args(rule, linear, alternating ? 1 << half : 3, t0 + it);
-            // A slot walks its sequence up to the start of its part.  Several workgroups meet at a barrier of about
-            // 2 us between parts, so a part holds all depths that REACH_WALK lets it (slot_ranges); a game's
-            // only workgroup synchronises for less than a walk's first step costs, and every depth is a part.
-            // Measured, FP32, 8 games of one workgroup in which each player moves m times in a row: m = 8 54 us an
-            // iteration against 57 with the longer parts, m = 50 312 against 327 (2,720 when every
-            // slot walked its whole sequence).
-            int32_t S0 = 0;
-            for (int32_t d = 0; d < Ds; d++) {
-                const int32_t *r = gr + d * GR_FIELDS_DEV;
-                const int32_t lo = r[0], hi = r[1] & ~REACH_CUT;
-                if (W == 1 ? d > 0 && lo < hi : (r[1] & REACH_CUT) != 0) {
-                    if (!game_barrier(barrier + gm, W, epoch, err, timeout_ticks)) return false;
-                    S0 = lo;
+            // A game's only workgroup synchronises for less than a walk's first step costs: its pass goes depth by
+            // depth, a lookup per slot.  Several meet at a barrier of about 2 us, so they walk (one_launch_ranges):
+            // once per set, since a thread has many.  Measured, us an iteration: 8 games of one workgroup in which
+            // each player moves m times in a row, FP32, m = 8 49 (57 with a walk per slot or set), m = 50 280 (327 and
+            // 338; 2,730 with whole sequences); game of 7 workgroups and 8 actions in which one move in seven goes
+            // on, FP64, 199 (217 with a walk per slot).
+            if (W == 1) {
+                for (int32_t d = 0; d < Ds; d++) {
+                    const int32_t *r = gr + d * DR_FIELDS;
+                    const int32_t lo = r[0], hi = r[1] & ~REACH_CUT;
+                    if (lo == hi) continue;
+                    for (int32_t q = lo + tid; q < hi; q += BLOCK) a.seq[q] = a.seq[a.slot_par[q]] * a.sigma[q];
+                    __syncthreads();
                 }
-                for (int32_t q = lo + rank * BLOCK + tid; q < hi; q += W * BLOCK)
-                    a.seq[q] = seq_reach<T>(a.slot_par[q], S0, a.slot_par, a.sigma, a.seq) * a.sigma[q];
+            } else {
+                int32_t S0 = 0;
+                for (int32_t d = 0; d < Ds; d++) {
+                    const int32_t *r = gr + d * DR_FIELDS;
+                    if (r[1] & REACH_CUT) {
+                        if (!game_barrier(barrier + gm, W, epoch, err, timeout_ticks)) return false;
+                        S0 = r[0];
+                    }
+                    for (int32_t i = r[8] + rank * BLOCK + tid; i < r[9]; i += W * BLOCK) set_reach<T, MAXA>(i, S0, a);
+                }
             }
             if (!game_barrier(barrier + gm, W, epoch, err, timeout_ticks)) return false;
             for (int32_t d = Ds - 1; d >= 0; d--) {
-                const int32_t *r = gr + d * GR_FIELDS_DEV;
+                const int32_t *r = gr + d * DR_FIELDS;
                 for (int32_t g = r[2] + rank; g < r[3]; g += W) {
                     update_group<T, MAXA, MPT, EXPLICIT, EXT, AF>(g, ru, a, L);
                     __syncthreads();
@@ -1026,7 +1053,7 @@ __global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, i
         };
         int32_t *ranges = w;
         for (int32_t d = tid; d < D; d += BLOCK) {
-            const int32_t *r = gr + d * GR_FIELDS_DEV;
+            const int32_t *r = gr + d * DR_FIELDS;
             ranges[6 * d] = g.grp_iset_off[r[2]];
             ranges[6 * d + 1] = g.grp_iset_off[r[3]];
             for (int k = 0; k < 4; k++) ranges[6 * d + 2 + k] = r[4 + k];
@@ -1065,29 +1092,35 @@ __global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, i
     __syncthreads();
     a.v = v; a.seq = seq; a.sigma = sig; a.R = R; a.sbar = sb; a.pred = pred;
     const int halves = alternating ? 2 : 1;
-    const int32_t *cuts = gr + (D + 1) * GR_FIELDS_DEV;
+    const int32_t *cuts = gr + (D + 1) * DR_FIELDS;
+    // a walk per slot while every slot has a thread, then one per set
+    const bool by_set = A > BLOCK;
     for (int32_t it = 1; it <= n_iter; it++) {
         for (int half = 0; half < halves; half++) {
             const RuleArgs ru = rule_args(rule, linear, alternating ? 1 << half : 3, t0 + it);
             // one part, unless sequences are longer than a walk
-            int32_t S0 = 0;
-            for (int32_t c = 0; c < n_cuts; c++) {
-                const int32_t S1 = cuts[c];
-                for (int32_t q = S0 + tid; q < S1; q += BLOCK)
-                    seq[q] = seq_reach<T>(a.slot_par[q], S0, a.slot_par, sig, seq) * sig[q];
+            auto part = [&](int32_t S0, int32_t S1, int32_t i0, int32_t i1) {
+                if (by_set)
+                    for (int32_t i = i0 + tid; i < i1; i += BLOCK) set_reach<T, MAXA>(i, S0, a);
+                else
+                    for (int32_t q = S0 + tid; q < S1; q += BLOCK)
+                        seq[q] = seq_reach<T>(a.slot_par[q], S0, a.slot_par, sig, seq) * sig[q];
                 __syncthreads();
-                S0 = S1;
+            };
+            int32_t S0 = 0, i0 = 0;
+            for (int32_t c = 0; c < n_cuts; c++) {
+                part(S0, cuts[2 * c], i0, cuts[2 * c + 1]);
+                S0 = cuts[2 * c];
+                i0 = cuts[2 * c + 1];
             }
-            for (int32_t q = S0 + tid; q < A; q += BLOCK)
-                seq[q] = seq_reach<T>(a.slot_par[q], S0, a.slot_par, sig, seq) * sig[q];
-            __syncthreads();
+            part(S0, A, i0, z.I);
             for (int32_t d = D - 1; d >= 0; d--) {
                 int32_t ib, ie, cb, ce, bb, be;
                 if constexpr (STAGED) {
                     const int32_t *r = lv + 6 * d;
                     ib = r[0]; ie = r[1]; cb = r[2]; ce = r[3]; bb = r[4]; be = r[5];
                 } else {
-                    const int32_t *r = gr + d * GR_FIELDS_DEV;
+                    const int32_t *r = gr + d * DR_FIELDS;
                     ib = g.grp_iset_off[r[2]]; ie = g.grp_iset_off[r[3]];
                     cb = r[4]; ce = r[5]; bb = r[6]; be = r[7];
                 }

@@ -73,15 +73,15 @@ struct cfr_handle {
     int32_t n_games = 1;
     std::vector<int64_t> game_slot_base;
     std::vector<int32_t> game_depth, game_range;
-    std::vector<int32_t> slot_range;   // game_range as the one-launch schedules read it
+    std::vector<int32_t> launch_range;   // one_launch_ranges
     std::vector<double> game_pot;
     // persistent schedule
     bool persistent = false;
     // set when a persistent launch stopped part-way (a barrier timed out): the state is partial, so
     // cfr_iterate refuses until cfr_reset starts over
     bool broken = false;
-    // LDS-resident schedule (one tiny game, one workgroup): per-depth ranges on the device, then the first slots
-    // of the reach pass's parts after the first
+    // LDS-resident schedule (one tiny game, one workgroup): per-depth ranges on the device, then the first slot
+    // and set of the reach pass's parts after the first
     bool lds = false;
     int32_t *lds_range = nullptr;
     int32_t lds_cuts = 0;
@@ -682,7 +682,7 @@ static cfr_status build_persistent_plan(cfr_handle *h, int32_t wg_nodes) {
     cfr_status st;
     if ((st = alloc((void **)&pp.tickets, table.size() * sizeof(int4))) != CFR_OK) return st;
     if ((st = alloc((void **)&pp.q_off, P.q_off.size() * sizeof(int32_t))) != CFR_OK) return st;
-    if ((st = alloc((void **)&pp.game_range, h->slot_range.size() * sizeof(int32_t))) != CFR_OK) return st;
+    if ((st = alloc((void **)&pp.game_range, h->launch_range.size() * sizeof(int32_t))) != CFR_OK) return st;
     if ((st = alloc((void **)&pp.game_depth, (size_t)n * sizeof(int32_t))) != CFR_OK) return st;
     // barrier counters of the games, then the queues' claim counters (zeroed together per launch)
     if ((st = alloc((void **)&pp.barrier, ((size_t)n + PERSISTENT_QUEUES) * sizeof(int32_t))) != CFR_OK) return st;
@@ -690,7 +690,7 @@ static cfr_status build_persistent_plan(cfr_handle *h, int32_t wg_nodes) {
     pp.claim = pp.barrier + n;
     HIP_TRY(hipMemcpy(pp.tickets, table.data(), table.size() * sizeof(int4), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(pp.q_off, P.q_off.data(), P.q_off.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(pp.game_range, h->slot_range.data(), h->slot_range.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(pp.game_range, h->launch_range.data(), h->launch_range.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(pp.game_depth, h->game_depth.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice));
     HIP_TRY(hipMemset(pp.err, 0, sizeof(int32_t)));
     {
@@ -954,7 +954,7 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     h->game_slot_base = DL.game_slot_base;
     h->game_depth = DL.game_depth;
     h->game_range = DL.game_range;
-    h->slot_range = slot_ranges(DL);
+    h->launch_range = one_launch_ranges(DL);
     for (int s = 0; s < n; s++) h->game_pot.push_back(games[s].pot);
     h->lc_hand_off = std::move(hand_off);
     h->lc_hand1 = std::move(hand1);
@@ -1668,14 +1668,17 @@ static cfr_status set_lds_schedule(cfr_handle *h) {
     if (prepare_lds(h->g, h->opt.rule, &bytes) != hipSuccess)
         return fail(CFR_EINVAL, "the LDS schedule supports at most 16 actions per information set");
     if (!h->lds_range) {
-        std::vector<int32_t> ranges = h->slot_range;
-        for (size_t d = 0; d < h->slot_range.size() / GR_FIELDS; d++)
-            if (h->slot_range[d * GR_FIELDS + 1] & REACH_CUT) ranges.push_back(h->slot_range[d * GR_FIELDS]);
+        std::vector<int32_t> ranges = h->launch_range;
+        for (size_t d = 0; d < h->launch_range.size(); d += DR_FIELDS)
+            if (h->launch_range[d + 1] & REACH_CUT) {
+                ranges.push_back(h->launch_range[d]);
+                ranges.push_back(h->launch_range[d + 8]);
+            }
         cfr_status st = dev_alloc(h, &h->lds_range, (int64_t)ranges.size());
         if (st != CFR_OK) return st;
         st = upload(h, h->lds_range, ranges.data(), ranges.size());
         if (st != CFR_OK) return st;
-        h->lds_cuts = (int32_t)(ranges.size() - h->slot_range.size());
+        h->lds_cuts = (int32_t)(ranges.size() - h->launch_range.size()) / 2;
     }
     if (h->pexec) { (void)hipGraphExecDestroy(h->pexec); h->pexec = nullptr; }
     if (h->pgraph) { (void)hipGraphDestroy(h->pgraph); h->pgraph = nullptr; }

@@ -95,25 +95,22 @@ int main(int argc, char **argv) {
                 CHECK((F.mem_seq[(size_t)m] >= 0) == (d >= 1));
             }
         }
-    // the one-launch schedules' slot ranges: a game's slots per depth, and parts in which no slot walks more
-    // than REACH_WALK slots up, none of them longer than it could be
-    const std::vector<int32_t> R = slot_ranges(F);
-    CHECK(R.size() == F.game_range.size());
-    int32_t slots = 0;
+    // the one-launch schedules' ranges: a game's slots and sets per depth, but for those whose moves all end the
+    // game, and parts in which no slot walks more than REACH_WALK slots up, none of them longer than it could be
+    const std::vector<int32_t> R = one_launch_ranges(F);
+    CHECK(R.size() / DR_FIELDS == F.game_range.size() / GR_FIELDS);
     for (int s = 0; s < n; s++) {
         std::vector<int32_t> starts(1, 0);
         for (int d = 0; d <= depth[(size_t)s]; d++) {
-            const int32_t *r = &R[((size_t)s * (md + 1) + d) * GR_FIELDS], *old = &F.game_range[((size_t)s * (md + 1) + d) * GR_FIELDS];
+            const int32_t *r = &R[((size_t)s * (md + 1) + d) * DR_FIELDS], *old = &F.game_range[((size_t)s * (md + 1) + d) * GR_FIELDS];
             for (int k = 2; k < GR_FIELDS; k++) CHECK(r[k] == old[k]);
-            const int32_t lo = r[0], hi = r[1] & ~REACH_CUT;
-            CHECK(hi - lo == (d < depth[(size_t)s] ? 2 : 0));
-            CHECK(lo == hi || lo == F.slot_off[(size_t)F.grp_iset_off[(size_t)r[2]]]);
-            slots += hi - lo;
+            const int32_t first = F.grp_iset_off[(size_t)r[2]], end = F.grp_iset_off[(size_t)r[3]];
+            CHECK(end - first == (d < depth[(size_t)s] ? 1 : 0));
+            CHECK(r[8] == first && r[9] == (d < depth[(size_t)s] - 1 ? end : first));
+            CHECK(r[0] == F.slot_off[(size_t)r[8]] && (r[1] & ~REACH_CUT) == F.slot_off[(size_t)r[9]]);
             auto longest = [&](int32_t S0) {
                 int w = 0;
-                for (int32_t q = lo; q < hi; q++) {
-                    int32_t i = 0;
-                    while (F.slot_off[(size_t)i + 1] <= q) i++;
+                for (int32_t i = first; i < end; i++) {
                     int k = 0;
                     for (int32_t p = F.iset_seq[(size_t)i]; p >= S0; k++) {
                         int32_t j = 0;
@@ -126,13 +123,13 @@ int main(int argc, char **argv) {
             };
             if (r[1] & REACH_CUT) {
                 CHECK(longest(starts.back()) == REACH_WALK + 1);
-                starts.push_back(lo);
+                starts.push_back(r[0]);
             }
             CHECK(longest(starts.back()) <= REACH_WALK);
         }
-        CHECK((int)starts.size() == (depth[(size_t)s] + 1) / 2 / (REACH_WALK + 1) + ((depth[(size_t)s] + 1) / 2 % (REACH_WALK + 1) > 0));
+        const int moves = (depth[(size_t)s] + 1) / 2;   // of the first player
+        CHECK((int)starts.size() == moves / (REACH_WALK + 1) + (moves % (REACH_WALK + 1) > 0));
     }
-    CHECK(slots == F.slot_off.back());
     std::printf("ok\n");
     return 0;
 }
