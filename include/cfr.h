@@ -119,8 +119,9 @@ enum { CFR_PRECISION_FP32 = 0, CFR_PRECISION_FP64 = 1 };
  *   LDS         one workgroup per cfr_iterate call running all n iterations of one tiny standalone
  *               game with its whole state in LDS (paper Sec. Results, cross-framework timing: the fixed
  *               launch-and-replay floor per iteration that small games cannot fill):
- *               values, both reach lanes, strategy, regrets, strategy sums (and the PCFR+
- *               prediction) must fit the device's LDS per workgroup, and sets have at most 16
+ *               8 bytes per slot for the strategy sums and, in the state type, three elements per node,
+ *               two per slot (three under PCFR+) and 256 must not exceed the device's LDS per workgroup
+ *               (the kernel needs less; games are admitted by this count), and sets have at most 16
  *               actions; same arithmetic as LEVEL, bitwise equal iterates */
 enum { CFR_SCHEDULE_LEVEL = 0, CFR_SCHEDULE_PERSISTENT = 1, CFR_SCHEDULE_LDS = 2 };
 
@@ -345,8 +346,7 @@ cfr_status cfr_get_game_state(cfr_handle *h, int32_t game, double *regrets, doub
  * [0, n_games)) without reallocating anything, so a captured graph stays valid.  The solver state
  * (regrets, strategy sums, counter) is left alone: call cfr_reset for a fresh solve, or continue
  * from the previous solution.  Both need the handle compiled with options.lifecycle = 1
- * (CFR_ESTATE otherwise), wait for queued work on `stream` to read the host array and return
- * with the rewrite queued on `stream`.
+ * (CFR_ESTATE otherwise) and wait for `stream`: the rewrite is done when they return.
  * cfr_set_payoffs: payoff[num_nodes] in the game description's node numbering (only terminal
  *   entries are read; finite), num_nodes as compiled.
  * cfr_set_root_chance: the root must be a chance node; prob[n] gives its children's probabilities
@@ -361,8 +361,8 @@ cfr_status cfr_set_root_chance(cfr_handle *h, int32_t game, const double *prob, 
  * over the root's children in child order (the joint deal of the two private hands, restricted to the
  * dealt pairs), and the template is rewritten as by cfr_set_root_chance.  r1 [n1], r2 [n2]: host,
  * finite, >= 0, n1 = num_hands1 and n2 = num_hands2 of the description.  CFR_ESTATE without lifecycle
- * records or without the hand map; CFR_EINVAL if W is 0.  Returns with the rewrite queued on
- * `stream` (the host arrays are read before it returns). */
+ * records or without the hand map; CFR_EINVAL if W is 0.  Waits for `stream`: the
+ * rewrite is done when it returns. */
 cfr_status cfr_set_root_ranges(cfr_handle *h, int32_t game, const double *r1, int64_t n1, const double *r2, int64_t n2,
                                void *stream);
 

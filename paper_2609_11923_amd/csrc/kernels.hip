@@ -399,7 +399,7 @@ struct GroupLds {
 //   r(I,a) = sum_h s_i pi_{-i}(h) (v(h.a) - v(h)), then R <- R + r (CFR+: max(R, 0)),
 //   sbar += w_t pi_i(I) sigma^t (FP64), sigma^{t+1} = regret matching of R.
 // Only this group reads sigma(I) during the backward pass (all members of I are here), and the
-// forward pass has already consumed it, so overwriting sigma(I) with sigma^{t+1} is safe.
+// reach pass has already consumed it, so overwriting sigma(I) with sigma^{t+1} is safe.
 // Sets with more members than a chunk are streamed through LDS chunk by chunk.  Must be called by
 // every thread of the block (it synchronises the block).
 template <typename T, int MAXA, int MPT, bool EXPLICIT, bool EXT>
@@ -1093,7 +1093,8 @@ __global__ void __launch_bounds__(BLOCK) k_lds(const int32_t *__restrict__ gr, i
     a.v = v; a.seq = seq; a.sigma = sig; a.R = R; a.sbar = sb; a.pred = pred;
     const int halves = alternating ? 2 : 1;
     const int32_t *cuts = gr + (D + 1) * DR_FIELDS;
-    // a walk per slot while every slot has a thread, then one per set
+    // a walk per slot while every slot has a thread, then one per set (FP32, us an iteration: Kuhn's 24 slots 3.9
+    // and 4.1; 1,696 slots of a 16-action game in which one move in ten goes on 35 and 27)
     const bool by_set = A > BLOCK;
     for (int32_t it = 1; it <= n_iter; it++) {
         for (int half = 0; half < halves; half++) {

@@ -61,10 +61,15 @@ constexpr float LOG_CUT = -30.f;  // below: log softplus(z) = z, sigmoid(z) / so
 //
 // Tiles (by rows, see rows_tile): 32 rows, one wave per 32 units, for up to 8,192 rows -- there a launch
 // has at most a block per compute unit, so the shortest chain per block wins -- and 128 rows beyond, whose
-// weight reads (0.3 MB per tile in inference) are shared by more rows.  In inference four waves of
+// weight reads (0.3 MB per tile in inference) are shared by more rows.  The line is where the small tile's blocks
+// begin to double up, below where the two tiles cost the same.  Both on both sides, us of a call or training step,
+// small / large tile: 128 -> 3 x 256 -> 4, inference 8,192 rows 11.4 / 18.2, 10,240 16.0 / 18.2, 16,384
+// 16.5 / 18.4, 20,480 21.5 / 18.6, 65,536 51.6 / 24.7; training 8,192 70 / 105, 16,384 103 / 131, 32,768 186 / 185.
+// 64 -> 3 x 64 -> 4, inference 4,096 8.1 / 7.2, 8,192 8.2 / 7.2, 10,240 9.5 / 7.4; training 8,192 52 / 86,
+// 32,768 115 / 143.  In inference four waves of
 // up to 4 x 2 tiles (half an LDS read and a quarter of a KB of weights per MFMA) leave room for two blocks per
 // compute unit, which hide each other's loads, stores and output layers.
-// Measured: 240,930 rows through 128 -> 3 x 256 -> 4, 377 -> 86 us (920 TFLOP/s; its products alone at the rate of
+// Measured: 240,930 rows through 128 -> 3 x 256 -> 4, 377 -> 87 us (920 TFLOP/s; its products alone at the rate of
 // a large library GEMM: 66 us).  A training step on 4,096 rows, 190 -> 60 us (23 launches before): this
 // kernel 39, k_wgrad 12, k_finish 9.
 //

@@ -291,7 +291,7 @@ static GroupRecords group_records(const DeviceLayout &D) {
     return R;
 }
 
-// Per-launch event timing for cfr_profile: class 0 tick, 1 forward, 2 level.
+// Per-launch event timing for cfr_profile: class 0 tick, 1 reach, 2 level.
 struct LaunchTimer {
     std::vector<hipEvent_t> ev;   // pairs (before, after)
     std::vector<int> cls;
@@ -1286,7 +1286,8 @@ cfr_status cfr_set_active(cfr_handle *h, const uint8_t *active, int32_t n, void 
 // game whose levels take 4 us.  With one iteration per graph a handle that has replayed RUN_AFTER of them
 // also captures RUN_ITERS in a row: an iteration of Leduc with 3 ranks in FP64 then takes 42 us instead
 // of 48 (41.5 at ten and at forty per graph).  The capture costs what about RUN_AFTER gaps do, so a
-// handle used once or retiring games between a few iterations does not pay for it.
+// handle used once or retiring games between a few iterations does not pay for it.  A call of fewer than
+// RUN_ITERS iterations replays single ones.
 constexpr int RUN_ITERS = 5, RUN_AFTER = 32;
 
 cfr_status cfr_iterate(cfr_handle *h, int64_t n, void *stream) {
@@ -1663,8 +1664,8 @@ static cfr_status set_lds_schedule(cfr_handle *h) {
     HIP_TRY(hipDeviceGetAttribute(&limit, hipDeviceAttributeMaxSharedMemoryPerBlock, h->opt.device));
     h->g.lds_limit = limit;
     if (bytes > (size_t)limit)
-        return fail(CFR_EINVAL, "the game needs " + std::to_string(bytes) + " bytes of LDS for the LDS schedule; "
-                                "a workgroup has " + std::to_string(limit));
+        return fail(CFR_EINVAL, "the LDS schedule counts " + std::to_string(bytes) + " bytes of LDS for the game "
+                                "(cfr.h says how); a workgroup has " + std::to_string(limit));
     if (prepare_lds(h->g, h->opt.rule, &bytes) != hipSuccess)
         return fail(CFR_EINVAL, "the LDS schedule supports at most 16 actions per information set");
     if (!h->lds_range) {
