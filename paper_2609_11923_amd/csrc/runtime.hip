@@ -17,8 +17,10 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <memory>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -153,7 +155,8 @@ struct cfr_handle {
     std::vector<Layout> layouts;
 };
 
-// fn(s) for s in [0, n) on up to 16 host threads (one game each at a time); fn must touch only game s.
+// fn(s) for s in [0, n) on up to 16 host threads (one game each at a time); fn must touch only game s.  What fn
+// throws first is thrown here once all threads are done.
 template <typename F>
 static void parallel_games(int n, F &&fn) {
     const int hw = (int)std::thread::hardware_concurrency();
@@ -163,13 +166,24 @@ static void parallel_games(int n, F &&fn) {
         return;
     }
     std::atomic<int> next{0};
+    std::atomic<bool> failed{false};
+    std::exception_ptr error;
+    auto work = [&]() {
+        try {
+            for (int s = next.fetch_add(1); s < n && !failed; s = next.fetch_add(1)) fn(s);
+        } catch (...) {
+            if (!failed.exchange(true)) error = std::current_exception();
+        }
+    };
     std::vector<std::thread> pool;
     pool.reserve((size_t)nt);
-    for (int k = 0; k < nt; k++)
-        pool.emplace_back([&]() {
-            for (int s = next.fetch_add(1); s < n; s = next.fetch_add(1)) fn(s);
-        });
+    try {
+        for (int k = 1; k < nt; k++) pool.emplace_back(work);
+    } catch (const std::system_error &) {   // fewer threads then
+    }
+    work();
     for (auto &t : pool) t.join();
+    if (error) std::rethrow_exception(error);
 }
 
 // The affine update's group headers, set records and member records (DevGame).  A group keeps its members
@@ -941,7 +955,8 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
                 lc.node[(size_t)j] = lo + (lc.node[(size_t)j] - lc.depth_off[s][(size_t)d]);
             }
     }
-    cfr_handle *h = new cfr_handle();
+    std::unique_ptr<cfr_handle, decltype(&free_handle)> owner(new cfr_handle(), &free_handle);
+    cfr_handle *h = owner.get();
     h->opt = o;
     h->use_graph = o.use_graph != 0;
     h->depth_off = DL.depth_off;
@@ -977,7 +992,7 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     GroupRecords rec;
     if (g.affine) rec = group_records(DL);
 
-#define ALLOC(ptr, cnt) do { st = dev_alloc(h, &(ptr), (cnt)); if (st != CFR_OK) { free_handle(h); return st; } } while (0)
+#define ALLOC(ptr, cnt) do { st = dev_alloc(h, &(ptr), (cnt)); if (st != CFR_OK) return st; } while (0)
     ALLOC(g.kid_off, N + 1);
     if (g.explicit_kids) ALLOC(g.kid, E);
     if (!h->slot_map.empty()) ALLOC(g.slot_map, A);
@@ -1026,10 +1041,8 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
         ALLOC(p, A + SEQ_FRONT);
         g.seqbar = p + SEQ_FRONT;
     }
-    if (hipHostMalloc((void **)&h->roots, sizeof(double) * 3 * (size_t)n) != hipSuccess) {
-        free_handle(h);
+    if (hipHostMalloc((void **)&h->roots, sizeof(double) * 3 * (size_t)n) != hipSuccess)
         return fail(CFR_ENOMEM, "pinned host allocation failed");
-    }
     ALLOC(g.slot_kids, A);
     ALLOC(g.chance_kids, (int64_t)DL.chance_kids.size());
     ALLOC(g.bigc_kids, (int64_t)DL.bigc_kids.size());
@@ -1040,7 +1053,7 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
 #undef ALLOC
     h->I_canon = I;
     h->R_base = (char *)g.R; h->sbar_base = (char *)g.sbar; h->sigma_base = (char *)g.sigma;
-#define UP(dst, src) do { st = upload(h, dst, (src).data(), (src).size()); if (st != CFR_OK) { free_handle(h); return st; } } while (0)
+#define UP(dst, src) do { st = upload(h, dst, (src).data(), (src).size()); if (st != CFR_OK) return st; } while (0)
     UP(g.kid_off, DL.kid_off);
     if (g.explicit_kids) UP(g.kid, DL.kid);
     if (g.slot_map) UP(g.slot_map, h->slot_map);
@@ -1117,7 +1130,7 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
         h->active.assign((size_t)ng, 1);
         for (auto *v : {&h->grp_off, &h->chance_off_l, &h->bigc_off_l}) v->assign((size_t)MD + 2, 0);
         h->reach_off.assign(h->reach_slot.size(), 0);
-#define BA(ptr, cnt) do { st = dev_alloc(h, &(ptr), (cnt)); if (st != CFR_OK) { free_handle(h); return st; } } while (0)
+#define BA(ptr, cnt) do { st = dev_alloc(h, &(ptr), (cnt)); if (st != CFR_OK) return st; } while (0)
         BA(g.reach_list, std::max<int64_t>((int64_t)h->reach_games.size(), 1));
         BA(g.grp_list, std::max<int64_t>(g.G, 1));
         BA(g.chance_list, std::max<int64_t>((int64_t)DL.chance_node.size(), 1));
@@ -1134,7 +1147,7 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
         const int64_t nt = (int64_t)lc.node.size(), nr = (int64_t)lc.root.size();
         int64_t maxn = 1;
         for (int64_t v : lc.nodes) maxn = std::max(maxn, v);
-#define LA(ptr, cnt) do { st = dev_alloc(h, &(ptr), (cnt)); if (st != CFR_OK) { free_handle(h); return st; } } while (0)
+#define LA(ptr, cnt) do { st = dev_alloc(h, &(ptr), (cnt)); if (st != CFR_OK) return st; } while (0)
         LA(h->lc_node, nt); LA(h->lc_in, nt); LA(h->lc_branch, nt); LA(h->lc_u, nt); LA(h->lc_pic, nt);
         LA(h->lc_root, nr); LA(h->lc_stage, maxn);
         std::vector<int2> hands;
@@ -1157,9 +1170,9 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
         if (g.fp64) { UP((double *)g.seq - 1, oned); } else { UP((float *)g.seq - 1, onef); }
         UP(g.seqbar - 1, oned);
         st = end_gathering(h);
-        if (st != CFR_OK) { free_handle(h); return st; }
+        if (st != CFR_OK) return st;
         hipError_t e = hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking);
-        if (e != hipSuccess) { free_handle(h); return fail(CFR_EDEVICE, std::string("setup: ") + hipGetErrorString(e)); }
+        if (e != hipSuccess) return fail(CFR_EDEVICE, std::string("setup: ") + hipGetErrorString(e));
     }
 #undef UP
     build_plan(h);
@@ -1171,22 +1184,31 @@ static cfr_status compile_games(const cfr_game_desc *games, int n, const cfr_opt
     }
     if (o.persistent != CFR_SCHEDULE_LEVEL) {
         st = cfr_set_schedule(h, o.persistent, o.wg_nodes);
-        if (st != CFR_OK) { free_handle(h); return st; }
+        if (st != CFR_OK) return st;
     }
     st = cfr_reset(h);
-    if (st != CFR_OK) { free_handle(h); return st; }
+    if (st != CFR_OK) return st;
     if (o.keep_layout) h->layouts = std::move(kept);
-    *out = h;
+    *out = owner.release();
     return CFR_OK;
+}
+
+// compile_games, with what it throws (host memory) as a status: no exception leaves the C boundary
+static cfr_status compile_status(const cfr_game_desc *games, int n, const cfr_options *opt, cfr_handle **out) {
+    try {
+        return compile_games(games, n, opt, out);
+    } catch (const std::exception &e) {
+        return fail(CFR_ENOMEM, std::string("host compile failed: ") + e.what());
+    }
 }
 
 cfr_status cfr_compile(const cfr_game_desc *game, const cfr_options *opt, cfr_handle **out) {
     if (!game) return fail(CFR_EINVAL, "game description is NULL");
-    return compile_games(game, 1, opt, out);
+    return compile_status(game, 1, opt, out);
 }
 
 cfr_status cfr_compile_batch(const cfr_game_desc *games, int32_t n, const cfr_options *opt, cfr_handle **out) {
-    return compile_games(games, n, opt, out);
+    return compile_status(games, n, opt, out);
 }
 
 cfr_status cfr_batch_size(cfr_handle *h, int32_t *n_games, int64_t *slot_base) {
