@@ -62,8 +62,9 @@ def test_slot_counts(sets, actions, rule, order):
     assert all(np.array_equal(x, y) for x, y in zip((*a.state(), a.strategy()), (*b.state(), b.strategy())))
 
 
-@pytest.mark.parametrize("actions,depth", [(6, 3), (5, 6)])
-def test_small_groups_cost_no_more_than_child_lists(actions, depth):
+# bars half way between the sixteen-round slot pass (1.22 and 1.10 times the child lists) and this one (1.03 and 0.94)
+@pytest.mark.parametrize("actions,depth,bar", [(6, 3, 1.13), (5, 6, 1.02)])
+def test_small_groups_cost_no_more_than_child_lists(actions, depth, bar):
     """The affine update reads less than the child-list update and must not take longer on groups of few slots."""
     game = tree(actions, depth)
     solvers = [cfr.Solver(game, affine=f) for f in (True, False)]
@@ -76,4 +77,4 @@ def test_small_groups_cost_no_more_than_child_lists(actions, depth):
             torch.cuda.synchronize()
             best[k] = min(best[k], (time.perf_counter() - t) * 1e4)
     print(f"[many actions] {actions}^{depth}: affine {best[0]:.2f} us, child lists {best[1]:.2f} us", flush=True)
-    assert best[0] <= 1.08 * best[1]
+    assert best[0] <= bar * best[1]
